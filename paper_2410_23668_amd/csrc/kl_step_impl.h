@@ -2943,10 +2943,14 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
     if (garrive >= 0) bar_arrive(P, garrive, ti);
 }
 
-// The final residual stream -> hidden_out (fp32).
+// The final residual stream -> hidden_out (fp32), elements spread over the
+// grid, threads tid = 0 .. nt - 1 of every workgroup.  (One memory round trip;
+// by one workgroup alone the copy is a chain of B H / kThreads of them, which
+// ended 130 us after the rest of the head at the 8B shape and batch 32, 280 us
+// at the 70B shape.)
 template <bool PS>
-__device__ __forceinline__ void copy_hidden(const StepParams &P) {
-    for (int idx = kl_tid(); idx < P.B * P.H; idx += kThreads) {
+__device__ __forceinline__ void copy_hidden(const StepParams &P, int tid, int nt) {
+    for (int idx = blockIdx.x * nt + tid; idx < P.B * P.H; idx += P.nwg * nt) {
         const int b = idx / P.H;
         const float x = from_fix((long long)ld_dev_u64(P.xf + (size_t)b * P.Hp + idx % P.H));
         P.hidden_out[idx] = ok_of<PS>(P, b) ? x : __builtin_nanf("");
@@ -2977,11 +2981,17 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
         }
         __syncthreads();
     };
+    // per-sequence path: the control wave copies the hidden state once the
+    // compute waves are busy with the product
+    auto hidden = [&]() {
+        if (P.hidden_out && (kl_tid() >> 6) == kCtlWave)
+            copy_hidden<!BAT>(P, kl_tid() & 63, 64);
+    };
     weight_phase<BAT>(
         P, S, reinterpret_cast<const uint8_t *>(P.lm_head), P.Hp / kTileK, R.first, R.count,
         [&]() {
             if (gwait >= 0) bar_wait(P, gwait, ti);
-            if (!BAT && blockIdx.x == 0 && P.hidden_out) copy_hidden<!BAT>(P);
+            if (!BAT && R.count == 0) hidden();   // (no rows: nothing is staged)
         },
         [&]() {
             // (folds the last down projection's partials, x: xf2 -> xf), and
@@ -2991,7 +3001,7 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
             __syncthreads();
             rms_table(P, S);
             if (is_ctl_lane0()) trace_stamp(P, ti, 3);
-            if (blockIdx.x == 0 && P.hidden_out) copy_hidden<!BAT>(P);
+            if (P.hidden_out) copy_hidden<!BAT>(P, kl_tid(), kThreads);
         },
         [&](int b) {
             if (P.multi) {
@@ -3002,6 +3012,7 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
                 stage_rms_deferred(P.xf + (size_t)b * P.Hp, P.final_norm, P.H, P.Hp, S.a, S.sm);
             }
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
+            if (b == 0) hidden();
         },
         [&](int c, int b0, int nb, uint16_t *buf) { stage_act_chunk(P, c, b0, nb, buf); },
         [&](int b, int r, float y0, float y1) {
