@@ -193,9 +193,9 @@ void lds_layout_for(kl_state &s) {
         s.lds_bar = s.lds_sm + 64;
         // + the step's epoch, position and validity per sequence, the head's
         // argmax keys of a group of sequences, the experts and their weights
-        // per sequence (two slots)
+        // per sequence (two slots), the workgroup's share of the attention
         s.lds_bytes = (s.lds_bar + 2 * kBarGroups + 4 + 2 * kMfmaBatch + 2 * kGemmBatch +
-                       4 * kMfmaBatch) * (int)sizeof(float);
+                       4 * kMfmaBatch + 8) * (int)sizeof(float);
     };
     layout(c.max_batch >= 2);
     if (s.multi_ok && s.lds_bytes > 160 * 1024 - 256) layout(false);
@@ -211,8 +211,8 @@ void lds_layout_for(kl_state &s) {
 //     kMfmaBatch - 1 sequences): rotated queries [B][nq d], the new key and
 //     value [B][nkv][d], chunk results [B][nkv][group][C][d + 2], the SwiGLU
 //     output [B][Fp];
-//   the matrix-core path's rotated queries [B][nq d] and attention chunk
-//     partials: outputs [B nkv C][group][d], (max, sum) pairs;
+//   the matrix-core path's rotated queries [B][nq d] (its split sequences'
+//     attention results take the chunk results' place: one per workgroup);
 //   the matrix-core path's two-term bf16 activations (both terms, [B][Hp],
 //     [B][Fp], [B][nq d]);
 //   on the matrix-core path also: the second residual buffer, the fp32 K-slice
@@ -223,7 +223,7 @@ struct ScratchPlan {
     int B;
     bool batched;
     size_t off_bar, off_cnt, off_cnt_end;
-    size_t off_x, off_q, off_po, off_ps, off_act, off_actm, off_acto;
+    size_t off_x, off_q, off_act, off_actm, off_acto;
     size_t off_qll, off_kvll, off_poll, off_mll;
     size_t off_x2, off_xp, off_gp, off_ss;
     size_t total;
@@ -246,7 +246,6 @@ ScratchPlan plan_scratch(const kl_state &S, int B) {
     p.off_bar = take(kBarBytes);
     p.off_cnt = take((size_t)(2 * nkv + S.Sc + norm_cnts) * 4);
     p.off_cnt_end = so;
-    const size_t items = (size_t)nkv * std::max(B, S.Sg);   // >= B * nkv * C for this batch
     p.off_x = take((size_t)B * S.Hp * 8);
     const int bl = std::min(B, S.batched_from - 1);           // per-sequence steps
     const size_t items_ll = (size_t)nkv * std::max(bl, S.Sg);
@@ -256,8 +255,6 @@ ScratchPlan plan_scratch(const kl_state &S, int B) {
     const int topk = c.n_experts > 1 ? c.top_k : 1;          // expert slots per token
     p.off_mll = take((size_t)bl * topk * S.Fp * 8);
     p.off_q = take((size_t)B * c.n_heads * d * 4);
-    p.off_po = take(items * g * d * 4);
-    p.off_ps = take(items * g * 2 * 4);
     p.off_act = take((size_t)B * S.Hp * 2 * 2);
     p.off_actm = take((size_t)B * S.Fp * 2 * 2);
     p.off_acto = take((size_t)B * S.Ap * 2 * 2);
@@ -284,8 +281,6 @@ void bind_scratch(StepParams &P, uint8_t *base, const ScratchPlan &p, const kl_s
     P.kv_ll = reinterpret_cast<unsigned long long *>(base + p.off_kvll);
     P.po_ll = reinterpret_cast<unsigned long long *>(base + p.off_poll);
     P.m_ll = reinterpret_cast<unsigned long long *>(base + p.off_mll);
-    P.part_o = reinterpret_cast<float *>(base + p.off_po);
-    P.part_s = reinterpret_cast<float *>(base + p.off_ps);
     P.act = reinterpret_cast<uint16_t *>(base + p.off_act);
     P.act_lo = P.act + (size_t)B * S.Hp;
     P.actm = reinterpret_cast<uint16_t *>(base + p.off_actm);
@@ -323,20 +318,18 @@ void free_state(kl_state *s) {
 //   matrix-core path, single phases:
 //     qkv       its product's grid barrier before the fold, and the RMSNorm
 //               slice counters;
-//     oproj     with several attention chunks, the merge's grid barrier;
 //     gateup    the RMSNorm slice counters;
 //     down      the SwiGLU fold's grid barrier;
 //     head      the final RMSNorm's slice counters;
-//     attn      none (its counters were completed by the qkv launch);
+//     attn      the parts of a sequence split over workgroups;
+//     oproj     none;
 //   per-sequence path, single phases: none (every counter a phase waits on
 //   belongs to an earlier phase).
-bool launch_waits_inside(int phases, bool batched, int C) {
+bool launch_waits_inside(int phases, bool batched) {
     if (phases & kPhEmbed) return phases != kPhEmbed;
     if (__builtin_popcount((unsigned)phases) > 1) return true;
     if (!batched) return false;
-    if (phases == kPhAttn) return false;
-    if (phases == kPhOproj) return C > 1;
-    return true;
+    return phases != kPhOproj;
 }
 
 StepParams base_params(const kl_state &s) {
@@ -685,16 +678,16 @@ static hipError_t launch_schedule(const StepParams &P, int32_t mode, int lds, hi
     e = launch_step(P, 0, 0, kPhEmbed, false, lds, s);
     if (mode == KL_MODE_PER_LAYER) {
         for (int l = 0; l < L && e == hipSuccess; ++l)
-            e = launch_step(P, l, l + 1, kPhLayer, launch_waits_inside(kPhLayer, bat, P.C), lds, s);
+            e = launch_step(P, l, l + 1, kPhLayer, launch_waits_inside(kPhLayer, bat), lds, s);
     } else {
         const int ops[] = {kPhQkv, kPhAttn, kPhOproj, kPhGateUp, kPhDown};
         for (int l = 0; l < L && e == hipSuccess; ++l)
             for (int ph : ops)
                 if (e == hipSuccess)
-                    e = launch_step(P, l, l + 1, ph, launch_waits_inside(ph, bat, P.C), lds, s);
+                    e = launch_step(P, l, l + 1, ph, launch_waits_inside(ph, bat), lds, s);
     }
     if (e == hipSuccess)
-        e = launch_step(P, 0, 0, kPhHead, launch_waits_inside(kPhHead, bat, P.C), lds, s);
+        e = launch_step(P, 0, 0, kPhHead, launch_waits_inside(kPhHead, bat), lds, s);
     return e;
 }
 
@@ -723,11 +716,11 @@ static kl_status launch_layer_graph(kl_state *st, const StepParams &P, hipStream
         for (int l = 0; l < P.L; ++l) {
             prev = node;
             HIP_TRY(add_step_node(st->graph, &node, &prev, P, l, l + 1, kPhLayer,
-                                  launch_waits_inside(kPhLayer, bat, P.C), lds));
+                                  launch_waits_inside(kPhLayer, bat), lds));
         }
         prev = node;
         HIP_TRY(add_step_node(st->graph, &node, &prev, P, 0, 0, kPhHead,
-                              launch_waits_inside(kPhHead, bat, P.C), lds));
+                              launch_waits_inside(kPhHead, bat), lds));
         HIP_TRY(hipGraphInstantiate(&st->graph_exec, st->graph, nullptr, nullptr, 0));
         for (int i = 0; i < 10; ++i) st->graph_key[i] = key[i];
     }

@@ -19,7 +19,6 @@ constexpr int kOEarly = 4;               // O projection: waves that gather the 
 constexpr int kRgBatch = 16;              // row groups reduced per LDS round
 constexpr int kAttnLoads = 5;             // K (and V) loads per lane per sub-chunk, short attention chunks
 constexpr int kAttnRing = 4;              // K (and V) slabs in flight per wave, streaming attention
-constexpr int kCombBatch = 32;            // chunk partials loaded together when merging
 // Batched steps (the matrix-core path) run the weight products on the matrix
 // cores.  An activation x enters them as two bf16 terms, hi = bf16(x) and
 // lo = bf16(x - hi), both multiplied into the same fp32 accumulators (about
@@ -118,8 +117,6 @@ struct StepParams {
     float *ssp;                // batched path: sums of squares of the last RMSNorm step's
                                // rows per kGemmChunkK columns [max_batch][ceil(Hp / chunk)]
     float *q;                  // batched path: [B][nq*d] rotated queries
-    float *part_o;             // batched path: attention chunk outputs [B*nkv*C][group*d]
-    float *part_s;             // batched path: attention chunk (max, sum) [B*nkv*C][group][2]
     // per-sequence path (batch below the model's matrix-core batch): values handed between
     // workgroups as tagged words (value in the low 32 bits, the tag of the
     // writing step and layer in the high 32 bits)
@@ -129,6 +126,7 @@ struct StepParams {
     unsigned long long *kv_ll; // [B][nkv][d]: new key (d/2 words: bf16 dims i, i + d/2),
                                // then new value (d/2 words: bf16 dims 2j, 2j + 1)
     unsigned long long *po_ll; // [B][nkv][group][C][d + 2]: chunk outputs, then max and sum
+                               // (batched path: [nkv][Sg][group][d + 2], max in log2 units)
     unsigned long long *m_ll;  // [B][Fp] SwiGLU output (fp32)
     // batched path: activations as bf16 hi and lo terms (hi + lo ~ the fp32 value)
     uint16_t *act, *act_lo;    // [max_batch][Hp] normalised activations

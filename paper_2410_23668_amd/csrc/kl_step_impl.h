@@ -279,6 +279,7 @@ __device__ __forceinline__ unsigned long long *bar_counter(const StepParams &P, 
 // At launch start: the barrier bases of this launch and the step's first tag
 // of the tagged hand-offs, into LDS (before any wait; any wave may do it).
 __device__ __forceinline__ unsigned *launch_epoch(const StepParams &P);
+__device__ __forceinline__ void seg_init(const StepParams &P, int lane);
 __device__ __forceinline__ void bar_init(const StepParams &P) {
     // Only this workgroup's own group counter is read: that group cannot
     // complete barrier 0 before this workgroup arrives, so the value rounds
@@ -294,6 +295,8 @@ __device__ __forceinline__ void bar_init(const StepParams &P) {
     } else if (t == 64) {
         *launch_epoch(P) = __hip_atomic_load(P.epoch_ptr, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
+    } else if (P.batched && t >= 128 && t < 192) {
+        seg_init(P, (int)t - 128);
     } else if (t >= 96 && t < 96 + kMfmaBatch && !P.batched) {
         const int b = (int)t - 96;
         if (b < P.B) {
@@ -358,9 +361,8 @@ __device__ __forceinline__ void spin_until(const StepParams &P, Done &&done) {
              KL_DEVERR_BARRIER))
             return;
         if (spins >= kSpinLimit) {
-            if ((kl_tid() & 63) == 0)
-                __hip_atomic_fetch_or(P.err, KL_DEVERR_BARRIER, __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_or(P.err, KL_DEVERR_BARRIER, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
             return;
         }
     }
@@ -1285,12 +1287,6 @@ __device__ __forceinline__ void gemm_rows(const uint8_t *__restrict__ W, int KT,
 //   cnt_qkv[g]     qkv -> attn: the workgroups of KV head g compute exactly
 //                  the q/k/v rows of that head, so the attention of head g
 //                  waits only for them (Sg arrivals per layer).
-//   cnt_attn[g]    attn -> oproj: the chunk results of KV head g (B * C per
-//                  layer), then (GEMV path, up to 4 query heads per KV head)
-//                  one more arrival once the workgroup that delivered the
-//                  last of them has merged them;
-//                  head g's workgroups then apply the O-projection columns of
-//                  head g to the merged output, adding into the residual.
 //   cnt_gu[j]      gateup -> down: column block j of the FFN (Rc workgroups
 //                  compute its SwiGLU values; the same Rc workgroups then
 //                  apply the matching columns of the down projection).
@@ -1498,36 +1494,6 @@ __device__ __forceinline__ void stage_bf16_chunk(const uint16_t *src, const uint
                                                  uint16_t *buf) {
     const int k0 = c * kGemmChunkK;
     ctl_copy_rows(src, src_lo, ld, k0, min(kGemmChunkK, K - k0), b0, nb, buf);
-}
-
-// Batched path, several attention chunks per (sequence, KV head): the merged
-// attention output o_h = sum_c w_ch A_ch / sum_c w_ch L_ch, w_ch =
-// exp(M_ch - M_h) (Sec. 2 attention, split over the context), as the two
-// bf16 terms the O projection stages; elements spread over the grid.  Ends
-// with grid barrier k.
-template <int D, int G>
-__device__ __forceinline__ void merge_batched(const StepParams &P, int k) {
-    const int C = P.C, n = P.nq * D, total = P.B * n;
-    for (int e = blockIdx.x * kThreads + kl_tid(); e < total; e += P.nwg * kThreads) {
-        const int b = e / n, j = e % n, h = j / D, g = h / G, hl = h % G, dd = j % D;
-        const size_t item0 = ((size_t)b * P.nkv + g) * C;
-        float M = -INFINITY;
-        for (int cc = 0; cc < C; ++cc)
-            M = fmaxf(M, ld_dev(P.part_s + ((item0 + cc) * G + hl) * 2));
-        float num = 0.f, den = 0.f;
-        for (int cc = 0; cc < C; ++cc) {
-            const float m = ld_dev(P.part_s + ((item0 + cc) * G + hl) * 2);
-            const float w = (m == -INFINITY) ? 0.f : expf(m - M);
-            num = fmaf(ld_dev(P.part_o + (item0 + cc) * G * D + hl * D + dd), w, num);
-            den = fmaf(ld_dev(P.part_s + ((item0 + cc) * G + hl) * 2 + 1), w, den);
-        }
-        uint16_t hi, lo;
-        split_bf16(num / den, hi, lo);
-        st_dev_u16(P.acto + (size_t)b * n + j, hi);
-        st_dev_u16(P.acto_lo + (size_t)b * n + j, lo);
-    }
-    bar_arrive(P, k, -1);
-    bar_wait(P, k, -1);
 }
 
 // Embedding block (Sec. 2): x = E[token] (exact in fixed point).  Workgroup 0
@@ -2102,8 +2068,8 @@ __device__ __forceinline__ void attn_item_ll(KArg ka, int l, int b, int g, int c
 }
 
 
-// Streaming attention item (batched path, where an item is a whole sequence
-// or a long chunk of one): each compute
+// Streaming attention item (per-sequence path with 8 query heads per KV
+// head): each compute
 // wave streams its own slabs of the chunk (slabs w, w + kWaves, ...; a slab
 // is PP positions, one 16-byte load per lane) through a ring of kAttnRing K
 // and kAttnRing V loads that is refilled as it is consumed, and each lane
@@ -2114,33 +2080,16 @@ __device__ __forceinline__ void attn_item_ll(KArg ka, int l, int b, int g, int c
 // in log2 units, so every weight is one hardware exp2).  No block barrier in
 // the loop: the PP lane groups of a wave are merged by shuffles, the waves in
 // order through LDS.  The queries are held in registers.  The new slot
-// (written this step by another workgroup) is read after the wait with
-// device-coherent loads into LDS and taken from there; its ring load targets
-// a shared dummy line.  Outputs as attn_item's batched path: the chunk's
-// (max, sum, unnormalised output), and the normalised output when the item is
-// the whole sequence.
-template <int D, int G, bool LL>
-__device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, int c, bool first,
-                                                 int ti) {
+// (written this step by another workgroup) arrives as tagged words and is
+// taken from LDS; its ring load targets a shared dummy line.  Outputs: the
+// chunk's (max, sum, unnormalised output) as tagged words.
+template <int D, int G>
+__device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, int c, int ti) {
     const StepParams P = load_params(ka);
     const Lds S = lds_layout(kl_smem, P);
     constexpr int LP = D / 8;                       // lanes per position
     constexpr int PP = 64 / LP;                     // positions per slab
     constexpr int R = kAttnRing;
-    // Batched path, D = 128: the scores of a ring round (R slabs of PP
-    // positions, 16 rows) are one v_mfma_f32_16x16x32_bf16 tile per 32
-    // columns, the K rows as A and the team's queries (scaled, as two bf16
-    // terms) as B.  The K ring then holds A-operand pieces: load ks of a
-    // round is columns 32 ks + 8 (l / 16) .. + 7 of tile row l % 16 (slab
-    // (l % 16) / PP, position (l % 16) % PP).  The tile goes through a
-    // per-wave LDS slot to the lanes of its positions; the softmax and the
-    // values stay on the vector units.  (Step time, same device: 8B shape,
-    // batch 32, 8.07 -> 7.97 ms; 70B shape, batch 32, 47.1-47.8 -> 46.3-46.7
-    // ms.  The per-sequence path's chunks are a few rounds long, where the
-    // vector-unit scores measured faster: 70B shape, batch 1, 23.8 against
-    // 24.2 ms.)
-    constexpr bool MC = D == 128 && !LL;
-    static_assert(!MC || (R * PP == 16 && R * 32 == D), "one 16-row tile per ring round");
     // more than 4 query heads per KV head: the waves split into NH teams of
     // HG heads each; every team streams the whole chunk (the second team's
     // loads of the same lines meet them in L2)
@@ -2151,7 +2100,7 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
     const int h0 = team * HG;                      // the team's first query head
     const int lane = kl_tid() & 63;
     const int pi = lane / LP, ds = (lane % LP) * 8;
-    const int pnew = pos_of<LL>(P, b), n = pnew + 1;
+    const int pnew = pos_of<true>(P, b), n = pnew + 1;
     int s0, s1;
     split_range((n + PP - 1) / PP, P.C, c, s0, s1);
     const bool compute = wid < kWaves;
@@ -2164,7 +2113,6 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
     float *wacc = wl + kWaves * HG;                      // [kWaves][HG][D] wave outputs
     uint16_t *kn = reinterpret_cast<uint16_t *>(wacc + kWaves * HG * D);  // [D] new key
     uint16_t *vn = kn + D;                                                // [D] new value
-    float *stile = reinterpret_cast<float *>(vn + D) + min(wid, kWaves - 1) * 256;   // [16][16]
     const size_t row0 = kv_row(P, l, b, g);
     const uint16_t *Kb = P.kc + row0 * D + ds;
     const uint16_t *Vb = P.vc + row0 * D + ds;
@@ -2176,15 +2124,6 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
     // new position loads the dummy line (zeros)
     u32x4 kr[R], vr[R];
     auto pos_of_item = [&](int i) { return (s0 + tw + i * TW) * PP + pi; };
-    // MC: this lane's tile row (slab ksl, position kpi) and columns
-    const int ksl = (lane & 15) / PP, kpi = (lane & 15) % PP, kcol = 8 * (lane >> 4);
-    auto kpos = [&](int i0) { return (s0 + tw + (i0 + ksl) * TW) * PP + kpi; };
-    auto kaddr = [&](int i0, int ks) -> const void * {
-        const int pos = kpos(i0);
-        return (i0 + ksl < mine && pos < n && pos != pnew)
-                   ? (const void *)(P.kc + (row0 + pos) * D + 32 * ks + kcol)
-                   : (const void *)P.dummy;
-    };
     auto addr = [&](const uint16_t *base, int i) -> const void * {
         const int pos = pos_of_item(i);
         return (i < mine && pos < n && pos != pnew) ? (const void *)(base + (size_t)pos * D)
@@ -2192,12 +2131,12 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
     };
     if (compute) {
 #pragma unroll
-        for (int s = 0; s < R; ++s) kr[s] = ld_stream_16B(MC ? kaddr(0, s) : addr(Kb, s));
+        for (int s = 0; s < R; ++s) kr[s] = ld_stream_16B(addr(Kb, s));
 #pragma unroll
         for (int s = 0; s < R; ++s) vr[s] = ld_stream_16B(addr(Vb, s));
     }
     if (is_ctl_lane0()) trace_stamp(P, ti, 1);
-    if constexpr (LL) {
+    {
         // the queries of head g's query heads and the new key and value, as
         // tagged words (every thread takes a few), into LDS
         const size_t qo = (size_t)b * P.nq * D + (size_t)g * G * D;
@@ -2216,26 +2155,6 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
                     reinterpret_cast<unsigned *>(vn)[i - G * D - D / 2] = v;
                 }
             });
-    } else {
-        if (first) local_wait(P, P.cnt + g, (unsigned)(l + 1) * (unsigned)P.Sg, ti);
-        // the queries and the new key and value (device-coherent loads, all
-        // unconditional from clamped addresses and issued together; masked
-        // when stored)
-        constexpr int NQ = (G * D + kThreads - 1) / kThreads;
-        float qv[NQ];
-        const float *qsrc = P.q + (size_t)b * P.nq * D + (size_t)g * G * D;
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) qv[k] = ld_dev(qsrc + min((int)kl_tid() + k * kThreads, G * D - 1));
-        const size_t o = (size_t)pnew * D + min((int)kl_tid(), D / 4 - 1) * 4;
-        const unsigned long long kw = ld_dev_u64(P.kc + row0 * D + o);
-        const unsigned long long vw = ld_dev_u64(P.vc + row0 * D + o);
-#pragma unroll
-        for (int k = 0; k < NQ; ++k)
-            if ((int)kl_tid() + k * kThreads < G * D) qs[kl_tid() + k * kThreads] = qv[k];
-        if (kl_tid() < D / 4) {
-            reinterpret_cast<unsigned long long *>(kn)[kl_tid()] = kw;
-            reinterpret_cast<unsigned long long *>(vn)[kl_tid()] = vw;
-        }
     }
     __syncthreads();
     if (is_ctl_lane0()) trace_stamp(P, ti, 2);
@@ -2249,81 +2168,33 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
         for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
     }
     if (compute) {
-        float q[MC ? 1 : HG][8];
-        bf16x8 qb[MC ? R : 1], qbl[MC ? R : 1];
-        if constexpr (MC) {
-            // B operand: column l % 16 = the team's head l % 16 (zero past HG)
-            const int hc = lane & 15;
+        float q[HG][8];
 #pragma unroll
-            for (int ks = 0; ks < R; ++ks) {
-                unsigned hw[4], lw[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int d0 = 32 * ks + kcol + 2 * j;
-                    const float x0 = hc < HG ? qs[(h0 + hc) * D + d0] * scale : 0.f;
-                    const float x1 = hc < HG ? qs[(h0 + hc) * D + d0 + 1] * scale : 0.f;
-                    split_bf16x2(x0, x1, hw[j], lw[j]);
-                }
-                qb[ks] = __builtin_bit_cast(bf16x8, u32x4{hw[0], hw[1], hw[2], hw[3]});
-                qbl[ks] = __builtin_bit_cast(bf16x8, u32x4{lw[0], lw[1], lw[2], lw[3]});
-            }
-        } else {
-#pragma unroll
-            for (int h = 0; h < HG; ++h) {
-                const float4 q0 = *reinterpret_cast<const float4 *>(qs + (h0 + h) * D + ds);
-                const float4 q1 = *reinterpret_cast<const float4 *>(qs + (h0 + h) * D + ds + 4);
-                q[h][0] = q0.x; q[h][1] = q0.y; q[h][2] = q0.z; q[h][3] = q0.w;
-                q[h][4] = q1.x; q[h][5] = q1.y; q[h][6] = q1.z; q[h][7] = q1.w;
-            }
+        for (int h = 0; h < HG; ++h) {
+            const float4 q0 = *reinterpret_cast<const float4 *>(qs + (h0 + h) * D + ds);
+            const float4 q1 = *reinterpret_cast<const float4 *>(qs + (h0 + h) * D + ds + 4);
+            q[h][0] = q0.x; q[h][1] = q0.y; q[h][2] = q0.z; q[h][3] = q0.w;
+            q[h][4] = q1.x; q[h][5] = q1.y; q[h][6] = q1.z; q[h][7] = q1.w;
         }
         // R slabs at a time: their scores, one rescale per head, their values
         for (int i0 = 0; i0 < mine; i0 += R) {
             float sc[R][HG];
-            if constexpr (MC) {
-                const bool knew = kpos(i0) == pnew;   // (the new key comes from LDS)
-                f32x4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int ks = 0; ks < R; ++ks) {
-                    const u32x4 kv = knew ? *reinterpret_cast<const u32x4 *>(kn + 32 * ks + kcol)
-                                          : kr[ks];
-                    kr[ks] = ld_stream_16B(kaddr(i0 + R, ks));
-                    const bf16x8 a = __builtin_bit_cast(bf16x8, kv);
-                    t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qb[ks], t, 0, 0, 0);
-                    t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qbl[ks], t, 0, 0, 0);
-                }
-                // D lane l: rows 4 (l / 16) + v, column l % 16 (wave-local slot:
-                // a wave's LDS accesses complete in order)
+            for (int s = 0; s < R; ++s) {
+                const int pos = pos_of_item(i0 + s);
+                const bool valid = i0 + s < mine && pos < n;
+                const u32x4 kv =
+                    pos == pnew ? *reinterpret_cast<const u32x4 *>(kn + ds) : kr[s];
+                kr[s] = ld_stream_16B(addr(Kb, i0 + s + R));
+                const float kf[8] = {bf_lo(kv.x), bf_hi(kv.x), bf_lo(kv.y), bf_hi(kv.y),
+                                     bf_lo(kv.z), bf_hi(kv.z), bf_lo(kv.w), bf_hi(kv.w)};
 #pragma unroll
-                for (int v = 0; v < 4; ++v) stile[(4 * (lane >> 4) + v) * 16 + (lane & 15)] = t[v];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                for (int h = 0; h < HG; ++h) {
+                    float d = 0.f;
 #pragma unroll
-                for (int s = 0; s < R; ++s) {
-                    const int pos = pos_of_item(i0 + s);
-                    const bool valid = i0 + s < mine && pos < n;
-                    const float4 v4 = *reinterpret_cast<const float4 *>(stile + (s * PP + pi) * 16);
-                    const float vv[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-                    for (int h = 0; h < HG; ++h) sc[s][h] = valid ? vv[h] : -INFINITY;
-                }
-            } else {
-#pragma unroll
-                for (int s = 0; s < R; ++s) {
-                    const int pos = pos_of_item(i0 + s);
-                    const bool valid = i0 + s < mine && pos < n;
-                    const u32x4 kv =
-                        pos == pnew ? *reinterpret_cast<const u32x4 *>(kn + ds) : kr[s];
-                    kr[s] = ld_stream_16B(addr(Kb, i0 + s + R));
-                    const float kf[8] = {bf_lo(kv.x), bf_hi(kv.x), bf_lo(kv.y), bf_hi(kv.y),
-                                         bf_lo(kv.z), bf_hi(kv.z), bf_lo(kv.w), bf_hi(kv.w)};
-#pragma unroll
-                    for (int h = 0; h < HG; ++h) {
-                        float d = 0.f;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) d = fmaf(q[h][e], kf[e], d);
-                        d = sum_lanes<LP>(d) * scale;
-                        sc[s][h] = valid ? d : -INFINITY;
-                    }
+                    for (int e = 0; e < 8; ++e) d = fmaf(q[h][e], kf[e], d);
+                    d = sum_lanes<LP>(d) * scale;
+                    sc[s][h] = valid ? d : -INFINITY;
                 }
             }
 #pragma unroll
@@ -2388,13 +2259,9 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
     }
     __syncthreads();
     // the waves in order: (max, sum, unnormalised output) of the chunk, the
-    // max published in natural-log units; per-sequence path: as tagged
-    // words, per query head h at [b][g][h][c] (D + 2 words: outputs, max,
-    // sum; one query head's chunks contiguous for the O projection, which
-    // polls them)
-    const size_t item = ((size_t)b * P.nkv + g) * P.C + c;
-    float *out = P.part_o + item * G * D;
-    float *sts = P.part_s + item * G * 2;
+    // max published in natural-log units, as tagged words, per query head h
+    // at [b][g][h][c] (D + 2 words: outputs, max, sum; one query head's
+    // chunks contiguous for the O projection, which polls them)
     unsigned long long *ll_out = P.po_ll + (((size_t)b * P.nkv + g) * G * P.C + c) * (D + 2);
     const size_t hstride = (size_t)P.C * (D + 2);
     const unsigned tag = ll_tag(P, l);
@@ -2410,46 +2277,542 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
             L = fmaf(wl[w * HG + hl], a, L);
             if (t < G * D) O = fmaf(wacc[(w * HG + hl) * D + dd], a, O);
         }
-        if constexpr (LL) {
-            if (t < G * D) {
-                st_ll_f(ll_out + h * hstride + dd, O, tag);
-            } else {
-                st_ll_f(ll_out + h * hstride + D, M * 0.6931471805599453f, tag);
-                st_ll_f(ll_out + h * hstride + D + 1, L, tag);
-            }
-        } else if (t < G * D) {
-            st_dev(out + t, O);
-            if (P.C == 1) {   // (one chunk: the merged output is final)
-                uint16_t hi, lo;
-                split_bf16(O / L, hi, lo);
-                const size_t o = (size_t)b * P.nq * D + (size_t)g * G * D + t;
-                st_dev_u16(P.acto + o, hi);
-                st_dev_u16(P.acto_lo + o, lo);
-            }
+        if (t < G * D) {
+            st_ll_f(ll_out + h * hstride + dd, O, tag);
         } else {
-            st_dev(sts + h * 2, M * 0.6931471805599453f);
-            st_dev(sts + h * 2 + 1, L);
+            st_ll_f(ll_out + h * hstride + D, M * 0.6931471805599453f, tag);
+            st_ll_f(ll_out + h * hstride + D + 1, L, tag);
         }
     }
     if (is_ctl_lane0()) trace_stamp(P, ti, 3);
     __syncthreads();   // (the attention area is the next item's)
 }
 
-// Attention of KV head g: the workgroups of head g take its items (sequence
-// b, chunk c) round-robin.  The per-sequence path hands the chunk results to
-// the O projection as tagged words; the batched path publishes them before a
-// grid barrier.
+// ---------------------------------------------------------------- attention by units (matrix-core path)
+//
+// Split-K flash decoding over the whole batch at once.  The cached positions
+// of a sequence are cut into units (attn_unit<D>() positions: 4 KiB of keys
+// and 4 KiB of values), a sequence of position p has p / unit + 1 of them
+// (the last holds the new position), and the units of all sequences, one
+// sequence after the other, are dealt in equal contiguous shares to the
+// workgroups of a KV head.  A share is one or more segments (a run of units
+// of one sequence); its start is found once per launch (seg_init).  A share
+// that starts inside a sequence hands its part of that sequence over as
+// tagged words; the share with the sequence's first units, which is its last
+// segment, merges them.  No barrier separates a share's segments: the waves go
+// on to the next one while the control wave merges and stages.  Equal
+// shares matter where contexts differ or the batch does not divide the
+// workgroups: with one item per (sequence, chunk) the phase lasted as long as
+// the longest item (8B shape, batch 32, contexts 2048 to 4096: ends spread
+// from 49 to 86 us).
+//
+// A compute wave takes every kWaves-th unit of a segment and keeps the loads
+// of two units in flight (16 KiB; 128 KiB per workgroup, across segments).
+// Both products run on the matrix cores, in layouts that need no exchange
+// between lanes:
+//   scores  v_mfma_f32_16x16x32_bf16, A = 16 key rows (16 bytes of a row per
+//           lane), B = the queries (scaled, log2 units) as two bf16 terms;
+//           column n is head n & 7 (zero past G).  Tile row 4 k + v is the
+//           position that the value product below wants from lane (k, n) in
+//           its register v.
+//   values  v_mfma_f32_16x16x4_f32 (fp32 probabilities, bf16 values exact in
+//           fp32): A_e = element e of each lane's 16 bytes of a value row
+//           (one load per lane covers a slab of 1024 / (2 D) positions), B =
+//           the slab's probabilities as they came out of the score tile.
+//           D = 64: a slab has 8 positions, 2 k and 2 k + 1 in lane group k;
+//           rows and columns 0-7 are the even ones' product, 8-15 the odd
+//           ones' (the other two quarters are never read).
+// All heads of the group share one pass over K and V, up to 8 of them at the
+// cost of one: per unit 32 fp32 products of 32 cycles against about 3000
+// cycles that its 8 KiB take from HBM (a SIMD's share).  The running maximum
+// moves only when a score passes it by 2^8 (the exponentials stay below 2^8
+// and exact sums are unaffected), so the loop has no cross-lane step.
+// 8B shape, batch 32, 4096 cached: see the phase table; 70B shape (8 heads a
+// group), batch 32: 166 us per layer with two head teams that each streamed
+// the chunk and multiplied on the vector units.
+template <int D> __device__ __forceinline__ constexpr int attn_unit() { return 2048 / D; }
+__device__ __forceinline__ int attn_units_of(int pnew, int up) { return pnew / up + 1; }
+
+// A workgroup's share, in LDS: first sequence, its first unit, units of the
+// share, units of the whole batch, workgroups that have shares.
+__device__ __forceinline__ int *seg_table(const StepParams &P) {
+    return route_table(P) + 4 * kMfmaBatch;
+}
+// (one wave, once per launch, before the launch's first barrier)
+__device__ __forceinline__ void seg_init(const StepParams &P, int lane) {
+    const int up = 2048 / P.d;
+    int T = 0;
+    for (int b0 = 0; b0 < P.B; b0 += 64) {
+        int u = b0 + lane < P.B ? attn_units_of(eff_pos(P, b0 + lane), up) : 0;
+        for (int off = 1; off < 64; off <<= 1) u += __shfl_xor(u, off);
+        T += u;
+    }
+    const int np = min(P.Sg, T), part = blockIdx.x % P.Sg;
+    int a = 0, e = 0;
+    if (part < np) split_range(T, np, part, a, e);
+    int *t = seg_table(P);
+    if (lane == 0) {
+        t[0] = t[1] = 0;
+        t[2] = e - a;
+        t[3] = T;
+        t[4] = np;
+    }
+    // the sequence that holds unit a
+    int before = 0;
+    for (int b0 = 0; b0 < P.B; b0 += 64) {
+        const int own = b0 + lane < P.B ? attn_units_of(eff_pos(P, b0 + lane), up) : 0;
+        int s = own;   // inclusive sum
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(s, off);
+            s += lane >= off ? o : 0;
+        }
+        const int s0 = before + s - own;
+        if (own > 0 && s0 <= a && a < s0 + own) {
+            t[0] = b0 + lane;
+            t[1] = a - s0;
+        }
+        before += __shfl(s, 63);
+    }
+}
+template <int D, int G>
+__device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int ti) {
+    const StepParams P = load_params(ka);
+    const Lds S = lds_layout(kl_smem, P);
+    constexpr int UP = attn_unit<D>();              // positions per unit
+    constexpr int PP = 512 / D;                     // positions per value slab
+    constexpr int HS = D + 4;                       // floats between heads' wave outputs (banks)
+    constexpr int WS = G * HS;                      // floats per wave
+    const int wid = __builtin_amdgcn_readfirstlane(kl_tid() >> 6);
+    const int lane = kl_tid() & 63, k4 = lane >> 4, n = lane & 15;
+    // two sets, alternating by segment: while a segment's units run, the
+    // control wave merges the waves of the one before and stages the queries
+    // of the one after
+    float *const qs0 = S.attn;                      // [2][G][D] queries
+    float *const wm0 = qs0 + 2 * G * D;             // [2][kWaves][G] wave maxima (log2 units)
+    float *const wl0 = wm0 + 2 * kWaves * G;        // [2][kWaves][G] wave sums
+    float *const wa0 = wl0 + 2 * kWaves * G;        // [2][kWaves][G][HS] wave outputs
+    uint16_t *const kn0 = reinterpret_cast<uint16_t *>(wa0 + 2 * kWaves * WS);   // [2][D] new key
+    uint16_t *const vn0 = kn0 + 2 * D;                                           // [2][D] new value
+    // waves done with the set's segments so far [2]; segments with staged queries
+    int *const flags = reinterpret_cast<int *>(vn0 + 2 * D);
+    auto flag = [&](int i) {
+        return __hip_atomic_load(flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    const int *tab = seg_table(P);
+    int b = __builtin_amdgcn_readfirstlane(tab[0]), u0 = __builtin_amdgcn_readfirstlane(tab[1]);
+    int left = __builtin_amdgcn_readfirstlane(tab[2]);
+    if (left <= 0) return;
+    int pnew = __builtin_amdgcn_readfirstlane(eff_pos(P, b));
+    const unsigned tag = ll_tag(P, l);
+
+    // the merged (max, sum, unnormalised output) of the waves of set z, for
+    // output t of the G D
+    auto merge_waves = [&](int z, int t, float &M, float &L, float &O) {
+        const float *wm = wm0 + z * kWaves * G, *wl = wl0 + z * kWaves * G;
+        const int h = t / D, dd = t % D;
+        M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, wm[w * G + h]);
+        O = 0.f, L = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float mw = wm[w * G + h];
+            const float a = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+            L = fmaf(wl[w * G + h], a, L);
+            O = fmaf(wa0[(z * kWaves + w) * WS + h * HS + dd], a, O);
+        }
+    };
+    // output t of sequence sb
+    auto finish = [&](int sb, int t, float L, float O) {
+        uint16_t hi, lo;
+        split_bf16(O / L, hi, lo);
+        const size_t o = (size_t)sb * P.nq * D + (size_t)g * G * D + t;
+        st_dev_u16(P.acto + o, hi);
+        st_dev_u16(P.acto_lo + o, lo);
+    };
+    // a share that starts inside a sequence hands its part of it to the
+    // workgroup that has the sequence's first units, as tagged words [head]
+    // [D outputs, max, sum]
+    unsigned long long *const parts = P.po_ll + (size_t)g * P.Sg * G * (D + 2);
+    auto hand_over = [&](int t, float M, float L, float O) {
+        unsigned long long *w = parts + ((size_t)part * G + t / D) * (D + 2);
+        st_ll_f(w + t % D, O, tag);
+        if (t % D == 0) {
+            st_ll_f(w + D, M, tag);
+            st_ll_f(w + D + 1, L, tag);
+        }
+    };
+
+    if (wid < kWaves) {
+        // tile row l % 16 of this lane: its position in the unit (D = 64: in
+        // the unit's first half), and the lane's position in a value slab
+        const int kp = D == 128 ? (n & 3) * 4 + (n >> 2) : 8 * ((n & 3) >> 1) + 2 * (n >> 2) + (n & 1);
+        const int vp = lane / (D / 8), kcol = 8 * k4, vcol = 8 * (lane % (D / 8));
+        // position of score register s (0 .. 3): D = 128: slab s, position k;
+        // D = 64: slab s, position 2 k (columns 0-7) or 2 k + 1 (columns 8-15)
+        const int sp = D == 128 ? k4 : 2 * k4 + (n >> 3);
+        u32x4 kr[2][4], vr[2][4];
+        const uint16_t *kb = nullptr, *vb = nullptr;
+        // the current segment: its sequence's units, its end and the end of
+        // its units with cached positions; the wave's units, its first one's
+        // position, the last cached position
+        int U = 0, u1 = 0, uc = 0, mine = 0, base = 0, last = 0, rot = 0;
+        // The wave's i-th unit is its (i + rot) mod mine -th in memory: the
+        // workgroups start at different places of their shares.  Shares are
+        // often whole powers of two apart, and in step they met in the same
+        // HBM banks (8B shape, batch 16, 8192 cached positions: 121 -> 95 us
+        // per layer; batch 32, contexts 2048-4096: 86 -> 81; batch 32, 4096:
+        // 90-93 either way).  Past the last unit: past the context.
+        auto place = [&](int i) {
+            const int x = i + rot;
+            return i >= mine ? (1 << 16) : (x >= mine ? x - mine : x);
+        };
+        // (loads of unit i of the wave; positions past the cached ones take
+        // the last cached one's, in range and masked when used)
+        auto issue_k = [&](int j, int i) {
+            const int p0 = base + place(i) * kWaves * UP + kp;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int t = D == 128 ? 0 : x >> 1, ks = D == 128 ? x : x & 1;
+                kr[j][x] = ld_stream_16B(kb + (size_t)min(p0 + 16 * t, last) * D + 32 * ks);
+            }
+        };
+        auto issue_v = [&](int j, int i) {
+            const int p0 = base + place(i) * kWaves * UP + vp;
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                vr[j][x] = ld_stream_16B(vb + (size_t)min(p0 + x * PP, last) * D);
+        };
+        // units of the segments so far (the waves take the share's units in
+        // turn, across its segments)
+        int taken = 0;
+        auto enter = [&]() {   // the segment (b, u0): addresses and the first two units' loads
+            const size_t row0 = kv_row(P, l, b, g);
+            kb = P.kc + row0 * D + kcol;
+            vb = P.vc + row0 * D + vcol;
+            last = max(pnew - 1, 0);
+            U = attn_units_of(pnew, UP);
+            u1 = u0 + min(left, U - u0);
+            uc = min(u1, (pnew + UP - 1) / UP);
+            const int f = u0 + ((wid - taken) & (kWaves - 1));
+            base = f * UP;
+            mine = f < uc ? (uc - f + kWaves - 1) / kWaves : 0;
+            rot = mine > 0 ? (int)(blockIdx.x * 5u) % mine : 0;
+            issue_k(0, 0);
+            issue_v(0, 0);
+            issue_k(1, 1);
+            issue_v(1, 1);
+        };
+        enter();
+        lds_barrier();
+        // queries in log2 units: softmax weights are 2^(s log2(e) - max)
+        const float scale = 1.4426950408889634f / sqrtf((float)D);
+        constexpr int NQB = 4;   // D = 128: 4 column blocks (both terms in one); D = 64: 2 terms x 2
+        for (int seg = 0;; ++seg) {
+            const int z = seg & 1;
+            left -= u1 - u0;
+            const int pnext = left > 0 ? __builtin_amdgcn_readfirstlane(eff_pos(P, b + 1)) : 0;
+            if (seg >= 2)   // (the first two were staged before the barrier)
+                while (flag(2) <= seg) __builtin_amdgcn_s_sleep(1);
+            asm volatile("" ::: "memory");
+            const int lq = kl_tid() & 63, kcq = 8 * (lq >> 4);
+            const float *qs = qs0 + z * G * D;
+            bf16x8 qb[NQB];
+#pragma unroll
+            for (int x = 0; x < NQB; ++x) {
+                const int h = lq & 7, ks = D == 128 ? x : x & 1;
+                const bool lo = D == 128 ? (lq & 8) != 0 : x >= 2;
+                unsigned w[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int d0 = 32 * ks + kcq + 2 * j;
+                    const float x0 = h < G ? qs[h * D + d0] * scale : 0.f;
+                    const float x1 = h < G ? qs[h * D + d0 + 1] * scale : 0.f;
+                    unsigned hw, lw;
+                    split_bf16x2(x0, x1, hw, lw);
+                    w[j] = lo ? lw : hw;
+                }
+                qb[x] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+            }
+            f32x4 acc[8];
+            float m = -INFINITY, lsum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // one unit whose first position is p0, cached positions below
+            // lim: keys kq, values vq; kdone() / vdone() refill the ring
+            auto unit = [&](u32x4 *kq, u32x4 *vq, int p0, int lim, auto &&kdone, auto &&vdone) {
+                float s[4];
+                if constexpr (D == 128) {
+                    f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kq[ks]),
+                                                                   qb[ks], t, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) s[v] = t[v] + dpp<0x128>(t[v]);   // both terms
+                } else {
+                    f32x4 t[2];
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) {
+                        t[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int x = 0; x < 4; ++x)
+                            t[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(bf16x8, kq[2 * y + (x & 1)]), qb[x], t[y], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        s[v] = n < 8 ? t[v >> 1][2 * (v & 1)] : t[v >> 1][2 * (v & 1) + 1];
+                }
+                kdone();
+                if (p0 + UP > lim) {   // (uniform: the context's last unit)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if (p0 + v * PP + sp >= lim) s[v] = -INFINITY;
+                        if (p0 + v * PP + vp >= lim) vq[v] = u32x4{0u, 0u, 0u, 0u};
+                    }
+                }
+                float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+                if (__any(mx > m + 8.f)) {
+                    if constexpr (D == 64) mx = fmaxf(mx, dpp<0x128>(mx));
+                    mx = fmaxf(mx, __shfl_xor(mx, 16));
+                    mx = fmaxf(mx, __shfl_xor(mx, 32));
+                    const float mn = fmaxf(m, mx);
+                    const float al = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+                    m = mn;
+                    lsum *= al;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[e] *= al;
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    s[v] = s[v] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s[v] - m);
+                    lsum += s[v];
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const u32x4 w = vq[v];
+                    const float vf[8] = {bf_lo(w.x), bf_hi(w.x), bf_lo(w.y), bf_hi(w.y),
+                                         bf_lo(w.z), bf_hi(w.z), bf_lo(w.w), bf_hi(w.w)};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e], s[v], acc[e], 0, 0, 0);
+                }
+                vdone();
+            };
+            for (int i = 0; i < mine; i += 2) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int p0 = base + place(i + j) * kWaves * UP;
+                    if (i + j < mine) {
+                        unit(kr[j], vr[j], p0, pnew, [&]() { issue_k(j, i + j + 2); },
+                             [&]() { issue_v(j, i + j + 2); });
+                    } else {
+                        issue_k(j, i + j + 2);
+                        issue_v(j, i + j + 2);
+                    }
+                }
+            }
+            if (u1 == U && ((wid - taken - (uc - u0)) & (kWaves - 1)) == 0) {
+                // the new position, from LDS (by the wave whose turn it is)
+                u32x4 kq[4], vq[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const int ks = D == 128 ? x : x & 1;
+                    const bool mk = n == 0 && (D == 128 || x < 2);
+                    kq[x] = *reinterpret_cast<const u32x4 *>(kn0 + z * D + 32 * ks + kcol);
+                    vq[x] = *reinterpret_cast<const u32x4 *>(vn0 + z * D + vcol);
+                    if (!mk) kq[x] = u32x4{0u, 0u, 0u, 0u};
+                }
+                unit(kq, vq, 0, 1, []() {}, []() {});
+            }
+            taken += uc - u0;
+            ++b;
+            u0 = 0;
+            pnew = pnext;
+            if (left > 0) enter();
+            // this wave's (max, sum, output) into set z
+            lsum += __shfl_xor(lsum, 16);
+            lsum += __shfl_xor(lsum, 32);
+            if constexpr (D == 64) {
+                lsum += dpp<0x128>(lsum);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[e][r] += __shfl_down(acc[e][r], 40);
+            }
+            const int le = kl_tid() & 63, ke = le >> 4, ne = le & 15;
+            if (ne < G && ke < D / 32) {
+                float *o = wa0 + (z * kWaves + wid) * WS + ne * HS + 32 * ke;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    *reinterpret_cast<float4 *>(o + 8 * r) =
+                        make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+                    *reinterpret_cast<float4 *>(o + 8 * r + 4) =
+                        make_float4(acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
+                }
+                if (ke == 0) {
+                    wm0[(z * kWaves + wid) * G + ne] = m;
+                    wl0[(z * kWaves + wid) * G + ne] = lsum;
+                }
+            }
+            if (left <= 0) break;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (le == 0)
+                __hip_atomic_fetch_add(flags + z, 1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    } else {
+        // the control wave: the queries and the new key and value of sequence
+        // sb, position spos, into set z
+        auto stage_q = [&](int sb, int spos, int z) {
+            constexpr int N2 = G * D / 2, NQ = (N2 + 63) / 64;   // pairs; per lane
+            const float *src = P.q + (size_t)sb * P.nq * D + (size_t)g * G * D;
+            const size_t o = (kv_row(P, l, sb, g) + spos) * D + (lane % (D / 4)) * 4;
+            unsigned long long qv[NQ];
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) qv[k] = ld_dev_u64(src + 2 * min(lane + 64 * k, N2 - 1));
+            const unsigned long long kv = ld_dev_u64((lane < 32 ? P.kc : P.vc) + o);
+            unsigned long long *dst = reinterpret_cast<unsigned long long *>(qs0 + z * G * D);
+#pragma unroll
+            for (int k = 0; k < NQ; ++k)
+                if (N2 % 64 == 0 || lane + 64 * k < N2) dst[lane + 64 * k] = qv[k];
+            if (lane % 32 < D / 4)
+                reinterpret_cast<unsigned long long *>((lane < 32 ? kn0 : vn0) + z * D)[lane % 32] = kv;
+        };
+        // (pn[i % 3]: the position of the share's segment i's sequence, b + i)
+        auto pos_at = [&](int i) { return __builtin_amdgcn_readfirstlane(eff_pos(P, b + i)); };
+        auto units_at = [&](int p) { return attn_units_of(p, UP); };
+        int rest = left - min(left, units_at(pnew) - u0);   // units after this segment
+        int pn1 = rest > 0 ? pos_at(1) : 0;
+        if (lane == 0) {
+            trace_stamp(P, ti, 1);
+            flags[0] = flags[1] = 0;
+            flags[2] = 2;
+            spin_until(P, [&]() {
+                return (int)(__hip_atomic_load(P.cnt + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
+                             (unsigned)(l + 1) * (unsigned)P.Sg) >= 0;
+            });
+        }
+        __builtin_amdgcn_wave_barrier();
+        stage_q(b, pnew, 0);
+        if (rest > 0) stage_q(b + 1, pn1, 1);
+        if (lane == 0) trace_stamp(P, ti, 2);
+        lds_barrier();
+        for (int seg = 0; rest > 0; ++seg) {
+            // (segment seg is not the share's last: it ends its sequence)
+            const int z = seg & 1, done = kWaves * (seg / 2 + 1);
+            const int rest1 = rest - min(rest, units_at(pn1));   // after the next segment
+            const int pn2 = rest1 > 0 ? pos_at(2) : 0;
+            while (flag(z) < done) __builtin_amdgcn_s_sleep(1);
+            asm volatile("" ::: "memory");
+            for (int t = kl_tid() & 63; t < G * D; t += 64) {
+                float M, L, O;
+                merge_waves(z, t, M, L, O);
+                if (u0 == 0) finish(b, t, L, O);
+                else hand_over(t, M, L, O);
+            }
+            if (rest1 > 0) {
+                stage_q(b + 2, pn2, z);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if ((kl_tid() & 63) == 0)
+                    __hip_atomic_store(flags + 2, seg + 3, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            ++b;
+            u0 = 0;
+            left = rest;
+            rest = rest1;
+            pnew = pn1;
+            pn1 = pn2;
+        }
+    }
+    lds_barrier();
+    // the share's last segment, by every thread: set and segment as the
+    // walks above left them, found again from the share
+    {
+        int nb = __builtin_amdgcn_readfirstlane(tab[0]), nu = __builtin_amdgcn_readfirstlane(tab[1]);
+        int nl = __builtin_amdgcn_readfirstlane(tab[2]), z = 0, U;
+        const int T = __builtin_amdgcn_readfirstlane(tab[3]);
+        const int np = __builtin_amdgcn_readfirstlane(tab[4]);
+        int seq0, e0;
+        split_range(T, np, part, seq0, e0);
+        seq0 -= nu;   // the sequence's first unit, counted over the batch
+        for (;;) {
+            U = attn_units_of(__builtin_amdgcn_readfirstlane(eff_pos(P, nb)), UP);
+            if (nl <= U - nu) break;
+            nl -= U - nu;
+            seq0 += U;
+            ++nb;
+            nu = 0;
+            z ^= 1;
+        }
+        // (the shares f + 1 .. e hold the rest of a sequence that starts here)
+        const int e = (int)(((long long)(seq0 + U) * np - 1) / T);
+        const int more = nu == 0 ? e - part : 0;
+        constexpr int NB = 8;   // shares whose words are loaded together
+        for (int t = kl_tid(); t < G * D; t += kThreads) {
+            float M, L, O;
+            merge_waves(z, t, M, L, O);
+            if (nu > 0) {
+                hand_over(t, M, L, O);
+                continue;
+            }
+            for (int q0 = 0; q0 < more; q0 += NB) {
+                unsigned long long v[NB][3];
+                spin_until(P, [&]() {
+                    bool ok = true;
+#pragma unroll
+                    for (int q = 0; q < NB; ++q) {
+                        const unsigned long long *w =
+                            parts + ((size_t)(part + 1 + min(q0 + q, more - 1)) * G + t / D) * (D + 2);
+                        v[q][0] = ld_dev_u64(w + t % D);
+                        v[q][1] = ld_dev_u64(w + D);
+                        v[q][2] = ld_dev_u64(w + D + 1);
+                    }
+#pragma unroll
+                    for (int q = 0; q < NB; ++q)
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) ok = ok && ll_current(v[q][i], tag);
+                    return ok;
+                });
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    if (q0 + q < more) {
+                        const float mq = __uint_as_float(ll_value(v[q][1]));
+                        const float mn = fmaxf(M, mq);
+                        const float a = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn);
+                        const float c = mq == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mq - mn);
+                        L = L * a + __uint_as_float(ll_value(v[q][2])) * c;
+                        O = O * a + __uint_as_float(ll_value(v[q][0])) * c;
+                        M = mn;
+                    }
+                }
+            }
+            finish(nb, t, L, O);
+        }
+    }
+    if (is_ctl_lane0()) trace_stamp(P, ti, 3);
+    lds_barrier();   // (the attention area is the next phase's)
+}
+
+// Attention of KV head g.  Per-sequence path: the workgroups of head g take
+// its items (sequence b, chunk c) round-robin and hand the chunk results to
+// the O projection as tagged words; batched path: by units (attn_units), the
+// merged outputs published before a grid barrier.
 template <int D, int G, bool BAT>
 __device__ __forceinline__ void phase_attn(KArg ka, int l, int garrive, int ti) {
     const StepParams P = load_params(ka);
     const int g = blockIdx.x / P.Sg, part = blockIdx.x % P.Sg;
     if (g < P.nkv) {
-        const int items = P.B * P.C;
-        for (int it = part; it < items; it += P.Sg)
-            if constexpr (!BAT && G <= 4)
-                attn_item_ll<D, G>(ka, l, it / P.C, g, it % P.C, ti);
-            else
-                attn_item_stream<D, G, !BAT>(ka, l, it / P.C, g, it % P.C, it == part, ti);
+        if constexpr (BAT) {
+            attn_units<D, G>(ka, l, g, part, ti);
+        } else {
+            const int items = P.B * P.C;
+            for (int it = part; it < items; it += P.Sg)
+                if constexpr (G <= 4) attn_item_ll<D, G>(ka, l, it / P.C, g, it % P.C, ti);
+                else attn_item_stream<D, G>(ka, l, it / P.C, g, it % P.C, ti);
+        }
     }
     if (garrive >= 0) bar_arrive(P, garrive, ti);
     else if (is_ctl_lane0()) trace_stamp(P, ti, 0);
@@ -2460,8 +2823,7 @@ __device__ __forceinline__ void phase_attn(KArg ka, int l, int garrive, int ti) 
 // residual.  GEMV path: the staged input is head g's merged attention output,
 // published by the attention phase.
 template <int D, int G, bool BAT>
-__device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int mbar, int garrive,
-                                            int ti) {
+__device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int garrive, int ti) {
     const StepParams P = load_params(ka);
     const Lds S = lds_layout(kl_smem, P);
     const int KTO = G * D / kTileK;
@@ -2488,7 +2850,7 @@ __device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int mbar,
         weight_phase<true>(
             P, S, Wo + (size_t)ksc * gps * P.o_rg * KTO * kTileBytes, gps * KTO, a0, a1 - a0,
             [&]() { if (gwait >= 0) bar_wait(P, gwait, ti); },
-            [&]() { if (mbar >= 0) merge_batched<D, G>(P, mbar); }, [&](int) {},
+            [&]() {}, [&](int) {},
             [&](int c, int b0, int nb, uint16_t *buf) {
                 stage_bf16_chunk(P.acto + col0, P.acto_lo + col0, P.nq * D, width, c, b0, nb, buf);
             },
@@ -3057,8 +3419,8 @@ __global__ __launch_bounds__(kThreads) void kl_step_kernel(StepParams P, int l0,
     const bool has_qkv = phases & kPhQkv, has_gu = phases & kPhGateUp, has_head = phases & kPhHead;
     const int nlay = (phases & kPhLayer) ? l1 - l0 : 0;
     // batched steps add grid barriers of their own: after the q/k/v product
-    // (its fold), in the SwiGLU fold, and before a merge of several attention
-    // chunks (their RMSNorm steps hand over through slice counters instead)
+    // (its fold) and in the SwiGLU fold (their RMSNorm steps hand over through
+    // slice counters instead)
     constexpr bool batched = BAT;
     bar_init(load_params(ka));
     int na = 0, ti = 0;   // grid arrivals so far; phase index (for the trace)
@@ -3079,10 +3441,8 @@ __global__ __launch_bounds__(kThreads) void kl_step_kernel(StepParams P, int l0,
         }
         if (phases & kPhAttn) phase_attn<D, G, BAT>(ka, l, BAT ? ga(has_op) : -1, ti++);
         if (phases & kPhOproj) {
-            // (batched, several attention chunks: the merge step's own barrier)
-            const int w = BAT && has_attn ? gw() : -1;
-            const int m = BAT && load_params(ka).C > 1 ? na++ : -1, a = ga(has_gu);
-            phase_oproj<D, G, BAT>(ka, l, w, m, a, ti++);
+            const int w = BAT && has_attn ? gw() : -1, a = ga(has_gu);
+            phase_oproj<D, G, BAT>(ka, l, w, a, ti++);
         }
         if (phases & kPhGateUp) {
             const int w = gw(), a = BAT ? ga(has_down) : -1;
