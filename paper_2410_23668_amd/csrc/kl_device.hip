@@ -14,7 +14,7 @@ namespace kl {
 // that loads this library, kept until the process ends.  In host code its name
 // stands for no device address: host code uses only the address
 // static_scratch_address returns.
-static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
+static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes + kStaticWordBytes];
 
 hipError_t static_scratch_address(int device, uint8_t **out) {
     static std::mutex mu;

@@ -48,6 +48,7 @@ struct kl_state {
     int nwg, lds_bytes;
     int lds_red, lds_sm, lds_bar;
     int lds_red_seq;                  // the GEMV partial sums on the per-sequence path
+    int own_max;                      // residual rows a workgroup owns, at most
     bool multi_ok;                    // up to kMultiSeq sequences share a GEMV pass
     int batched_from;                 // first batch of the matrix-core path
 };
@@ -156,25 +157,17 @@ int folded_k_slices(int n, int t, int nblk, int nwg) {
 void lds_layout_for(kl_state &s) {
     const kl_config &c = s.cfg;
     const int g = c.n_heads / c.n_kv_heads, d = c.head_dim;
-    // attention: the queries, the new key and value, and (streaming item)
-    // the waves' (max, sum, output) per head of their team or (short-chunk
-    // item) a sub-chunk's scores, the softmax state and the waves' outputs
-    const int hg = std::min(g, 4);
-    const int sub = kWaves * kAttnLoads * (64 / (d / 8));
-    // (+ the streaming item's per-wave score tiles, 16 x 16 floats)
-    const int attn_main = std::max(g * d + 2 * kWaves * hg + kWaves * hg * d + d + kWaves * 256,
-                                   g * d + g * sub + g * 4 + kWaves * g * d + d);
-    // O projection: o, chunk weights, running sums, the chunk results
-    const int oproj_stage = d + kMergeChunks + 4 + kMergeChunks * (d + 2);
+    // attention: two sets of queries, waves' (max, sum, output) per head, new
+    // key and value; flags
+    const int attn_main = 3 * g * (d + 8) + 4 * kWaves * g + 2 * kWaves * g * (d + 4) + 2 * d + 4;
     const auto round64 = [](int v) { return (v + 63) & ~63; };
     const int rs = kWaves * kRgBatch * kTileRows;   // one sequence's GEMV partial sums
-    // per-sequence path, one sequence per GEMV pass: activations and RoPE row
-    const int one = round64(std::max({2 * s.Hp + d, s.KTc * kTileK, attn_main, oproj_stage}));
-    // kMultiSeq sequences per pass: their activations and RoPE rows, their
-    // SwiGLU blocks, their merged attention outputs before the merge's area
+    // per-sequence path, one sequence per GEMV pass: activations and RoPE row,
+    // a SwiGLU block, the merged attention output
+    const int one = round64(std::max({2 * s.Hp + d, s.KTc * kTileK, attn_main, s.Ap}));
+    // kMultiSeq sequences per pass
     const int multi = round64(std::max({kMultiSeq * (s.Hp + d), kMultiSeq * s.KTc * kTileK,
-                                        kMultiSeq * d + kMergeChunks + 4 + kMergeChunks * (d + 2),
-                                        attn_main, 2 * s.Hp + d}));
+                                        kMultiSeq * s.Ap, attn_main, 2 * s.Hp + d}));
     // The first batch of the matrix-core path: with several sequences per
     // GEMV pass the per-sequence path serves up to kMultiSeq sequences (a
     // mixture of experts: up to kMfmaBatch - 1, as its routing needs).  The
@@ -193,9 +186,11 @@ void lds_layout_for(kl_state &s) {
         s.lds_bar = s.lds_sm + 64;
         // + the step's epoch, position and validity per sequence, the head's
         // argmax keys of a group of sequences, the experts and their weights
-        // per sequence (two slots), the workgroup's share of the attention
+        // per sequence (two slots), the workgroup's share of the attention, its
+        // residual rows
+        const int seqs = std::min(c.max_batch, s.batched_from - 1);
         s.lds_bytes = (s.lds_bar + 2 * kBarGroups + 4 + 2 * kMfmaBatch + 2 * kGemmBatch +
-                       4 * kMfmaBatch + 8) * (int)sizeof(float);
+                       4 * kMfmaBatch + 8 + 2 * seqs * s.own_max) * (int)sizeof(float);
     };
     layout(c.max_batch >= 2);
     if (s.multi_ok && s.lds_bytes > 160 * 1024 - 256) layout(false);
@@ -209,27 +204,35 @@ void lds_layout_for(kl_state &s) {
 //   the residual stream, int64 fixed point [B][Hp];
 //   the per-sequence path's tagged words (8 bytes each, for up to
 //     kMfmaBatch - 1 sequences): rotated queries [B][nq d], the new key and
-//     value [B][nkv][d], chunk results [B][nkv][group][C][d + 2], the SwiGLU
-//     output [B][Fp];
-//   the matrix-core path's rotated queries [B][nq d] (its split sequences'
-//     attention results take the chunk results' place: one per workgroup);
+//     value [B][nkv][d], the SwiGLU output [B][Fp];
+//   the matrix-core path's rotated queries [B][nq d];
 //   the matrix-core path's two-term bf16 activations (both terms, [B][Hp],
 //     [B][Fp], [B][nq d]);
 //   on the matrix-core path also: the second residual buffer, the fp32 K-slice
 //     partials of the O and down projections [slices][B][Hp] and of the
 //     gate/up or q/k/v product (never live at the same time), and the
-//     RMSNorm sums of squares per kGemmChunkK columns [B][slices].
+//     RMSNorm sums of squares per kGemmChunkK columns [B][slices];
+// up to here 'base' bytes, and then the larger hand-offs as tagged words:
+//   the attention parts [nkv][workgroups per KV head + B][group][d + 2]
+//     (matrix-core path: [nkv][workgroups per KV head][group][d + 2]), and on
+//     the per-sequence path the residual after the attention and after the
+//     layer [B][Hp] each, the merged attention output [B][nq d] and the down
+//     projection's partial sums [B][expert slots x FFN column blocks][Hp].
+// With 'exact' every step of the scratch has B sequences (the regions of the
+// path that B does not take are left out); without, up to B.
 struct ScratchPlan {
     int B;
     bool batched;
     size_t off_bar, off_cnt, off_cnt_end;
     size_t off_x, off_q, off_act, off_actm, off_acto;
-    size_t off_qll, off_kvll, off_poll, off_mll;
+    size_t off_qll, off_kvll, off_mll;
     size_t off_x2, off_xp, off_gp, off_ss;
+    size_t base;
+    size_t off_poll, off_xall, off_xbll, off_oll, off_dpll;
     size_t total;
 };
 
-ScratchPlan plan_scratch(const kl_state &S, int B) {
+ScratchPlan plan_scratch(const kl_state &S, int B, bool exact) {
     const kl_config &c = S.cfg;
     const int d = c.head_dim, g = c.n_heads / c.n_kv_heads, nkv = c.n_kv_heads;
     ScratchPlan p{};
@@ -247,18 +250,17 @@ ScratchPlan plan_scratch(const kl_state &S, int B) {
     p.off_cnt = take((size_t)(2 * nkv + S.Sc + norm_cnts) * 4);
     p.off_cnt_end = so;
     p.off_x = take((size_t)B * S.Hp * 8);
-    const int bl = std::min(B, S.batched_from - 1);           // per-sequence steps
-    const size_t items_ll = (size_t)nkv * std::max(bl, S.Sg);
+    // sequences of a per-sequence step
+    const int bl = exact && p.batched ? 0 : std::min(B, S.batched_from - 1);
     p.off_qll = take((size_t)bl * c.n_heads * d * 8);
     p.off_kvll = take((size_t)bl * nkv * d * 8);
-    p.off_poll = take(items_ll * g * (d + 2) * 8);
     const int topk = c.n_experts > 1 ? c.top_k : 1;          // expert slots per token
     p.off_mll = take((size_t)bl * topk * S.Fp * 8);
-    p.off_q = take((size_t)B * c.n_heads * d * 4);
-    p.off_act = take((size_t)B * S.Hp * 2 * 2);
-    p.off_actm = take((size_t)B * S.Fp * 2 * 2);
-    p.off_acto = take((size_t)B * S.Ap * 2 * 2);
     if (p.batched) {
+        p.off_q = take((size_t)B * c.n_heads * d * 4);
+        p.off_act = take((size_t)B * S.Hp * 2 * 2);
+        p.off_actm = take((size_t)B * S.Fp * 2 * 2);
+        p.off_acto = take((size_t)B * S.Ap * 2 * 2);
         const size_t qkv_rows = (size_t)nkv * S.qkv_rg * kTileRows;
         p.off_x2 = take((size_t)B * S.Hp * 8);
         p.off_xp = take((size_t)std::max(S.KSo, S.KSd) * B * S.Hp * 4);
@@ -266,6 +268,12 @@ ScratchPlan plan_scratch(const kl_state &S, int B) {
                                  (size_t)S.KSq * B * qkv_rows) * 4);
         p.off_ss = take((size_t)B * nslices * 4);
     }
+    p.base = so;
+    p.off_poll = take((size_t)nkv * (S.Sg + bl) * g * (d + 2) * 8);
+    p.off_xall = take((size_t)bl * S.Hp * 8);
+    p.off_xbll = take((size_t)bl * S.Hp * 8);
+    p.off_oll = take((size_t)bl * S.Ap * 8);
+    p.off_dpll = take((size_t)bl * topk * S.Sc * S.Hp * 8);
     p.total = so;
     return p;
 }
@@ -281,6 +289,10 @@ void bind_scratch(StepParams &P, uint8_t *base, const ScratchPlan &p, const kl_s
     P.kv_ll = reinterpret_cast<unsigned long long *>(base + p.off_kvll);
     P.po_ll = reinterpret_cast<unsigned long long *>(base + p.off_poll);
     P.m_ll = reinterpret_cast<unsigned long long *>(base + p.off_mll);
+    P.xa_ll = reinterpret_cast<unsigned long long *>(base + p.off_xall);
+    P.xb_ll = reinterpret_cast<unsigned long long *>(base + p.off_xbll);
+    P.o_ll = reinterpret_cast<unsigned long long *>(base + p.off_oll);
+    P.dp_ll = reinterpret_cast<unsigned long long *>(base + p.off_dpll);
     P.act = reinterpret_cast<uint16_t *>(base + p.off_act);
     P.act_lo = P.act + (size_t)B * S.Hp;
     P.actm = reinterpret_cast<uint16_t *>(base + p.off_actm);
@@ -323,12 +335,14 @@ void free_state(kl_state *s) {
 //     head      the final RMSNorm's slice counters;
 //     attn      the parts of a sequence split over workgroups;
 //     oproj     none;
-//   per-sequence path, single phases: none (every counter a phase waits on
-//   belongs to an earlier phase).
+//   per-sequence path, single phases:
+//     oproj     the merged attention outputs;
+//     down      the partial sums of the owned residual rows;
+//     others    none (the words a phase polls were written by an earlier one).
 bool launch_waits_inside(int phases, bool batched) {
     if (phases & kPhEmbed) return phases != kPhEmbed;
     if (__builtin_popcount((unsigned)phases) > 1) return true;
-    if (!batched) return false;
+    if (!batched) return phases == kPhOproj || phases == kPhDown;
     return phases != kPhOproj;
 }
 
@@ -358,6 +372,7 @@ StepParams base_params(const kl_state &s) {
     P.dummy = s.arena + s.off_dummy;
     P.nwg = s.nwg;
     P.lds_red = s.lds_red; P.lds_sm = s.lds_sm; P.lds_bar = s.lds_bar;
+    P.own_max = s.own_max;
     P.trace = s.trace;
     P.trace_max = s.trace_max;
     return P;
@@ -441,6 +456,7 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     TRY(hipMalloc(&S->arena, S->arena_bytes));
 
     // grid: one persistent workgroup per CU
+    S->own_max = (S->o_rg + S->nwg - 1) / S->nwg * kTileRows;
     lds_layout_for(*S);
     if (S->lds_bytes > 160 * 1024 - 256)
         return bail(fail(KL_ERR_UNSUPPORTED, "LDS need %d bytes exceeds 160 KiB", S->lds_bytes));
@@ -457,7 +473,7 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     S->KSq = folded_k_slices(KTH, 1, qkv_rows / 16, S->nwg);
 
     // step scratch for the largest batch, zeroed; the device error word
-    S->scratch_bytes = plan_scratch(*S, c.max_batch).total;
+    S->scratch_bytes = plan_scratch(*S, c.max_batch, false).total;
     TRY(hipMalloc(&S->scratch, S->scratch_bytes));
     TRY(hipMemsetAsync(S->scratch, 0, S->scratch_bytes, s));
     TRY(hipMalloc(&S->err, 256));
@@ -659,7 +675,6 @@ static StepParams step_params(const kl_state &st, uint8_t *base, const ScratchPl
     P.kc = reinterpret_cast<uint16_t *>(kv->k); P.vc = reinterpret_cast<uint16_t *>(kv->v);
     P.kv_batch = kv->batch; P.cap = kv->capacity;
     P.logits = logits_out; P.hidden_out = hidden_out;
-    P.C = std::max(1, st.Sg / batch);
     P.batched = batch >= st.batched_from ? 1 : 0;
     // (several sequences share a GEMV pass; the partial sums' place differs
     // between the two paths)
@@ -742,16 +757,16 @@ static kl_status enqueue_step(kl_state *st, const int32_t *token_ids, const int3
     ScratchPlan plan;
     uint8_t *base;
     if (no_alloc) {
-        plan = plan_scratch(*st, batch);
-        if (plan.total > kStaticScratchBytes)
+        plan = plan_scratch(*st, batch, true);
+        if (plan.base > kStaticScratchBytes || plan.total - plan.base > kStaticWordBytes)
             return fail(KL_ERR_UNSUPPORTED,
                         "this step needs %zu bytes of scratch; the static scratch holds %zu "
-                        "(use kl_decode_step)", plan.total, kStaticScratchBytes);
+                        "(use kl_decode_step)", plan.base, kStaticScratchBytes);
         if (!st->static_scratch)
             return fail(KL_ERR_HIP, "the static scratch of device %d is not resolved", st->device);
         base = st->static_scratch;
     } else {
-        plan = plan_scratch(*st, c.max_batch);
+        plan = plan_scratch(*st, c.max_batch, false);
         base = st->scratch;
     }
     const StepParams P = step_params(*st, base, plan, token_ids, positions, batch, kv, logits_out,
@@ -798,7 +813,7 @@ kl_status kl_decode_greedy(kl_state *st, const int32_t *token_ids, const int32_t
     if (!tokens_out || !aligned(tokens_out, 4))
         return fail(KL_ERR_INVALID_ARGUMENT, "tokens_out must be a 4-byte aligned pointer");
     const kl_config &c = st->cfg;
-    StepParams P = step_params(*st, st->scratch, plan_scratch(*st, c.max_batch), token_ids,
+    StepParams P = step_params(*st, st->scratch, plan_scratch(*st, c.max_batch, false), token_ids,
                                positions, batch, kv, logits_out, nullptr);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // step n: positions + n; its head leaves the argmax keys in keys[n % 2],
@@ -828,7 +843,7 @@ kl_status kl_get_device_error(kl_state *st, int32_t *code) {
     if (v & KL_DEVERR_BARRIER) {
         // a timed-out barrier leaves its counters mid-count: start them afresh
         // (the static scratch is cleared by every call that uses it)
-        const ScratchPlan pl = plan_scratch(*st, st->cfg.max_batch);
+        const ScratchPlan pl = plan_scratch(*st, st->cfg.max_batch, false);
         HIP_TRY(hipMemset(st->scratch + pl.off_bar, 0, pl.off_cnt_end - pl.off_bar));
     }
     return fail(KL_ERR_DEVICE_FAULT, "device error word 0x%x", v);
@@ -869,7 +884,7 @@ kl_status kl_get_info(const kl_state *st, kl_info *info) {
     info->mfma_min_batch = st->batched_from;
     info->arena_bytes = (int64_t)st->arena_bytes;
     info->scratch_bytes = (int64_t)st->scratch_bytes;
-    info->noalloc_scratch_bytes = (int64_t)plan_scratch(*st, st->cfg.max_batch).total;
+    info->noalloc_scratch_bytes = (int64_t)plan_scratch(*st, st->cfg.max_batch, true).base;
     info->noalloc_scratch_limit = (int64_t)kStaticScratchBytes;
     return KL_OK;
 }

@@ -15,10 +15,7 @@ namespace kl {
 constexpr int kWaves = 8;                 // compute waves per workgroup
 constexpr int kCtlWave = kWaves;          // the control wave: barriers and counters only
 constexpr int kThreads = (kWaves + 1) * 64;   // threads per workgroup
-constexpr int kOEarly = 4;               // O projection: waves that gather the merge (the rest load early)
 constexpr int kRgBatch = 16;              // row groups reduced per LDS round
-constexpr int kAttnLoads = 5;             // K (and V) loads per lane per sub-chunk, short attention chunks
-constexpr int kAttnRing = 4;              // K (and V) slabs in flight per wave, streaming attention
 // Batched steps (the matrix-core path) run the weight products on the matrix
 // cores.  An activation x enters them as two bf16 terms, hi = bf16(x) and
 // lo = bf16(x - hi), both multiplied into the same fp32 accumulators (about
@@ -49,7 +46,6 @@ constexpr int kGemmActBytes = kGemmBatch * kActStride * 2;   // one term of one 
 constexpr int kGemmLdsBytes = 4 * kGemmActBytes + kWaves * 2048;
 constexpr int kNormCntStride = 64;        // words between batched RMSNorm slice counters
 constexpr int kMaxGroup = 8;              // max query heads per KV head
-constexpr int kMergeChunks = 32;          // attention chunk results merged per LDS round
 constexpr int kDownGather = 8;            // tagged words per control-wave lane per gather round
 constexpr int kBarGroups = kSyncBarGroups;   // first level of the grid barrier
 constexpr int kBarBytes = 8192;           // barrier counters: kBarGroups lines of 256 B
@@ -125,8 +121,13 @@ struct StepParams {
     unsigned long long *q_ll;  // [B][nq*d] rotated queries (fp32)
     unsigned long long *kv_ll; // [B][nkv][d]: new key (d/2 words: bf16 dims i, i + d/2),
                                // then new value (d/2 words: bf16 dims 2j, 2j + 1)
-    unsigned long long *po_ll; // [B][nkv][group][C][d + 2]: chunk outputs, then max and sum
-                               // (batched path: [nkv][Sg][group][d + 2], max in log2 units)
+    unsigned long long *po_ll; // attention parts, [nkv][Sg + B][group][d + 2]: outputs, max
+                               // (log2 units) and sum (batched path: [nkv][Sg][..])
+    unsigned long long *o_ll;  // [B][nq*d] merged attention output (fp32)
+    unsigned long long *xa_ll, *xb_ll;   // [B][Hp] residual after the attention, after the
+                               // layer (fp32; layer l's input has tag epoch + l)
+    unsigned long long *dp_ll; // [B][topk Sc][Hp] down projection's partial sums (fp32)
+    int own_max;               // residual rows a workgroup owns, at most (LDS stride)
     unsigned long long *m_ll;  // [B][Fp] SwiGLU output (fp32)
     // batched path: activations as bf16 hi and lo terms (hi + lo ~ the fp32 value)
     uint16_t *act, *act_lo;    // [max_batch][Hp] normalised activations
@@ -142,7 +143,6 @@ struct StepParams {
     int batched;               // this step runs the matrix-core path (set by the host)
     int multi;                 // per-sequence path: the B <= kMultiSeq sequences share each
                                // GEMV pass (set by the host)
-    int C;                     // attention chunks per (sequence, KV head)
     unsigned long long *trace; // optional phase timestamps (see kl_set_trace), or null
     int trace_max;             // phases recorded per launch
 };
@@ -165,6 +165,9 @@ hipError_t step_kernel_setup(int d, int group, int lds_bytes, int *max_blocks_pe
 // The static scratch of kl_decode_step_noalloc: one array per device, of
 // this many bytes, held until the process ends.
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;
+// It is followed by a reserve for the larger hand-offs as tagged words: up to
+// 7 sequences' down partials in 64 column blocks (experts), 20K rows wide.
+constexpr size_t kStaticWordBytes = size_t(88) << 20;
 // This device's address of the static scratch ('device' must be current);
 // resolved with hipGetSymbolAddress once per device, then cached.
 hipError_t static_scratch_address(int device, uint8_t **out);

@@ -53,12 +53,9 @@ __device__ __forceinline__ float bf_lo(unsigned u) { return __uint_as_float(u <<
 __device__ __forceinline__ float bf_hi(unsigned u) { return __uint_as_float(u & 0xffff0000u); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((unsigned)h << 16); }
 
-// fp32 -> bf16, round to nearest even (NaN stays NaN).
+// fp32 -> bf16, round to nearest even (one conversion instruction on gfx950).
 __device__ __forceinline__ uint16_t f2bf(float f) {
-    unsigned u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));
 }
 
 // The two bf16 terms of a matrix-core activation: hi = bf16(x), lo =
@@ -96,15 +93,42 @@ __device__ __forceinline__ float sum_lanes(float v) {
     else return sum16(v);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-    v = sum16(v);
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+// op(v, v of lane ^ 16) and op(v, v of lane ^ 32) by the row and half swaps
+// of gfx950.  (The shuffle built on the lane index keeps that index live across
+// the whole kernel; spilled, its reload in a staging step waits for every
+// load in flight, the weight ring included.)
+template <class Op>
+__device__ __forceinline__ float xor16(float v, Op &&op) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+template <class Op>
+__device__ __forceinline__ float xor32(float v, Op &&op) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_16_32(float v) {
+    const auto add = [](float a, float b) { return a + b; };
+    return xor32(xor16(v, add), add);
+}
+__device__ __forceinline__ float max_16_32(float v) {
+    const auto mx = [](float a, float b) { return fmaxf(a, b); };
+    return xor32(xor16(v, mx), mx);
+}
+__device__ __forceinline__ float wave_sum(float v) { return sum_16_32(sum16(v)); }
 __device__ __forceinline__ float wave_max(float v) {
-    for (int off = 1; off < 64; off <<= 1) v = fmaxf(v, __shfl_xor(v, off));
-    return v;
+    v = fmaxf(v, dpp<0xB1>(v));
+    v = fmaxf(v, dpp<0x4E>(v));
+    v = fmaxf(v, dpp<0x141>(v));
+    v = fmaxf(v, dpp<0x140>(v));
+    return max_16_32(v);
+}
+// the value of another lane
+__device__ __forceinline__ int from_lane(int v, int lane) {
+    return __builtin_amdgcn_ds_bpermute(lane * 4, v);
+}
+__device__ __forceinline__ float from_lane(float v, int lane) {
+    return __int_as_float(from_lane(__float_as_int(v), lane));
 }
 
 // Sum over the workgroup; every thread gets the same value (fixed order).
@@ -212,11 +236,6 @@ __device__ __forceinline__ long long to_fix(float v) {
 __device__ __forceinline__ float from_fix(long long v) {
     return (float)v * (1.0f / 4294967296.0f);
 }
-__device__ __forceinline__ void add_fix(long long *p, float v) {
-    __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(p),
-                           (unsigned long long)to_fix(v), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ void st_dev_u64(unsigned long long *p, unsigned long long v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -280,6 +299,9 @@ __device__ __forceinline__ unsigned long long *bar_counter(const StepParams &P, 
 // of the tagged hand-offs, into LDS (before any wait; any wave may do it).
 __device__ __forceinline__ unsigned *launch_epoch(const StepParams &P);
 __device__ __forceinline__ void seg_init(const StepParams &P, int lane);
+struct OwnRows { int first, count; };
+__device__ __forceinline__ OwnRows own_rows(const StepParams &P);
+__device__ __forceinline__ long long *own_x(const StepParams &P);
 __device__ __forceinline__ void bar_init(const StepParams &P) {
     // Only this workgroup's own group counter is read: that group cannot
     // complete barrier 0 before this workgroup arrives, so the value rounds
@@ -295,7 +317,7 @@ __device__ __forceinline__ void bar_init(const StepParams &P) {
     } else if (t == 64) {
         *launch_epoch(P) = __hip_atomic_load(P.epoch_ptr, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
-    } else if (P.batched && t >= 128 && t < 192) {
+    } else if (t >= 128 && t < 192) {
         seg_init(P, (int)t - 128);
     } else if (t >= 96 && t < 96 + kMfmaBatch && !P.batched) {
         const int b = (int)t - 96;
@@ -303,6 +325,12 @@ __device__ __forceinline__ void bar_init(const StepParams &P) {
             seq_table(P)[b] = eff_pos(P, b);
             seq_table(P)[kMfmaBatch + b] = seq_ok(P, b) ? 1 : 0;
         }
+    }
+    if (!P.batched) {   // the residual as the launch before left it
+        const OwnRows R = own_rows(P);
+        for (int i = (int)t; i < P.B * R.count; i += kThreads)
+            own_x(P)[(i / R.count) * P.own_max + i % R.count] = (long long)ld_dev_u64(
+                P.xf + (size_t)(i / R.count) * P.Hp + R.first + i % R.count);
     }
     __syncthreads();
 }
@@ -549,6 +577,16 @@ __device__ __forceinline__ int *route_table(const StepParams &P) {
     return reinterpret_cast<int *>(amax_slots(P) + kGemmBatch);
 }
 
+// (then: the workgroup's share of the attention, see seg_init)
+__device__ __forceinline__ int *seg_table(const StepParams &P) {
+    return route_table(P) + 4 * kMfmaBatch;
+}
+// (then, per-sequence path: the residual rows this workgroup owns, int64
+// fixed point [sequence][own_max])
+__device__ __forceinline__ long long *own_x(const StepParams &P) {
+    return reinterpret_cast<long long *>(seg_table(P) + 8);
+}
+
 // ---------------------------------------------------------------- activations
 
 // Control wave only: copy 'bytes' (a multiple of 16; src and dst 16-byte
@@ -581,15 +619,27 @@ constexpr int kStageBatch = 8;
 // scale r = 1 / sqrt(mean(x^2) + eps) applied in the epilogue (rms_scale).
 // Stages a = x g (zero padding) and leaves each wave's partial sum of x^2
 // in sm[wave]; the weight stream starts as soon as a is in LDS, without
-// waiting for a block-wide reduction.
-__device__ __forceinline__ void stage_rms_deferred(const long long *__restrict__ xf,
-                                                   const float *__restrict__ gain, int n, int npad,
-                                                   float *a, float *sm,
+// waiting for a block-wide reduction.  x arrives as tagged words (xw, tag),
+// which the threads poll themselves: the hand-off costs the words' stores and
+// one load round trip, where a grid barrier cost the drain of the adds, its
+// counters' round trip and then the load's.
+__device__ __forceinline__ bool give_up(const StepParams &P, int spins) {
+    if ((spins & 63) == 0 &&
+        (__hip_atomic_load(P.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & KL_DEVERR_BARRIER))
+        return true;
+    if (spins < kSpinLimit) return false;
+    __hip_atomic_fetch_or(P.err, KL_DEVERR_BARRIER, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+__device__ __forceinline__ void stage_rms_deferred(const StepParams &P,
+                                                   const unsigned long long *__restrict__ xw,
+                                                   unsigned tag, const float *__restrict__ gain,
+                                                   int n, int npad, float *a, float *sm,
                                                    const float *esrc = nullptr,
                                                    float *edst = nullptr, int ne = 0) {
     float ss = 0.f;
     for (int i0 = kl_tid(); i0 < npad; i0 += kStageBatch * kThreads) {
-        long long v[kStageBatch];
+        unsigned long long v[kStageBatch];
         float gv[kStageBatch];
         float ev = 0.f;
         const bool first = i0 == (int)kl_tid();
@@ -598,17 +648,23 @@ __device__ __forceinline__ void stage_rms_deferred(const long long *__restrict__
         // waits for its load before the next one is issued)
 #pragma unroll
         for (int k = 0; k < kStageBatch; ++k) {
-            const int i = i0 + k * kThreads, ic = min(i, n - 1);
-            const long long xv = (long long)ld_dev_u64(xf + ic);
-            const float g = gain[ic];
-            v[k] = i < n ? xv : 0ll;
+            const int i = i0 + k * kThreads;
+            const float g = gain[min(i, n - 1)];
             gv[k] = i < n ? g : 0.f;
         }
         if (first && (int)kl_tid() < ne) ev = esrc[kl_tid()];
+        for (int spins = 1;; ++spins) {
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < kStageBatch; ++k) v[k] = ld_dev_u64(xw + min(i0 + k * kThreads, n - 1));
+#pragma unroll
+            for (int k = 0; k < kStageBatch; ++k) ok = ok && ll_current(v[k], tag);
+            if (ok || give_up(P, spins)) break;
+        }
 #pragma unroll
         for (int k = 0; k < kStageBatch; ++k) {
             const int i = i0 + k * kThreads;
-            const float x = from_fix(v[k]);
+            const float x = i < n ? __uint_as_float(ll_value(v[k])) : 0.f;
             ss = fmaf(x, x, ss);
             if (i < npad) a[i] = x * gv[k];
         }
@@ -619,21 +675,22 @@ __device__ __forceinline__ void stage_rms_deferred(const long long *__restrict__
     lds_barrier();
 }
 // The same for sequences 0 .. nb - 1 (nb <= kMultiSeq) together, their loads
-// issued in one batch: sequence b's residual row at xf + b xstride, its
+// issued in one batch: sequence b's words at xw + b xstride, its
 // staged vector at a + b astride, its wave sums at sm + b kSmSeq, and the ne
 // floats esrc(b) -> edst(b).  (Loads for b >= nb repeat sequence nb - 1's
 // and are dropped: every load stays unconditional.)  Half the batch per
 // sequence keeps the loads in flight within the registers the weight ring
-// leaves.  Each sequence's sums are those stage_rms_deferred leaves for it
-// alone only up to the order of the additions: the sum of a thread's terms is
-// taken in the same order, so the values are the same.
+// leaves.  The sum of a thread's terms is taken in the order of
+// stage_rms_deferred, so the values are the same.
 constexpr int kSmSeq = kThreads / 64;   // floats between sequences' wave sums
 constexpr int kStageMulti = 4;          // loads per thread and sequence per batch
 struct NoExtra {   // stage_rms_multi without an extra vector
     __device__ float *operator()(int) const { return nullptr; }
 };
 template <class ESrc, class EDst>
-__device__ __forceinline__ void stage_rms_multi(const long long *__restrict__ xf, int xstride,
+__device__ __forceinline__ void stage_rms_multi(const StepParams &P,
+                                                const unsigned long long *__restrict__ xw,
+                                                int xstride, unsigned tag,
                                                 const float *__restrict__ gain, int n, int npad,
                                                 int nb, float *a, int astride, float *sm,
                                                 ESrc &&esrc, EDst &&edst, int ne) {
@@ -641,24 +698,32 @@ __device__ __forceinline__ void stage_rms_multi(const long long *__restrict__ xf
 #pragma unroll
     for (int bb = 0; bb < kMultiSeq; ++bb) ss[bb] = 0.f;
     for (int i0 = kl_tid(); i0 < npad; i0 += kStageMulti * kThreads) {
-        long long v[kMultiSeq][kStageMulti];
+        unsigned long long v[kMultiSeq][kStageMulti];
         float gv[kStageMulti], ev[kMultiSeq];
         const bool first = i0 == (int)kl_tid();
 #pragma unroll
         for (int k = 0; k < kStageMulti; ++k) {
-            const int i = i0 + k * kThreads, ic = min(i, n - 1);
-            const float g = gain[ic];
+            const int i = i0 + k * kThreads;
+            const float g = gain[min(i, n - 1)];
             gv[k] = i < n ? g : 0.f;
-#pragma unroll
-            for (int bb = 0; bb < kMultiSeq; ++bb) {
-                const long long xv =
-                    (long long)ld_dev_u64(xf + (size_t)min(bb, nb - 1) * xstride + ic);
-                v[bb][k] = i < n ? xv : 0ll;
-            }
         }
         if (first && (int)kl_tid() < ne) {
 #pragma unroll
             for (int bb = 0; bb < kMultiSeq; ++bb) ev[bb] = esrc(min(bb, nb - 1))[kl_tid()];
+        }
+        for (int spins = 1;; ++spins) {
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < kStageMulti; ++k)
+#pragma unroll
+                for (int bb = 0; bb < kMultiSeq; ++bb)
+                    v[bb][k] = ld_dev_u64(xw + (size_t)min(bb, nb - 1) * xstride +
+                                          min(i0 + k * kThreads, n - 1));
+#pragma unroll
+            for (int k = 0; k < kStageMulti; ++k)
+#pragma unroll
+                for (int bb = 0; bb < kMultiSeq; ++bb) ok = ok && ll_current(v[bb][k], tag);
+            if (ok || give_up(P, spins)) break;
         }
 #pragma unroll
         for (int bb = 0; bb < kMultiSeq; ++bb) {
@@ -666,7 +731,7 @@ __device__ __forceinline__ void stage_rms_multi(const long long *__restrict__ xf
 #pragma unroll
                 for (int k = 0; k < kStageMulti; ++k) {
                     const int i = i0 + k * kThreads;
-                    const float x = from_fix(v[bb][k]);
+                    const float x = i < n ? __uint_as_float(ll_value(v[bb][k])) : 0.f;
                     ss[bb] = fmaf(x, x, ss[bb]);
                     if (i < npad) a[bb * astride + i] = x * gv[k];
                 }
@@ -707,7 +772,12 @@ __device__ __forceinline__ float *seq_sm(const StepParams &P, const Lds &S, int 
 // issued before wait() (the grid barrier that publishes the activations) and
 // before stage(b) (which fills a with sequence b's activation vector); each
 // next batch's first loads are issued before the previous batch's reduction.
-constexpr int kGemvDepth = 16;   // tile loads in flight per wave (16 KiB)
+// Tile loads in flight per wave (8 KiB; 16 MB over the chip, 2.5 us of HBM).
+// Twice as many stream no faster, and what a phase waits for at its start
+// (tagged words, activations) queues behind the first ring: 8B shape, batch
+// 1, 2980 us a step against 3129 with 16.
+constexpr int kGemvDepth = 8;
+constexpr int kGemmDepth = 16;   // matrix-core path
 // one sequence's GEMV partial sums in the reduction area (either row sharing)
 constexpr int kRedStride = kWaves * kRgBatch * kTileRows;
 
@@ -719,9 +789,8 @@ constexpr int kRedStride = kWaves * kRgBatch * kTileRows;
 // lanes share (one cache line per wave), and only the consumption of a slot
 // is conditional.
 //
-// A workgroup owns the row groups first, first + stride, ... (count of
-// them).  The phases use stride 1 (a contiguous block per workgroup): a
-// strided assignment (stride = grid size) was measured no faster.
+// A workgroup owns the row groups first .. first + count - 1 (a strided
+// assignment, stride = grid size, was measured no faster).
 struct RgRange { int first, count; };
 __device__ __forceinline__ RgRange own_rgs(int nrg, const StepParams &P) {
     int a, b;
@@ -736,17 +805,16 @@ __device__ __forceinline__ RgRange own_rgs(int nrg, const StepParams &P) {
 //   row-split (short rows): wave w takes whole row groups w, w + kWaves, ...
 //             of the batch and needs no cross-wave sum.
 // Both orders are fixed by the partition alone.
-// Early (the usual case): the first ring of loads is issued before wait() and
-// stage(0), overlapping their latency; otherwise after stage(0), so that the
-// loads stage(0) makes are not queued behind them (a wave's loads complete in
-// order).  Waves from early_from on issue theirs early in either case (they
-// must then take no part in stage's loads).
-template <bool RowSplit, bool Early, bool Split, class Wait, class Stage, class Epi>
+// The first ring of loads is issued before wait() and stage(0), overlapping
+// their latency.
+// KTG > 0: the K range spans several packed matrices of KTG k-tiles per row
+// group each, gstride tiles apart (k-tile kt of row group r is tile
+// (kt / KTG) gstride + r KTG + kt % KTG); 0: one matrix of KT.
+template <bool RowSplit, int KTG, class Wait, class Stage, class Epi>
 __device__ __forceinline__ void gemv_rows(const uint8_t *__restrict__ W, int KT, int first,
-                                          int count, int stride, int B,
-                                          const float *__restrict__ a, float *red,
-                                          const uint8_t *dummy, Wait &&wait, Stage &&stage,
-                                          Epi &&epi, int early_from = kWaves + 1) {
+                                          int count, int B, const float *__restrict__ a,
+                                          float *red, const uint8_t *dummy, Wait &&wait,
+                                          Stage &&stage, Epi &&epi, int gstride = 0) {
     constexpr int U = kGemvDepth;
     constexpr int BATCH = RowSplit ? kWaves * kRgBatch : kRgBatch;   // row groups per LDS round
     // wave-uniform values live in scalar registers, so every branch below is
@@ -762,26 +830,45 @@ __device__ __forceinline__ void gemv_rows(const uint8_t *__restrict__ W, int KT,
     u32x4 buf[U];
     int n = 0, ltile = 0, lk = 0, left = 0;   // batch items; next tile, its k index; tiles left
 
-    // from a wave's last tile of one row group to its first of the next
-    const int jump = (rstep * stride - 1) * KT + (KT - nk) + 1;
+    // from a wave's last tile of one row group to its first of the next, and
+    // (KTG) from the last tile of one packed matrix to the first of the next
+    const int ktr = KTG ? KTG : KT;   // tiles between row groups
+    const int kg0 = KTG ? kt0 / ktr : 0, kr0 = KTG ? kt0 % ktr : kt0;
+    const int jump = KTG ? 0 : (rstep - 1) * KT + (KT - nk) + 1;
+    int lrg = 0, kr = 0, kg = 0;
     // load the next tile of the batch, or the dummy line (branch-free)
     auto load_next = [&]() {
-        const int t = __builtin_amdgcn_readfirstlane(ltile);
         const bool real = left > 0;
-        const u32x4 v = ld_stream_16B(real ? base + (size_t)t * kTileBytes : dummy);
-        const bool wrap = lk + 1 == nk;
-        ltile = real ? ltile + (wrap ? jump : 1) : ltile;
-        lk = real ? (wrap ? 0 : lk + 1) : lk;
-        left = real ? left - 1 : left;
-        return v;
+        if constexpr (KTG != 0) {
+            const int t = __builtin_amdgcn_readfirstlane(kg * gstride + lrg * ktr + kr);
+            const u32x4 v = ld_stream_16B(real ? base + (size_t)t * kTileBytes : dummy);
+            const bool wrap = lk + 1 == nk, over = kr + 1 == ktr;
+            lk = wrap ? 0 : lk + 1;
+            lrg = wrap ? lrg + rstep : lrg;
+            kg = wrap ? kg0 : (over ? kg + 1 : kg);
+            kr = wrap ? kr0 : (over ? 0 : kr + 1);
+            left = real ? left - 1 : left;
+            return v;
+        } else {
+            const int t = __builtin_amdgcn_readfirstlane(ltile);
+            const u32x4 v = ld_stream_16B(real ? base + (size_t)t * kTileBytes : dummy);
+            const bool wrap = lk + 1 == nk;
+            ltile = real ? ltile + (wrap ? jump : 1) : ltile;
+            lk = real ? (wrap ? 0 : lk + 1) : lk;
+            left = real ? left - 1 : left;
+            return v;
+        }
     };
     auto start = [&](int ib) {   // batch of row groups ib .. ib + BATCH - 1
         const int nb = min(BATCH, count - ib);
         const int mine = RowSplit ? (nb > wid ? (nb - wid + kWaves - 1) / kWaves : 0) : nb;
         n = nk * mine;
         left = n;
-        ltile = (first + (ib + (RowSplit ? wid : 0)) * stride) * KT + kt0;
+        lrg = first + ib + (RowSplit ? wid : 0);
+        ltile = lrg * KT + kt0;
         lk = 0;
+        kg = kg0;
+        kr = kr0;
 #pragma unroll
         for (int s = 0; s < U; ++s) buf[s] = load_next();
     };
@@ -789,20 +876,13 @@ __device__ __forceinline__ void gemv_rows(const uint8_t *__restrict__ W, int KT,
     // the control wave takes part in the staging and the epilogue only
     const bool compute = wid < kWaves;
     const bool has_rows = count > 0;
-    // (waves from early_from on issue their first loads early too)
-    const bool early = Early || (Split && wid >= early_from);
-    if (early && has_rows && compute) start(0);
+    if (has_rows && compute) start(0);
     wait();
     if (!has_rows) return;
     for (int b = 0; b < B; ++b) {
         for (int ib = 0; ib < count; ib += BATCH) {
-            if (early) {
-                if ((b > 0 || ib > 0) && compute) start(ib);
-                if (ib == 0) stage(b);
-            } else {
-                if (ib == 0) stage(b);
-                if (compute) start(ib);
-            }
+            if ((b > 0 || ib > 0) && compute) start(ib);
+            if (ib == 0) stage(b);
             const int nrg = min(BATCH, count - ib);
             int cr = RowSplit ? wid : 0, ck = 0;   // batch item of the row group in progress
             float acc = 0.f;
@@ -853,7 +933,7 @@ __device__ __forceinline__ void gemv_rows(const uint8_t *__restrict__ W, int KT,
                         y1 += red[(w * kRgBatch + rgi) * kTileRows + pr + 1];
                     }
                 }
-                epi(b, (first + (ib + rgi) * stride) * kTileRows + pr, y0, y1);
+                epi(b, (first + ib + rgi) * kTileRows + pr, y0, y1);
             }
             lds_barrier();
         }
@@ -873,12 +953,12 @@ __device__ __forceinline__ void gemv_rows(const uint8_t *__restrict__ W, int KT,
 // group's tiles sit in consecutive ring slots, known at compile time in the
 // unrolled loop.
 constexpr int kMultiRg = 4;
-template <bool RowSplit, bool Early, bool Split, class Wait, class Stage, class Epi>
+template <bool RowSplit, int KTG, class Wait, class Stage, class Epi>
 __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, int KT, int first,
-                                                int count, int stride, int B,
-                                                const float *__restrict__ a, int astride,
-                                                float *red, const uint8_t *dummy, Wait &&wait,
-                                                Stage &&stage, Epi &&epi, int early_from) {
+                                                int count, int B, const float *__restrict__ a,
+                                                int astride, float *red, const uint8_t *dummy,
+                                                Wait &&wait, Stage &&stage, Epi &&epi,
+                                                int gstride) {
     constexpr int U = kGemvDepth, NP = kMultiRg;
     static_assert(U % NP == 0, "a ring slot's place in its group must be fixed");
     constexpr int BATCH = RowSplit ? kWaves * kRgBatch : kRgBatch;
@@ -887,20 +967,25 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
     const int row = lane >> 3, sub = lane & 7;
     const int kt0 = RowSplit ? 0 : (wid * KT) / kWaves;
     const int nk = RowSplit ? KT : ((wid + 1) * KT) / kWaves - kt0;
-    const int rsz = (RowSplit ? kWaves : 1) * stride * KT;   // tiles between a wave's row groups
+    // tiles between a wave's row groups, and (KTG) from one packed matrix's
+    // last tile of a row group to the next one's first
+    const int ktr = KTG ? KTG : KT, rsz = (RowSplit ? kWaves : 1) * ktr;
+    const int kover = KTG ? gstride - ktr + 1 : 1;
     const uint8_t *base = W + (size_t)lane * 16;
     const float *abase = a + sub * 8;
     u32x4 buf[U];
     // loads: the wave's row groups gi .. gi + NP - 1 of the batch (mine of
     // them), at k index lk; tile0 = the first row group's first tile
-    int n = 0, mine = 0, tile0 = 0, gi = 0, lk = 0;
+    int n = 0, mine = 0, tile0 = 0, gi = 0, lk = 0, lt = 0, kr = 0;   // (lt: tiles from k index 0)
     auto load_h = [&](int h) {
         const bool real = gi + h < mine;
-        const int t = __builtin_amdgcn_readfirstlane(tile0 + (gi + h) * rsz + lk);
+        const int t = __builtin_amdgcn_readfirstlane(tile0 + (gi + h) * rsz + lt);
         const u32x4 v = ld_stream_16B(real ? base + (size_t)t * kTileBytes : dummy);
         if (h == NP - 1) {
-            const bool wrap = lk + 1 == nk;
+            const bool wrap = lk + 1 == nk, over = KTG && kr + 1 == ktr;
             lk = wrap ? 0 : lk + 1;
+            lt = wrap ? 0 : lt + (over ? kover : 1);
+            kr = wrap ? (KTG ? kt0 % ktr : 0) : (over ? 0 : kr + 1);
             gi = wrap ? gi + NP : gi;
         }
         return v;
@@ -909,28 +994,22 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
         const int nb = min(BATCH, count - ib);
         mine = RowSplit ? (nb > wid ? (nb - wid + kWaves - 1) / kWaves : 0) : nb;
         n = nk * NP * ((mine + NP - 1) / NP);
-        tile0 = (first + (ib + (RowSplit ? wid : 0)) * stride) * KT + kt0;
-        gi = 0;
-        lk = 0;
+        tile0 = (first + ib + (RowSplit ? wid : 0)) * ktr +
+                (KTG ? (kt0 / ktr) * gstride + kt0 % ktr : kt0);
+        gi = lk = lt = 0;
+        kr = KTG ? kt0 % ktr : 0;
 #pragma unroll
         for (int s = 0; s < U; ++s) buf[s] = load_h(s % NP);
     };
     const bool compute = wid < kWaves;
     const bool has_rows = count > 0;
-    const bool early = Early || (Split && wid >= early_from);
-    if (early && has_rows && compute) start(0);
+    if (has_rows && compute) start(0);
     wait();
     if (!has_rows) return;
     for (int ib = 0; ib < count; ib += BATCH) {
-        if (early) {
-            if (ib > 0 && compute) start(ib);
-            if (ib == 0)
-                for (int bb = 0; bb < B; ++bb) stage(bb);
-        } else {
-            if (ib == 0)
-                for (int bb = 0; bb < B; ++bb) stage(bb);
-            if (compute) start(ib);
-        }
+        if (ib > 0 && compute) start(ib);
+        if (ib == 0)
+            for (int bb = 0; bb < B; ++bb) stage(bb);
         const int nrg = min(BATCH, count - ib);
         int cr = 0, ck = 0;   // the group in progress (its first row group), its k index
         float acc[NP][kMultiSeq];
@@ -1010,7 +1089,7 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
                     y1 += rd[(w * kRgBatch + rgi) * kTileRows + pr + 1];
                 }
             }
-            epi(bb, (first + (ib + rgi) * stride) * kTileRows + pr, y0, y1);
+            epi(bb, (first + ib + rgi) * kTileRows + pr, y0, y1);
         }
         lds_barrier();
     }
@@ -1019,26 +1098,23 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
 // Row groups are shared split-K when they are long enough for every wave to
 // hold two or more tiles, else row-split.  Multi: the B sequences share each
 // pass (gemv_rows_multi).
-template <bool Early, bool Split = false, bool Multi = false, class Wait, class Stage, class Epi>
+template <bool Multi = false, int KTG = 0, class Wait, class Stage, class Epi>
 __device__ __forceinline__ void gemv_phase(const uint8_t *__restrict__ W, int KT, int first,
-                                           int count, int stride, int B,
-                                           const float *__restrict__ a, float *red,
-                                           const uint8_t *dummy, Wait &&wait, Stage &&stage,
-                                           Epi &&epi, int early_from = kWaves + 1,
-                                           int astride = 0) {
+                                           int count, int B, const float *__restrict__ a,
+                                           float *red, const uint8_t *dummy, Wait &&wait,
+                                           Stage &&stage, Epi &&epi, int astride = 0,
+                                           int gstride = 0) {
     if constexpr (Multi) {
         if (KT >= 2 * kWaves)
-            gemv_rows_multi<false, Early, Split>(W, KT, first, count, stride, B, a, astride, red,
-                                                 dummy, wait, stage, epi, early_from);
+            gemv_rows_multi<false, KTG>(W, KT, first, count, B, a, astride, red, dummy, wait, stage,
+                                        epi, gstride);
         else
-            gemv_rows_multi<true, Early, Split>(W, KT, first, count, stride, B, a, astride, red,
-                                                dummy, wait, stage, epi, early_from);
+            gemv_rows_multi<true, KTG>(W, KT, first, count, B, a, astride, red, dummy, wait, stage,
+                                       epi, gstride);
     } else if (KT >= 2 * kWaves) {
-        gemv_rows<false, Early, Split>(W, KT, first, count, stride, B, a, red, dummy, wait, stage,
-                                       epi, early_from);
+        gemv_rows<false, KTG>(W, KT, first, count, B, a, red, dummy, wait, stage, epi, gstride);
     } else {
-        gemv_rows<true, Early, Split>(W, KT, first, count, stride, B, a, red, dummy, wait, stage,
-                                      epi, early_from);
+        gemv_rows<true, KTG>(W, KT, first, count, B, a, red, dummy, wait, stage, epi, gstride);
     }
 }
 
@@ -1115,7 +1191,7 @@ __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, in
                                                int count, int ktg, size_t gstride, int b0,
                                                int nb, const uint8_t *dummy, const GemmLds &L,
                                                Pre &&pre, Stage &&stage, Epi &&epi) {
-    constexpr int U = kGemvDepth;
+    constexpr int U = kGemmDepth;
     constexpr int CT = kGemmChunkK / kTileK;   // k-tiles per chunk
     constexpr int MB = kGemmMaxBlk;
     static_assert(U == 2 * CT, "a ring pass is one chunk of one 16-row block");
@@ -1310,8 +1386,8 @@ struct NoGroupDone {
 // Per-sequence path: with P.multi, the sequences' vectors sit astride floats
 // apart and share each pass (stage1(b) is called for every b before the
 // pass; stage1(0) may stage them all).
-template <bool BAT, bool Early = true, class Wait, class Prep, class Stage1, class StageB,
-          class Epi, class Done = NoGroupDone>
+template <bool BAT, class Wait, class Prep, class Stage1, class StageB, class Epi,
+          class Done = NoGroupDone>
 __device__ __forceinline__ void weight_phase(const StepParams &P, const Lds &S,
                                              const uint8_t *W, int KT, int first, int count,
                                              Wait &&wait, Prep &&prep, Stage1 &&stage1,
@@ -1320,11 +1396,10 @@ __device__ __forceinline__ void weight_phase(const StepParams &P, const Lds &S,
                                              int astride = 0) {
     if constexpr (!BAT) {
         if (P.multi)
-            gemv_phase<Early, false, true>(W, KT, first, count, 1, P.B, S.a, S.red, P.dummy, wait,
-                                           stage1, epi, kWaves + 1, astride);
+            gemv_phase<true>(W, KT, first, count, P.B, S.a, S.red, P.dummy, wait, stage1, epi,
+                             astride);
         else
-            gemv_phase<Early>(W, KT, first, count, 1, P.B, S.a, S.red, P.dummy, wait, stage1,
-                              epi);
+            gemv_phase(W, KT, first, count, P.B, S.a, S.red, P.dummy, wait, stage1, epi);
         return;
     }
     const GemmLds L = gemm_lds(kl_smem);
@@ -1496,6 +1571,63 @@ __device__ __forceinline__ void stage_bf16_chunk(const uint16_t *src, const uint
     ctl_copy_rows(src, src_lo, ld, k0, min(kGemmChunkK, K - k0), b0, nb, buf);
 }
 
+// Per-sequence path: the residual has one owner per row, the workgroup that
+// has the row's O projection (own_rows), which keeps it in LDS (own_x; a copy
+// in memory for later launches) and publishes each new value as the float
+// that the next RMSNorm reads, as tagged words.  The down projection's
+// partial sums come to the owner as tagged words too, one per FFN column
+// block (and expert slot), each rounded to the fixed-point grid and added:
+// the same exact sum as by atomics, without their traffic (one 8-byte
+// read-modify-write per partial at memory) and without the drain and the
+// grid barrier that a sum by many writers needs before it can be read.
+__device__ __forceinline__ OwnRows own_rows(const StepParams &P) {
+    int a, b;
+    split_range(P.o_rg, P.nwg, blockIdx.x, a, b);
+    return OwnRows{a * kTileRows, (b - a) * kTileRows};
+}
+// row r of this workgroup's (sequence b) := x, published in 'words' with 'tag'
+__device__ __forceinline__ void put_x(const StepParams &P, int b, int r, const OwnRows &R,
+                                      long long x, unsigned long long *words, unsigned tag) {
+    const size_t i = (size_t)b * P.Hp + R.first + r;
+    own_x(P)[b * P.own_max + r] = x;
+    st_ll_f(words + i, from_fix(x), tag);
+    st_dev_u64(reinterpret_cast<unsigned long long *>(P.xf + i), (unsigned long long)x);
+}
+// Control wave, after layer l's down projection: the owned rows' partial sums
+// (nj per row and sequence), the new residual.
+__device__ __forceinline__ void gather_down(const StepParams &P, int l, int nj) {
+    const OwnRows R = own_rows(P);
+    const int n = nj * R.count, lane = kl_tid() & 63;
+    if (n == 0) return;
+    for (int b = 0; b < P.B; ++b) {
+        const unsigned long long *src = P.dp_ll + (size_t)b * nj * P.Hp + R.first;
+        unsigned long long *own = reinterpret_cast<unsigned long long *>(own_x(P) + b * P.own_max);
+        ll_gather<8>(
+            P, n, ll_tag(P, l), lane, 64,
+            [&](int i) { return src + (size_t)(i / R.count) * P.Hp + i % R.count; },
+            [&](int i, unsigned v) {
+                __hip_atomic_fetch_add(own + i % R.count,
+                                       (unsigned long long)to_fix(__uint_as_float(v)),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            });
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane; i < P.B * R.count; i += 64) {
+        const int b = i / R.count, r = i % R.count;
+        put_x(P, b, r, R, own_x(P)[b * P.own_max + r], P.xb_ll, ll_tag(P, l + 1));
+    }
+}
+
+// Before the threads poll for the residual after a down projection: this
+// workgroup's own rows have arrived at their owner (the control wave comes
+// here from gather_down), so the others' are about to.  Without it every
+// workgroup that is early polls the whole residual over and over, 8 MB a round
+// across the chip, and the words the others wait for queue behind that.
+__device__ __forceinline__ void owners_wait(const StepParams &P, int ti) {
+    lds_barrier();
+    if (is_ctl_lane0()) trace_stamp(P, ti, 1);
+}
+
 // Embedding block (Sec. 2): x = E[token] (exact in fixed point).  Workgroup 0
 // records bad token ids and positions, and zeroes the local counters.
 __device__ __forceinline__ void phase_embed(KArg ka, int gwait, int garrive, int ti) {
@@ -1517,6 +1649,17 @@ __device__ __forceinline__ void phase_embed(KArg ka, int gwait, int garrive, int
                        (P.batched ? kNormCntStride * ((P.Hp + kGemmChunkK - 1) / kGemmChunkK) : 0);
         for (int i = kl_tid(); i < nc; i += kThreads)
             __hip_atomic_store(P.cnt + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!P.batched) {   // every workgroup its own residual rows, published as layer 0's input
+        const OwnRows R = own_rows(P);
+        for (int i = kl_tid(); i < P.B * R.count; i += kThreads) {
+            const int b = i / R.count, r = i % R.count;
+            put_x(P, b, r, R, to_fix(bf2f(P.embed[(size_t)eff_tok(P, b) * P.H + R.first + r])),
+                  P.xb_ll, ll_tag(P, 0));
+        }
+        lds_barrier();
+        if (is_ctl_lane0()) trace_stamp(P, ti, 0);
+        return;
     }
     const int total = P.B * P.Hp;
     for (int idx = blockIdx.x * kThreads + kl_tid(); idx < total; idx += P.nwg * kThreads) {
@@ -1670,7 +1813,7 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
     const int row0 = g * P.qkv_rg * kTileRows;   // first packed row of head g's block
     weight_phase<false>(
         P, S, Lb + P.off_qkv, P.Hp / kTileK, g * P.qkv_rg + a0, a1 - a0,
-        [&]() { if (gwait >= 0) bar_wait(P, gwait, ti); }, [&]() {},
+        [&]() { owners_wait(P, ti); }, [&]() {},
         [&](int b) {
             // the RoPE row of the sequence's position rides along (rope_row)
             auto rsrc = [&](int bb) {
@@ -1679,11 +1822,12 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
             };
             if (P.multi) {
                 if (b == 0)
-                    stage_rms_multi(P.xf, P.Hp, gain, P.H, P.Hp, P.B, S.a, P.Hp, S.sm, rsrc,
+                    stage_rms_multi(P, P.xb_ll, P.Hp, ll_tag(P, l), gain, P.H, P.Hp, P.B, S.a, P.Hp,
+                                    S.sm, rsrc,
                                     [&](int bb) { return rope_row(P, S, bb); }, 2 * half);
             } else {
-                stage_rms_deferred(P.xf + (size_t)b * P.Hp, gain, P.H, P.Hp, S.a, S.sm, rsrc(b),
-                                   rope_row(P, S, b), 2 * half);
+                stage_rms_deferred(P, P.xb_ll + (size_t)b * P.Hp, ll_tag(P, l), gain, P.H, P.Hp, S.a,
+                                   S.sm, rsrc(b), rope_row(P, S, b), 2 * half);
             }
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
         },
@@ -1707,588 +1851,7 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
     if (is_ctl_lane0()) trace_stamp(P, ti, 0);
 }
 
-// The merged attention output of query head hq of KV head g for sequence b
-// (Sec. 2 attention, split over the context): o = sum_c w_c A_c / sum_c w_c
-// L_c with w_c = exp(M_c - M), M the largest chunk maximum, over the C chunk
-// results (A_c the unnormalised output, M_c the maximum, L_c the sum of the
-// chunk).  The results arrive as tagged words, kMergeChunks chunks per round;
-// a later round rescales the running sums to its new maximum.  Chunks are
-// taken in order, so the sums are the same in every schedule.  Threads
-// 0 .. NT - 1 gather the results; leaves o[0 .. D) (LDS), with the LDS
-// area scr for the chunk results.
-template <int D, int G, int NT = kThreads>
-__device__ __forceinline__ void merge_ll(const StepParams &P, int l, int b, int g, int hq,
-                                         float *o, float *scr) {
-    constexpr int WD = D + 2;                       // words per chunk and head
-    float *wts = scr;                               // [kMergeChunks]
-    float *run = wts + kMergeChunks;                // running max, running sum, rescale
-    float *raw = run + 4;                           // [kMergeChunks][D + 2] values
-    const unsigned tag = ll_tag(P, l);
-    const int C = P.C;
-    // chunk c's words of query head hq: src + c (D + 2) + j (contiguous)
-    const unsigned long long *src = P.po_ll + (((size_t)b * P.nkv + g) * G + hq) * C * WD;
-    auto val = [&](int i) { return raw[i]; };
-    for (int c0 = 0; c0 < C; c0 += kMergeChunks) {
-        const int nc = min(kMergeChunks, C - c0);
-        if (NT == kThreads || kl_tid() < NT)
-            ll_gather<(kMergeChunks * WD + NT - 1) / NT>(
-                P, nc * WD, tag, kl_tid(), NT, [&](int i) { return src + (size_t)c0 * WD + i; },
-                [&](int i, unsigned v) { raw[i] = __uint_as_float(v); });
-        lds_barrier();
-        if (kl_tid() < 64) {   // wave 0: this round's chunk weights and sum
-            const int lane = kl_tid();
-            float mx = -INFINITY;
-            for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, val(c * WD + D));
-            mx = wave_max(mx);
-            const float mold = c0 == 0 ? -INFINITY : run[0];
-            const float mnew = fmaxf(mold, mx);
-            float den = 0.f;
-            for (int c = lane; c < nc; c += 64) {
-                const float m = val(c * WD + D);
-                const float w = (m == -INFINITY) ? 0.f : expf(m - mnew);
-                wts[c] = w;
-                den = fmaf(val(c * WD + D + 1), w, den);
-            }
-            den = wave_sum(den);
-            if (lane == 0) {
-                const float resc = (mold == -INFINITY) ? 0.f : expf(mold - mnew);
-                run[1] = (c0 == 0 ? 0.f : run[1] * resc) + den;
-                run[2] = resc;
-                run[0] = mnew;
-            }
-        }
-        lds_barrier();
-        for (int t = kl_tid(); t < D; t += kThreads) {
-            float acc = c0 == 0 ? 0.f : o[t] * run[2];
-            for (int c = 0; c < nc; ++c) acc = fmaf(wts[c], val(c * WD + t), acc);
-            o[t] = acc;
-        }
-        lds_barrier();
-    }
-    for (int t = kl_tid(); t < D; t += kThreads) o[t] = o[t] / run[1];
-    lds_barrier();
-}
-// The same for sequences 0 .. nb - 1 together (nb C <= kMergeChunks): one
-// gather of all their chunk results, then wave b forms sequence b's chunk
-// weights and sum; sequence b's output goes to S.a + b D.  Each output is
-// the one merge_ll gives for its sequence alone (a single round there).
-template <int D, int G, int NT = kThreads>
-__device__ __forceinline__ void merge_ll_multi(const StepParams &P, int l, int nb, int g, int hq,
-                                               const Lds &S) {
-    constexpr int WD = D + 2;
-    float *wts = S.a + kMultiSeq * D;               // [nb][C]
-    float *den = wts + kMergeChunks;                // [nb]
-    float *raw = den + 4;                           // [nb][C][D + 2] values
-    const unsigned tag = ll_tag(P, l);
-    const int C = P.C, per = C * WD;
-    const size_t sstride = (size_t)P.nkv * G * per;   // words between sequences
-    const unsigned long long *src = P.po_ll + ((size_t)g * G + hq) * per;
-    if (NT == kThreads || kl_tid() < NT)
-        ll_gather<(kMergeChunks * WD + NT - 1) / NT>(
-            P, nb * per, tag, kl_tid(), NT,
-            [&](int i) {
-                const int bb = i / per;
-                return src + bb * sstride + (i - bb * per);
-            },
-            [&](int i, unsigned v) { raw[i] = __uint_as_float(v); });
-    lds_barrier();
-    const int wid = kl_tid() >> 6;
-    if (wid < nb) {
-        const int lane = kl_tid() & 63;
-        const float *rv = raw + wid * per;
-        float mx = -INFINITY;
-        for (int c = lane; c < C; c += 64) mx = fmaxf(mx, rv[c * WD + D]);
-        mx = wave_max(mx);
-        float dn = 0.f;
-        for (int c = lane; c < C; c += 64) {
-            const float m = rv[c * WD + D];
-            const float w = (m == -INFINITY) ? 0.f : expf(m - mx);
-            wts[wid * C + c] = w;
-            dn = fmaf(rv[c * WD + D + 1], w, dn);
-        }
-        dn = wave_sum(dn);
-        if (lane == 0) den[wid] = 0.f + dn;
-    }
-    lds_barrier();
-    for (int t = kl_tid(); t < nb * D; t += kThreads) {
-        const int bb = t / D, j = t - bb * D;
-        const float *rv = raw + bb * per;
-        float acc = 0.f;
-        for (int c = 0; c < C; ++c) acc = fmaf(wts[bb * C + c], rv[c * WD + j], acc);
-        S.a[bb * D + j] = acc / den[bb];
-    }
-    lds_barrier();
-}
-
-// One attention work item of the per-sequence path with up to 4 query heads
-// per KV head, where a chunk is short (at batch 1: 128 positions): chunk c of
-// sequence b against KV head g, for the G query heads of that group
-// (split-K flash decoding).  Positions are grouped in slabs of PP positions
-// (one 16-byte load per lane covers a slab); chunk c owns a contiguous range
-// of slabs, and inside a sub-chunk slab q is held by wave q % kWaves, so
-// every compute wave takes part even when a chunk is short.  The scores of a
-// sub-chunk go through LDS to a block softmax (wave h for head h), then the
-// values.  Scores and probabilities are fp32.  The chunk's K/V vectors are
-// loaded before the wait for the queries, except the new slot, which the
-// Q/K/V phase hands over as tagged words with the queries; loads are
-// unconditional (spare ones target a shared 16-byte line) and masked when
-// consumed.  The chunk result (max, sum, unnormalised output per head)
-// leaves as tagged words.  (At these chunk lengths this form measured
-// faster than the streaming item below: 9.8 against 10.6 us per layer.)
-template <int D, int NG>
-constexpr int attn_sub() { return kWaves * NG * (64 / (D / 8)); }
-
-template <int D, int G>
-__device__ __forceinline__ void attn_item_ll(KArg ka, int l, int b, int g, int c, int ti) {
-    const StepParams P = load_params(ka);
-    const Lds S = lds_layout(kl_smem, P);
-    constexpr int LP = D / 8;                       // lanes per position
-    constexpr int PP = 64 / LP;                     // positions per slab
-    constexpr int NG = kAttnLoads;                  // slabs per wave per sub-chunk
-    constexpr int SUB = attn_sub<D, NG>();          // positions per sub-chunk
-    const int wid = __builtin_amdgcn_readfirstlane(kl_tid() >> 6);
-    const int lane = kl_tid() & 63;
-    const int pi = lane / LP, ds = (lane % LP) * 8;
-    const int pnew = pos_of<true>(P, b), n = pnew + 1;
-    int s0, s1;
-    split_range((n + PP - 1) / PP, P.C, c, s0, s1);
-    const int j0 = min(n, s0 * PP), j1 = min(n, s1 * PP);
-    const bool compute = wid < kWaves;
-
-    float *qs = S.attn;                 // [G][D]
-    float *sp = qs + G * D;             // [G][SUB]
-    float *st = sp + G * SUB;           // [G][4]: max, sum, rescale
-    float *red = st + G * 4;            // [kWaves][G][D]
-    uint16_t *kn = reinterpret_cast<uint16_t *>(red + kWaves * G * D);   // [D] new key
-    uint16_t *vn = kn + D;                                               // [D] new value
-    const size_t row0 = kv_row(P, l, b, g);
-    const uint16_t *Kb = P.kc + row0 * D;
-    const uint16_t *Vb = P.vc + row0 * D;
-    const float scale = 1.0f / sqrtf((float)D);
-
-    // local position of (wave, load t) in a sub-chunk
-    auto jloc = [&](int t) { return (t * kWaves + wid) * PP + pi; };
-    u32x4 kr[NG], vr[NG];
-    // K (or V) vectors of a sub-chunk; the next sub-chunk's K is issued once
-    // the scores have used this one's, and its V once the values have (the
-    // loop is software-pipelined over sub-chunks)
-    auto issue_one = [&](u32x4 *r, const uint16_t *base, int js, int len) {
-#pragma unroll
-        for (int t = 0; t < NG; ++t) {
-            const int jl = jloc(t), pos = js + jl;
-            const bool real = jl < len && pos != pnew;
-            r[t] = ld_stream_16B(real ? (const void *)(base + (size_t)pos * D + ds) : P.dummy);
-        }
-    };
-    if (compute) {   // (the control wave keeps its load queue empty for the barrier)
-        issue_one(kr, Kb, j0, min(SUB, j1 - j0));
-        issue_one(vr, Vb, j0, min(SUB, j1 - j0));
-    }
-    // the new slot (written during this step by another workgroup) arrives
-    // as tagged words; the lanes that hold it take it from LDS after the wait,
-    // into registers of their own, in place of their ring value (no ring
-    // load is conditional, so the compiler's waits for the ring stay exact)
-    u32x4 knew = {0u, 0u, 0u, 0u}, vnew = {0u, 0u, 0u, 0u};
-    const int pl = (pnew - j0) % SUB;   // its place in its sub-chunk
-    const bool holds_new =
-        compute && pnew >= j0 && pnew < j1 && (pl / PP) % kWaves == wid && pl % PP == pi;
-    {
-        // the queries of head g's query heads and the new key and value, as
-        // tagged words (every thread takes a few), into LDS
-        if (is_ctl_lane0()) trace_stamp(P, ti, 1);
-        const size_t qo = (size_t)b * P.nq * D + (size_t)g * G * D;
-        const unsigned long long *kvl = P.kv_ll + ((size_t)b * P.nkv + g) * D;
-        ll_gather<(G * D + D + kThreads - 1) / kThreads>(
-            P, G * D + D, ll_tag(P, l), kl_tid(), kThreads,
-            [&](int i) { return i < G * D ? P.q_ll + qo + i : kvl + (i - G * D); },
-            [&](int i, unsigned v) {
-                if (i < G * D) {
-                    qs[i] = __uint_as_float(v);
-                } else if (i < G * D + D / 2) {   // key dims j and j + D/2
-                    const int j = i - G * D;
-                    kn[j] = (uint16_t)v;
-                    kn[j + D / 2] = (uint16_t)(v >> 16);
-                } else {                           // value dims 2j and 2j + 1
-                    reinterpret_cast<unsigned *>(vn)[i - G * D - D / 2] = v;
-                }
-            });
-    }
-    if (kl_tid() < G) {
-        st[kl_tid() * 4 + 0] = -INFINITY;
-        st[kl_tid() * 4 + 1] = 0.f;
-    }
-    lds_barrier();
-    if (is_ctl_lane0()) trace_stamp(P, ti, 2);
-    if (holds_new) {
-        knew = *reinterpret_cast<const u32x4 *>(kn + ds);
-        vnew = *reinterpret_cast<const u32x4 *>(vn + ds);
-    }
-    float acc[G][8];
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
-
-    // (the loop is split by role: in the compute waves' copy every ring load
-    // is consumed on every path, so the compiler's waits stay exact; the
-    // control wave takes part in the barriers only)
-    if (!compute) {
-        for (int js = j0; js < j1; js += SUB) {
-            lds_barrier();
-            lds_barrier();
-            lds_barrier();
-        }
-    } else {
-        // one sub-chunk; refill: issue the next sub-chunk's loads (every
-        // sub-chunk but the last; decided at run time: a chunk is mostly one
-        // sub-chunk here, where a peeled last copy costs more code than its
-        // exact waits gain)
-        auto sub_chunk = [&](int js, auto refill) {
-            const int len = min(SUB, j1 - js);
-            const int jn = js + SUB, lenn = min(SUB, j1 - jn);   // the next sub-chunk
-            // scores (q is read from LDS; all lanes take part in the lane sums)
-            {
-#pragma unroll
-                for (int t = 0; t < NG; ++t) {
-                    const int jl = jloc(t);
-                    const u32x4 kv = js + jl == pnew ? knew : kr[t];
-                    const float kf[8] = {bf_lo(kv.x), bf_hi(kv.x), bf_lo(kv.y), bf_hi(kv.y),
-                                         bf_lo(kv.z), bf_hi(kv.z), bf_lo(kv.w), bf_hi(kv.w)};
-#pragma unroll
-                    for (int h = 0; h < G; ++h) {
-                        const float4 q0 = *reinterpret_cast<const float4 *>(qs + h * D + ds);
-                        const float4 q1 = *reinterpret_cast<const float4 *>(qs + h * D + ds + 4);
-                        float s = 0.f;
-                        s = fmaf(q0.x, kf[0], s);
-                        s = fmaf(q0.y, kf[1], s);
-                        s = fmaf(q0.z, kf[2], s);
-                        s = fmaf(q0.w, kf[3], s);
-                        s = fmaf(q1.x, kf[4], s);
-                        s = fmaf(q1.y, kf[5], s);
-                        s = fmaf(q1.z, kf[6], s);
-                        s = fmaf(q1.w, kf[7], s);
-                        s = sum_lanes<LP>(s);
-                        if (jl < len && (lane % LP) == 0) sp[h * SUB + jl] = s * scale;
-                    }
-                }
-            }
-            if (bool(refill)) issue_one(kr, Kb, jn, lenn);
-            lds_barrier();
-            // softmax statistics: wave h owns head h
-            if (wid < G) {
-                const int h = wid;
-                float mx = -INFINITY;
-                for (int j = lane; j < len; j += 64) mx = fmaxf(mx, sp[h * SUB + j]);
-                mx = wave_max(mx);
-                const float mold = st[h * 4], mnew = fmaxf(mold, mx);
-                const float resc = (mold == -INFINITY) ? 0.f : expf(mold - mnew);
-                float sum = 0.f;
-                for (int j = lane; j < len; j += 64) {
-                    const float e = expf(sp[h * SUB + j] - mnew);
-                    sp[h * SUB + j] = e;
-                    sum += e;
-                }
-                sum = wave_sum(sum);
-                if (lane == 0) {
-                    st[h * 4 + 0] = mnew;
-                    st[h * 4 + 1] = st[h * 4 + 1] * resc + sum;
-                    st[h * 4 + 2] = resc;
-                }
-            }
-            lds_barrier();
-            // values
-            {
-#pragma unroll
-                for (int h = 0; h < G; ++h) {
-                    const float r = st[h * 4 + 2];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[h][e] *= r;
-                }
-#pragma unroll
-                for (int t = 0; t < NG; ++t) {
-                    const int jl = jloc(t);
-                    if (jl < len) {
-                        const u32x4 vv = js + jl == pnew ? vnew : vr[t];
-                        const float vf[8] = {bf_lo(vv.x), bf_hi(vv.x), bf_lo(vv.y), bf_hi(vv.y),
-                                             bf_lo(vv.z), bf_hi(vv.z), bf_lo(vv.w), bf_hi(vv.w)};
-#pragma unroll
-                        for (int h = 0; h < G; ++h) {
-                            const float pr = sp[h * SUB + jl];
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) acc[h][e] = fmaf(pr, vf[e], acc[h][e]);
-                        }
-                    }
-                }
-            }
-            if (bool(refill)) issue_one(vr, Vb, jn, lenn);
-            lds_barrier();
-        };
-        for (int js = j0; js < j1; js += SUB) sub_chunk(js, js + SUB < j1);
-    }
-    // reduce the PP position slots of each wave, then the waves in order
-    if (compute) {
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float v = acc[h][e];
-#pragma unroll
-                for (int off = LP; off < 64; off <<= 1) v += __shfl_xor(v, off);
-                acc[h][e] = v;
-            }
-        if (pi == 0) {
-#pragma unroll
-            for (int h = 0; h < G; ++h)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) red[(wid * G + h) * D + ds + e] = acc[h][e];
-        }
-    }
-    lds_barrier();
-    // publish: unnormalised outputs [G][D] and (max, sum) per head
-    {
-        // tagged words, per query head h: outputs, max, sum (D + 2 words at
-        // [b][g][h][c]: the chunks of one query head are contiguous for the
-        // O projection, which polls them; no drain, no counter)
-        const unsigned tag = ll_tag(P, l);
-        unsigned long long *out = P.po_ll + (((size_t)b * P.nkv + g) * G * P.C + c) * (D + 2);
-        const size_t hstride = (size_t)P.C * (D + 2);
-        for (int t = kl_tid(); t < G * D; t += kThreads) {
-            const int h = t / D, dd = t % D;
-            float s = 0.f;
-            for (int w = 0; w < kWaves; ++w) s += red[(w * G + h) * D + dd];
-            st_ll_f(out + h * hstride + dd, s, tag);
-        }
-        if (kl_tid() < G) {
-            st_ll_f(out + kl_tid() * hstride + D, st[kl_tid() * 4 + 0], tag);
-            st_ll_f(out + kl_tid() * hstride + D + 1, st[kl_tid() * 4 + 1], tag);
-        }
-    }
-    if (is_ctl_lane0()) trace_stamp(P, ti, 3);
-    lds_barrier();   // (the attention area is the next item's)
-}
-
-
-// Streaming attention item (per-sequence path with 8 query heads per KV
-// head): each compute
-// wave streams its own slabs of the chunk (slabs w, w + kWaves, ...; a slab
-// is PP positions, one 16-byte load per lane) through a ring of kAttnRing K
-// and kAttnRing V loads that is refilled as it is consumed, and each lane
-// group (the LP lanes of one position) keeps its own running softmax per
-// query head: max m, sum l and the unnormalised output over its 8 dims,
-// updated once per kAttnRing slabs (their scores first, one rescale by
-// 2^(m_old - m_new) when the max grows, then their values; scores are kept
-// in log2 units, so every weight is one hardware exp2).  No block barrier in
-// the loop: the PP lane groups of a wave are merged by shuffles, the waves in
-// order through LDS.  The queries are held in registers.  The new slot
-// (written this step by another workgroup) arrives as tagged words and is
-// taken from LDS; its ring load targets a shared dummy line.  Outputs: the
-// chunk's (max, sum, unnormalised output) as tagged words.
-template <int D, int G>
-__device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, int c, int ti) {
-    const StepParams P = load_params(ka);
-    const Lds S = lds_layout(kl_smem, P);
-    constexpr int LP = D / 8;                       // lanes per position
-    constexpr int PP = 64 / LP;                     // positions per slab
-    constexpr int R = kAttnRing;
-    // more than 4 query heads per KV head: the waves split into NH teams of
-    // HG heads each; every team streams the whole chunk (the second team's
-    // loads of the same lines meet them in L2)
-    constexpr int HG = G < 4 ? G : 4, NH = G / HG, TW = kWaves / NH;
-    static_assert(G % HG == 0 && kWaves % NH == 0, "head teams");
-    const int wid = __builtin_amdgcn_readfirstlane(kl_tid() >> 6);
-    const int team = wid / TW, tw = wid % TW;      // (the control wave: team NH)
-    const int h0 = team * HG;                      // the team's first query head
-    const int lane = kl_tid() & 63;
-    const int pi = lane / LP, ds = (lane % LP) * 8;
-    const int pnew = pos_of<true>(P, b), n = pnew + 1;
-    int s0, s1;
-    split_range((n + PP - 1) / PP, P.C, c, s0, s1);
-    const bool compute = wid < kWaves;
-    // this wave's slabs: s0 + tw, s0 + tw + TW, ... < s1
-    const int mine = compute && s0 + tw < s1 ? (s1 - s0 - tw + TW - 1) / TW : 0;
-
-    float *qs = S.attn;                                  // [G][D]
-    float *wm = qs + G * D;                              // [kWaves][HG] wave maxima (log2 units)
-    float *wl = wm + kWaves * HG;                        // [kWaves][HG] wave sums
-    float *wacc = wl + kWaves * HG;                      // [kWaves][HG][D] wave outputs
-    uint16_t *kn = reinterpret_cast<uint16_t *>(wacc + kWaves * HG * D);  // [D] new key
-    uint16_t *vn = kn + D;                                                // [D] new value
-    const size_t row0 = kv_row(P, l, b, g);
-    const uint16_t *Kb = P.kc + row0 * D + ds;
-    const uint16_t *Vb = P.vc + row0 * D + ds;
-    // scores in log2 units: softmax weights are 2^(s log2(e) - max)
-    const float scale = 1.4426950408889634f / sqrtf((float)D);
-
-    // the ring: item i of this wave (slab s0 + wid + i kWaves) sits in slot
-    // i % R; a slot past the wave's slabs, past the context or holding the
-    // new position loads the dummy line (zeros)
-    u32x4 kr[R], vr[R];
-    auto pos_of_item = [&](int i) { return (s0 + tw + i * TW) * PP + pi; };
-    auto addr = [&](const uint16_t *base, int i) -> const void * {
-        const int pos = pos_of_item(i);
-        return (i < mine && pos < n && pos != pnew) ? (const void *)(base + (size_t)pos * D)
-                                                    : (const void *)P.dummy;
-    };
-    if (compute) {
-#pragma unroll
-        for (int s = 0; s < R; ++s) kr[s] = ld_stream_16B(addr(Kb, s));
-#pragma unroll
-        for (int s = 0; s < R; ++s) vr[s] = ld_stream_16B(addr(Vb, s));
-    }
-    if (is_ctl_lane0()) trace_stamp(P, ti, 1);
-    {
-        // the queries of head g's query heads and the new key and value, as
-        // tagged words (every thread takes a few), into LDS
-        const size_t qo = (size_t)b * P.nq * D + (size_t)g * G * D;
-        const unsigned long long *kvl = P.kv_ll + ((size_t)b * P.nkv + g) * D;
-        ll_gather<(G * D + D + kThreads - 1) / kThreads>(
-            P, G * D + D, ll_tag(P, l), kl_tid(), kThreads,
-            [&](int i) { return i < G * D ? P.q_ll + qo + i : kvl + (i - G * D); },
-            [&](int i, unsigned v) {
-                if (i < G * D) {
-                    qs[i] = __uint_as_float(v);
-                } else if (i < G * D + D / 2) {   // key dims j and j + D/2
-                    const int j = i - G * D;
-                    kn[j] = (uint16_t)v;
-                    kn[j + D / 2] = (uint16_t)(v >> 16);
-                } else {                           // value dims 2j and 2j + 1
-                    reinterpret_cast<unsigned *>(vn)[i - G * D - D / 2] = v;
-                }
-            });
-    }
-    __syncthreads();
-    if (is_ctl_lane0()) trace_stamp(P, ti, 2);
-
-    float acc[HG][8], m[HG], lsum[HG];
-#pragma unroll
-    for (int h = 0; h < HG; ++h) {
-        m[h] = -INFINITY;
-        lsum[h] = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
-    }
-    if (compute) {
-        float q[HG][8];
-#pragma unroll
-        for (int h = 0; h < HG; ++h) {
-            const float4 q0 = *reinterpret_cast<const float4 *>(qs + (h0 + h) * D + ds);
-            const float4 q1 = *reinterpret_cast<const float4 *>(qs + (h0 + h) * D + ds + 4);
-            q[h][0] = q0.x; q[h][1] = q0.y; q[h][2] = q0.z; q[h][3] = q0.w;
-            q[h][4] = q1.x; q[h][5] = q1.y; q[h][6] = q1.z; q[h][7] = q1.w;
-        }
-        // R slabs at a time: their scores, one rescale per head, their values
-        for (int i0 = 0; i0 < mine; i0 += R) {
-            float sc[R][HG];
-#pragma unroll
-            for (int s = 0; s < R; ++s) {
-                const int pos = pos_of_item(i0 + s);
-                const bool valid = i0 + s < mine && pos < n;
-                const u32x4 kv =
-                    pos == pnew ? *reinterpret_cast<const u32x4 *>(kn + ds) : kr[s];
-                kr[s] = ld_stream_16B(addr(Kb, i0 + s + R));
-                const float kf[8] = {bf_lo(kv.x), bf_hi(kv.x), bf_lo(kv.y), bf_hi(kv.y),
-                                     bf_lo(kv.z), bf_hi(kv.z), bf_lo(kv.w), bf_hi(kv.w)};
-#pragma unroll
-                for (int h = 0; h < HG; ++h) {
-                    float d = 0.f;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) d = fmaf(q[h][e], kf[e], d);
-                    d = sum_lanes<LP>(d) * scale;
-                    sc[s][h] = valid ? d : -INFINITY;
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < HG; ++h) {
-                float mx = m[h];
-#pragma unroll
-                for (int s = 0; s < R; ++s) mx = fmaxf(mx, sc[s][h]);
-                const float al = m[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[h] - mx);
-                float sum = 0.f;
-#pragma unroll
-                for (int s = 0; s < R; ++s) {
-                    sc[s][h] = sc[s][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[s][h] - mx);
-                    sum += sc[s][h];
-                }
-                lsum[h] = fmaf(lsum[h], al, sum);
-                m[h] = mx;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[h][e] *= al;
-            }
-#pragma unroll
-            for (int s = 0; s < R; ++s) {
-                const int pos = pos_of_item(i0 + s);
-                const u32x4 vv = pos == pnew ? *reinterpret_cast<const u32x4 *>(vn + ds) : vr[s];
-                vr[s] = ld_stream_16B(addr(Vb, i0 + s + R));
-                const float vf[8] = {bf_lo(vv.x), bf_hi(vv.x), bf_lo(vv.y), bf_hi(vv.y),
-                                     bf_lo(vv.z), bf_hi(vv.z), bf_lo(vv.w), bf_hi(vv.w)};
-#pragma unroll
-                for (int h = 0; h < HG; ++h)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[h][e] = fmaf(sc[s][h], vf[e], acc[h][e]);
-            }
-        }
-        // merge the PP lane groups of the wave (lanes ds apart by LP, 2 LP, ...)
-#pragma unroll
-        for (int off = LP; off < 64; off <<= 1) {
-#pragma unroll
-            for (int h = 0; h < HG; ++h) {
-                const float m2 = __shfl_xor(m[h], off), l2 = __shfl_xor(lsum[h], off);
-                const float mn = fmaxf(m[h], m2);
-                const float a1 = m[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[h] - mn);
-                const float a2 = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m2 - mn);
-                lsum[h] = lsum[h] * a1 + l2 * a2;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float o2 = __shfl_xor(acc[h][e], off);
-                    acc[h][e] = acc[h][e] * a1 + o2 * a2;
-                }
-                m[h] = mn;
-            }
-        }
-        if (pi == 0) {
-#pragma unroll
-            for (int h = 0; h < HG; ++h) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) wacc[(wid * HG + h) * D + ds + e] = acc[h][e];
-                if (ds == 0) {
-                    wm[wid * HG + h] = m[h];
-                    wl[wid * HG + h] = lsum[h];
-                }
-            }
-        }
-    }
-    __syncthreads();
-    // the waves in order: (max, sum, unnormalised output) of the chunk, the
-    // max published in natural-log units, as tagged words, per query head h
-    // at [b][g][h][c] (D + 2 words: outputs, max, sum; one query head's
-    // chunks contiguous for the O projection, which polls them)
-    unsigned long long *ll_out = P.po_ll + (((size_t)b * P.nkv + g) * G * P.C + c) * (D + 2);
-    const size_t hstride = (size_t)P.C * (D + 2);
-    const unsigned tag = ll_tag(P, l);
-    for (int t = kl_tid(); t < G * D + G; t += kThreads) {
-        const int h = t < G * D ? t / D : t - G * D, dd = t % D;
-        const int w0 = (h / HG) * TW, hl = h % HG;   // the head's team, its slot
-        float M = -INFINITY;
-        for (int w = w0; w < w0 + TW; ++w) M = fmaxf(M, wm[w * HG + hl]);
-        float O = 0.f, L = 0.f;
-        for (int w = w0; w < w0 + TW; ++w) {
-            const float mw = wm[w * HG + hl];
-            const float a = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
-            L = fmaf(wl[w * HG + hl], a, L);
-            if (t < G * D) O = fmaf(wacc[(w * HG + hl) * D + dd], a, O);
-        }
-        if (t < G * D) {
-            st_ll_f(ll_out + h * hstride + dd, O, tag);
-        } else {
-            st_ll_f(ll_out + h * hstride + D, M * 0.6931471805599453f, tag);
-            st_ll_f(ll_out + h * hstride + D + 1, L, tag);
-        }
-    }
-    if (is_ctl_lane0()) trace_stamp(P, ti, 3);
-    __syncthreads();   // (the attention area is the next item's)
-}
-
-// ---------------------------------------------------------------- attention by units (matrix-core path)
+// ---------------------------------------------------------------- attention
 //
 // Split-K flash decoding over the whole batch at once.  The cached positions
 // of a sequence are cut into units (attn_unit<D>() positions: 4 KiB of keys
@@ -2299,8 +1862,10 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
 // of one sequence); its start is found once per launch (seg_init).  A share
 // that starts inside a sequence hands its part of that sequence over as
 // tagged words; the share with the sequence's first units, which is its last
-// segment, merges them.  No barrier separates a share's segments: the waves go
-// on to the next one while the control wave merges and stages.  Equal
+// segment, merges them (matrix-core path; on the per-sequence path every
+// segment is handed over and the O projection merges, merge_parts).  No
+// barrier separates a share's segments: the waves go on to the next one while
+// the control wave merges and stages.  Equal
 // shares matter where contexts differ or the batch does not divide the
 // workgroups: with one item per (sequence, chunk) the phase lasted as long as
 // the longest item (8B shape, batch 32, contexts 2048 to 4096: ends spread
@@ -2311,8 +1876,9 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
 // Both products run on the matrix cores, in layouts that need no exchange
 // between lanes:
 //   scores  v_mfma_f32_16x16x32_bf16, A = 16 key rows (16 bytes of a row per
-//           lane), B = the queries (scaled, log2 units) as two bf16 terms;
-//           column n is head n & 7 (zero past G).  Tile row 4 k + v is the
+//           lane), B = the queries (scaled, log2 units) as two bf16 terms
+//           (three on the per-sequence path: their 24 bits); column n is
+//           head n & 7 (zero past G).  Tile row 4 k + v is the
 //           position that the value product below wants from lane (k, n) in
 //           its register v.
 //   values  v_mfma_f32_16x16x4_f32 (fp32 probabilities, bf16 values exact in
@@ -2333,18 +1899,15 @@ __device__ __forceinline__ void attn_item_stream(KArg ka, int l, int b, int g, i
 template <int D> __device__ __forceinline__ constexpr int attn_unit() { return 2048 / D; }
 __device__ __forceinline__ int attn_units_of(int pnew, int up) { return pnew / up + 1; }
 
-// A workgroup's share, in LDS: first sequence, its first unit, units of the
-// share, units of the whole batch, workgroups that have shares.
-__device__ __forceinline__ int *seg_table(const StepParams &P) {
-    return route_table(P) + 4 * kMfmaBatch;
-}
+// A workgroup's share, in LDS (seg_table): first sequence, its first unit,
+// units of the share, units of the whole batch, workgroups that have shares.
 // (one wave, once per launch, before the launch's first barrier)
 __device__ __forceinline__ void seg_init(const StepParams &P, int lane) {
     const int up = 2048 / P.d;
     int T = 0;
     for (int b0 = 0; b0 < P.B; b0 += 64) {
         int u = b0 + lane < P.B ? attn_units_of(eff_pos(P, b0 + lane), up) : 0;
-        for (int off = 1; off < 64; off <<= 1) u += __shfl_xor(u, off);
+        for (int off = 1; off < 64; off <<= 1) u += from_lane(u, lane ^ off);
         T += u;
     }
     const int np = min(P.Sg, T), part = blockIdx.x % P.Sg;
@@ -2363,7 +1926,7 @@ __device__ __forceinline__ void seg_init(const StepParams &P, int lane) {
         const int own = b0 + lane < P.B ? attn_units_of(eff_pos(P, b0 + lane), up) : 0;
         int s = own;   // inclusive sum
         for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(s, off);
+            const int o = from_lane(s, max(lane - off, 0));
             s += lane >= off ? o : 0;
         }
         const int s0 = before + s - own;
@@ -2371,10 +1934,10 @@ __device__ __forceinline__ void seg_init(const StepParams &P, int lane) {
             t[0] = b0 + lane;
             t[1] = a - s0;
         }
-        before += __shfl(s, 63);
+        before += __builtin_amdgcn_readlane(s, 63);
     }
 }
-template <int D, int G>
+template <int D, int G, bool LL>
 __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int ti) {
     const StepParams P = load_params(ka);
     const Lds S = lds_layout(kl_smem, P);
@@ -2387,8 +1950,9 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
     // two sets, alternating by segment: while a segment's units run, the
     // control wave merges the waves of the one before and stages the queries
     // of the one after
-    float *const qs0 = S.attn;                      // [2][G][D] queries
-    float *const wm0 = qs0 + 2 * G * D;             // [2][kWaves][G] wave maxima (log2 units)
+    constexpr int NT = LL ? 3 : 2, QS = D + 8;      // query terms; bf16 per row (banks)
+    uint16_t *const qs0 = reinterpret_cast<uint16_t *>(S.attn);   // [2][NT][G][QS] scaled queries
+    float *const wm0 = S.attn + 2 * NT * G * QS / 2;   // [2][kWaves][G] wave maxima (log2 units)
     float *const wl0 = wm0 + 2 * kWaves * G;        // [2][kWaves][G] wave sums
     float *const wa0 = wl0 + 2 * kWaves * G;        // [2][kWaves][G][HS] wave outputs
     uint16_t *const kn0 = reinterpret_cast<uint16_t *>(wa0 + 2 * kWaves * WS);   // [2][D] new key
@@ -2402,7 +1966,7 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
     int b = __builtin_amdgcn_readfirstlane(tab[0]), u0 = __builtin_amdgcn_readfirstlane(tab[1]);
     int left = __builtin_amdgcn_readfirstlane(tab[2]);
     if (left <= 0) return;
-    int pnew = __builtin_amdgcn_readfirstlane(eff_pos(P, b));
+    int pnew = __builtin_amdgcn_readfirstlane(pos_of<LL>(P, b));
     const unsigned tag = ll_tag(P, l);
 
     // the merged (max, sum, unnormalised output) of the waves of set z, for
@@ -2433,9 +1997,11 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
     // a share that starts inside a sequence hands its part of it to the
     // workgroup that has the sequence's first units, as tagged words [head]
     // [D outputs, max, sum]
-    unsigned long long *const parts = P.po_ll + (size_t)g * P.Sg * G * (D + 2);
-    auto hand_over = [&](int t, float M, float L, float O) {
-        unsigned long long *w = parts + ((size_t)part * G + t / D) * (D + 2);
+    // (slot: the workgroup's part; per-sequence path: part + sequence, since
+    // every segment is handed over)
+    unsigned long long *const parts = P.po_ll + (size_t)g * (LL ? P.Sg + P.B : P.Sg) * G * (D + 2);
+    auto hand_over = [&](int sb, int t, float M, float L, float O) {
+        unsigned long long *w = parts + ((size_t)(LL ? part + sb : part) * G + t / D) * (D + 2);
         st_ll_f(w + t % D, O, tag);
         if (t % D == 0) {
             st_ll_f(w + D, M, tag);
@@ -2451,7 +2017,10 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
         // position of score register s (0 .. 3): D = 128: slab s, position k;
         // D = 64: slab s, position 2 k (columns 0-7) or 2 k + 1 (columns 8-15)
         const int sp = D == 128 ? k4 : 2 * k4 + (n >> 3);
-        u32x4 kr[2][4], vr[2][4];
+        // units whose values are in flight (per-sequence path: one, where two
+        // spilled, and the reloads of spilled registers waited for the rings)
+        constexpr int VD = LL ? 1 : 2;
+        u32x4 kr[2][4], vr[VD][4];
         const uint16_t *kb = nullptr, *vb = nullptr;
         // the current segment: its sequence's units, its end and the end of
         // its units with cached positions; the wave's units, its first one's
@@ -2481,7 +2050,7 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
             const int p0 = base + place(i) * kWaves * UP + vp;
 #pragma unroll
             for (int x = 0; x < 4; ++x)
-                vr[j][x] = ld_stream_16B(vb + (size_t)min(p0 + x * PP, last) * D);
+                vr[j % VD][x] = ld_stream_16B(vb + (size_t)min(p0 + x * PP, last) * D);
         };
         // units of the segments so far (the waves take the share's units in
         // turn, across its segments)
@@ -2501,39 +2070,35 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
             issue_k(0, 0);
             issue_v(0, 0);
             issue_k(1, 1);
-            issue_v(1, 1);
+            if (VD > 1) issue_v(1, 1);
         };
         enter();
         lds_barrier();
-        // queries in log2 units: softmax weights are 2^(s log2(e) - max)
-        const float scale = 1.4426950408889634f / sqrtf((float)D);
-        constexpr int NQB = 4;   // D = 128: 4 column blocks (both terms in one); D = 64: 2 terms x 2
+        // D = 128: 4 column blocks with two terms in one, the third apart;
+        // D = 64: 2 column blocks per term
+        constexpr int NQB = D == 128 ? (LL ? 8 : 4) : (LL ? 6 : 4);
         for (int seg = 0;; ++seg) {
             const int z = seg & 1;
             left -= u1 - u0;
-            const int pnext = left > 0 ? __builtin_amdgcn_readfirstlane(eff_pos(P, b + 1)) : 0;
+            const int pnext = left > 0 ? __builtin_amdgcn_readfirstlane(pos_of<LL>(P, b + 1)) : 0;
             if (seg >= 2)   // (the first two were staged before the barrier)
                 while (flag(2) <= seg) __builtin_amdgcn_s_sleep(1);
             asm volatile("" ::: "memory");
-            const int lq = kl_tid() & 63, kcq = 8 * (lq >> 4);
-            const float *qs = qs0 + z * G * D;
-            bf16x8 qb[NQB];
+
+            // (operand x: the terms past the second stay in LDS and are read for
+            // each unit, which keeps their registers free)
+            const uint16_t *qs = qs0 + z * NT * G * QS;
+            auto query = [&](int x, int lq) {
+                const int h = lq & 7, ks = D == 128 ? x & 3 : x & 1;
+                const int term = D == 128 ? 2 * (x >> 2) + ((lq >> 3) & 1) : x >> 1;
+                const bool live = h < G && term < NT;
+                const u32x4 w = *reinterpret_cast<const u32x4 *>(
+                    qs + ((live ? term : 0) * G + (live ? h : 0)) * QS + 32 * ks + 8 * (lq >> 4));
+                return __builtin_bit_cast(bf16x8, live ? w : u32x4{0u, 0u, 0u, 0u});
+            };
+            bf16x8 qb[4];
 #pragma unroll
-            for (int x = 0; x < NQB; ++x) {
-                const int h = lq & 7, ks = D == 128 ? x : x & 1;
-                const bool lo = D == 128 ? (lq & 8) != 0 : x >= 2;
-                unsigned w[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int d0 = 32 * ks + kcq + 2 * j;
-                    const float x0 = h < G ? qs[h * D + d0] * scale : 0.f;
-                    const float x1 = h < G ? qs[h * D + d0 + 1] * scale : 0.f;
-                    unsigned hw, lw;
-                    split_bf16x2(x0, x1, hw, lw);
-                    w[j] = lo ? lw : hw;
-                }
-                qb[x] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
-            }
+            for (int x = 0; x < 4; ++x) qb[x] = query(x, kl_tid() & 63);
             f32x4 acc[8];
             float m = -INFINITY, lsum = 0.f;
 #pragma unroll
@@ -2545,20 +2110,22 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
                 if constexpr (D == 128) {
                     f32x4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int ks = 0; ks < 4; ++ks)
-                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kq[ks]),
-                                                                   qb[ks], t, 0, 0, 0);
+                    for (int x = 0; x < NQB; ++x)
+                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, kq[x & 3]), x < 4 ? qb[x & 3] : query(x, lane), t,
+                            0, 0, 0);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) s[v] = t[v] + dpp<0x128>(t[v]);   // both terms
+                    for (int v = 0; v < 4; ++v) s[v] = t[v] + dpp<0x128>(t[v]);   // the terms
                 } else {
                     f32x4 t[2];
 #pragma unroll
                     for (int y = 0; y < 2; ++y) {
                         t[y] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int x = 0; x < 4; ++x)
+                        for (int x = 0; x < NQB; ++x)
                             t[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf16x8, kq[2 * y + (x & 1)]), qb[x], t[y], 0, 0, 0);
+                                __builtin_bit_cast(bf16x8, kq[2 * y + (x & 1)]),
+                                x < 4 ? qb[x & 3] : query(x, lane), t[y], 0, 0, 0);
                     }
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
@@ -2575,8 +2142,7 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
                 float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
                 if (__any(mx > m + 8.f)) {
                     if constexpr (D == 64) mx = fmaxf(mx, dpp<0x128>(mx));
-                    mx = fmaxf(mx, __shfl_xor(mx, 16));
-                    mx = fmaxf(mx, __shfl_xor(mx, 32));
+                    mx = max_16_32(mx);
                     const float mn = fmaxf(m, mx);
                     const float al = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
                     m = mn;
@@ -2605,11 +2171,11 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
                 for (int j = 0; j < 2; ++j) {
                     const int p0 = base + place(i + j) * kWaves * UP;
                     if (i + j < mine) {
-                        unit(kr[j], vr[j], p0, pnew, [&]() { issue_k(j, i + j + 2); },
-                             [&]() { issue_v(j, i + j + 2); });
+                        unit(kr[j], vr[j % VD], p0, pnew, [&]() { issue_k(j, i + j + 2); },
+                             [&]() { issue_v(j, i + j + VD); });
                     } else {
                         issue_k(j, i + j + 2);
-                        issue_v(j, i + j + 2);
+                        issue_v(j, i + j + VD);
                     }
                 }
             }
@@ -2632,14 +2198,13 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
             pnew = pnext;
             if (left > 0) enter();
             // this wave's (max, sum, output) into set z
-            lsum += __shfl_xor(lsum, 16);
-            lsum += __shfl_xor(lsum, 32);
+            lsum = sum_16_32(lsum);
             if constexpr (D == 64) {
                 lsum += dpp<0x128>(lsum);
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[e][r] += __shfl_down(acc[e][r], 40);
+                    for (int r = 0; r < 4; ++r) acc[e][r] += from_lane(acc[e][r], ((kl_tid() & 63) + 40) & 63);
             }
             const int le = kl_tid() & 63, ke = le >> 4, ne = le & 15;
             if (ne < G && ke < D / 32) {
@@ -2665,7 +2230,39 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
     } else {
         // the control wave: the queries and the new key and value of sequence
         // sb, position spos, into set z
+        // queries in log2 units: softmax weights are 2^(s log2(e) - max)
+        const float scale = 1.4426950408889634f / sqrtf((float)D);
+        auto put_q = [&](int z, int i, float q) {   // its bf16 terms
+            uint16_t *d = qs0 + (z * NT * G + i / D) * QS + i % D;
+            float x = q * scale;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const uint16_t h = f2bf(x);
+                d[t * G * QS] = h;
+                x -= bf2f(h);
+            }
+        };
         auto stage_q = [&](int sb, int spos, int z) {
+            if constexpr (LL) {   // (tagged words)
+                const size_t qo = (size_t)sb * P.nq * D + (size_t)g * G * D;
+                const unsigned long long *kvl = P.kv_ll + ((size_t)sb * P.nkv + g) * D;
+                uint16_t *kn = kn0 + z * D, *vn = vn0 + z * D;
+                ll_gather<(G * D + D + 63) / 64>(
+                    P, G * D + D, tag, lane, 64,
+                    [&](int i) { return i < G * D ? P.q_ll + qo + i : kvl + (i - G * D); },
+                    [&](int i, unsigned v) {
+                        if (i < G * D) {
+                            put_q(z, i, __uint_as_float(v));
+                        } else if (i < G * D + D / 2) {   // key dims j and j + D/2
+                            const int j = i - G * D;
+                            kn[j] = (uint16_t)v;
+                            kn[j + D / 2] = (uint16_t)(v >> 16);
+                        } else {                           // value dims 2j and 2j + 1
+                            reinterpret_cast<unsigned *>(vn)[i - G * D - D / 2] = v;
+                        }
+                    });
+                return;
+            }
             constexpr int N2 = G * D / 2, NQ = (N2 + 63) / 64;   // pairs; per lane
             const float *src = P.q + (size_t)sb * P.nq * D + (size_t)g * G * D;
             const size_t o = (kv_row(P, l, sb, g) + spos) * D + (lane % (D / 4)) * 4;
@@ -2673,15 +2270,18 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
 #pragma unroll
             for (int k = 0; k < NQ; ++k) qv[k] = ld_dev_u64(src + 2 * min(lane + 64 * k, N2 - 1));
             const unsigned long long kv = ld_dev_u64((lane < 32 ? P.kc : P.vc) + o);
-            unsigned long long *dst = reinterpret_cast<unsigned long long *>(qs0 + z * G * D);
 #pragma unroll
-            for (int k = 0; k < NQ; ++k)
-                if (N2 % 64 == 0 || lane + 64 * k < N2) dst[lane + 64 * k] = qv[k];
+            for (int k = 0; k < NQ; ++k) {
+                if (N2 % 64 == 0 || lane + 64 * k < N2) {
+                    put_q(z, 2 * (lane + 64 * k), __uint_as_float((unsigned)qv[k]));
+                    put_q(z, 2 * (lane + 64 * k) + 1, __uint_as_float((unsigned)(qv[k] >> 32)));
+                }
+            }
             if (lane % 32 < D / 4)
                 reinterpret_cast<unsigned long long *>((lane < 32 ? kn0 : vn0) + z * D)[lane % 32] = kv;
         };
         // (pn[i % 3]: the position of the share's segment i's sequence, b + i)
-        auto pos_at = [&](int i) { return __builtin_amdgcn_readfirstlane(eff_pos(P, b + i)); };
+        auto pos_at = [&](int i) { return __builtin_amdgcn_readfirstlane(pos_of<LL>(P, b + i)); };
         auto units_at = [&](int p) { return attn_units_of(p, UP); };
         int rest = left - min(left, units_at(pnew) - u0);   // units after this segment
         int pn1 = rest > 0 ? pos_at(1) : 0;
@@ -2689,10 +2289,12 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
             trace_stamp(P, ti, 1);
             flags[0] = flags[1] = 0;
             flags[2] = 2;
-            spin_until(P, [&]() {
-                return (int)(__hip_atomic_load(P.cnt + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
-                             (unsigned)(l + 1) * (unsigned)P.Sg) >= 0;
-            });
+            if (!LL)
+                spin_until(P, [&]() {
+                    return (int)(__hip_atomic_load(P.cnt + g, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT) -
+                                 (unsigned)(l + 1) * (unsigned)P.Sg) >= 0;
+                });
         }
         __builtin_amdgcn_wave_barrier();
         stage_q(b, pnew, 0);
@@ -2709,8 +2311,8 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
             for (int t = kl_tid() & 63; t < G * D; t += 64) {
                 float M, L, O;
                 merge_waves(z, t, M, L, O);
-                if (u0 == 0) finish(b, t, L, O);
-                else hand_over(t, M, L, O);
+                if (!LL && u0 == 0) finish(b, t, L, O);
+                else hand_over(b, t, M, L, O);
             }
             if (rest1 > 0) {
                 stage_q(b + 2, pn2, z);
@@ -2739,7 +2341,7 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
         split_range(T, np, part, seq0, e0);
         seq0 -= nu;   // the sequence's first unit, counted over the batch
         for (;;) {
-            U = attn_units_of(__builtin_amdgcn_readfirstlane(eff_pos(P, nb)), UP);
+            U = attn_units_of(__builtin_amdgcn_readfirstlane(pos_of<LL>(P, nb)), UP);
             if (nl <= U - nu) break;
             nl -= U - nu;
             seq0 += U;
@@ -2754,8 +2356,8 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
         for (int t = kl_tid(); t < G * D; t += kThreads) {
             float M, L, O;
             merge_waves(z, t, M, L, O);
-            if (nu > 0) {
-                hand_over(t, M, L, O);
+            if (LL || nu > 0) {
+                hand_over(nb, t, M, L, O);
                 continue;
             }
             for (int q0 = 0; q0 < more; q0 += NB) {
@@ -2796,44 +2398,100 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
     lds_barrier();   // (the attention area is the next phase's)
 }
 
-// Attention of KV head g.  Per-sequence path: the workgroups of head g take
-// its items (sequence b, chunk c) round-robin and hand the chunk results to
-// the O projection as tagged words; batched path: by units (attn_units), the
-// merged outputs published before a grid barrier.
+// Per-sequence path, control wave: the merged attention outputs this
+// workgroup hands on, o = sum_c w_c A_c / sum_c w_c L_c with w_c = 2^(M_c - M),
+// M the largest of the parts' maxima (A_c, M_c, L_c the parts' unnormalised
+// outputs, maxima in log2 units and sums).  Items of 16 outputs of one query
+// head and sequence are spread over the grid (8B shape, batch 1: one per
+// workgroup), so that every part is read once, where a merge by every
+// workgroup that needs a head's outputs read all of its parts in each of
+// them.  Lane 16 c + j takes output j of parts c, c + 4, ..., lane c the
+// maximum and sum of part c.
+template <int D, int G>
+__device__ __forceinline__ void merge_parts(const StepParams &P, int l) {
+    constexpr int MD = 16, WD = D + 2, NB = 8;   // outputs per item; loads per lane and round
+    const int lane = kl_tid() & 63, j = lane & 15, cl = lane >> 4;
+    const unsigned tag = ll_tag(P, l);
+    const int T = __builtin_amdgcn_readfirstlane(seg_table(P)[3]);
+    const int np = __builtin_amdgcn_readfirstlane(seg_table(P)[4]);
+    const int items = P.nq * (D / MD);
+    int seq0 = 0;
+    for (int b = 0; b < P.B; ++b) {
+        const int U = attn_units_of(__builtin_amdgcn_readfirstlane(pos_of<true>(P, b)), 2048 / D);
+        const int f = (int)(((long long)(seq0 + 1) * np - 1) / T);
+        const int nc = (int)(((long long)(seq0 + U) * np - 1) / T) - f + 1;
+        seq0 += U;
+        for (int it = blockIdx.x; it < items; it += P.nwg) {
+            const int h = it / (D / MD), d0 = it % (D / MD) * MD, g = h / G;
+            const unsigned long long *src =
+                P.po_ll + (((size_t)g * (P.Sg + P.B) + f + b) * G + h % G) * WD;
+            float M = -INFINITY, L = 0.f, O = 0.f;
+            for (int c0 = 0; c0 < nc; c0 += 4 * NB) {
+                const int n = min(4 * NB, nc - c0);
+                unsigned long long v[NB], vm, vl;
+                for (int spins = 1;; ++spins) {
+                    bool ok = true;
+                    const unsigned long long *q = src + (size_t)(c0 + min(lane, n - 1)) * G * WD + D;
+                    vm = ld_dev_u64(q);
+                    vl = ld_dev_u64(q + 1);
+#pragma unroll
+                    for (int k = 0; k < NB; ++k)
+                        v[k] = ld_dev_u64(src + (size_t)(c0 + min(cl + 4 * k, n - 1)) * G * WD + d0 + j);
+#pragma unroll
+                    for (int k = 0; k < NB; ++k) ok = ok && ll_current(v[k], tag);
+                    ok = ok && ll_current(vm, tag) && ll_current(vl, tag);
+                    if (__all(ok) || give_up(P, spins)) break;
+                }
+                const float mc = lane < n ? __uint_as_float(ll_value(vm)) : -INFINITY;
+                const float mn = fmaxf(M, wave_max(mc));
+                const float al = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn);
+                const float w = mc == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mc - mn);
+                L = L * al + wave_sum(w * (lane < n ? __uint_as_float(ll_value(vl)) : 0.f));
+                float o = 0.f;
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    const float wk = from_lane(w, cl + 4 * k);   // (zero past n)
+                    o = fmaf(cl + 4 * k < n ? __uint_as_float(ll_value(v[k])) : 0.f, wk, o);
+                }
+                o = sum_16_32(o);
+                O = O * al + o;
+                M = mn;
+            }
+            if (lane < MD) st_ll_f(P.o_ll + (size_t)b * P.nq * D + h * D + d0 + j, O / L, tag);
+        }
+    }
+}
+
+// Attention of KV head g, by units (attn_units).  Per-sequence path: the
+// segments' results leave as tagged words; batched path: the merged outputs
+// are published before a grid barrier.
 template <int D, int G, bool BAT>
 __device__ __forceinline__ void phase_attn(KArg ka, int l, int garrive, int ti) {
     const StepParams P = load_params(ka);
     const int g = blockIdx.x / P.Sg, part = blockIdx.x % P.Sg;
     if (g < P.nkv) {
-        if constexpr (BAT) {
-            attn_units<D, G>(ka, l, g, part, ti);
-        } else {
-            const int items = P.B * P.C;
-            for (int it = part; it < items; it += P.Sg)
-                if constexpr (G <= 4) attn_item_ll<D, G>(ka, l, it / P.C, g, it % P.C, ti);
-                else attn_item_stream<D, G>(ka, l, it / P.C, g, it % P.C, ti);
-        }
+        attn_units<D, G, !BAT>(ka, l, g, part, ti);
     }
     if (garrive >= 0) bar_arrive(P, garrive, ti);
     else if (is_ctl_lane0()) trace_stamp(P, ti, 0);
 }
 
-// O projection of KV head g: x += Wo[:, columns of head g] o_g, for the rows
-// this workgroup owns among head g's workgroups, added into the fixed-point
-// residual.  GEMV path: the staged input is head g's merged attention output,
-// published by the attention phase.
+// O projection: x += Wo o.  Per-sequence path: each workgroup for the rows it
+// owns, over all of K (the packed matrices of all query heads): the weight
+// ring starts at once (8B shape: it holds the whole share, 128 KiB), the
+// control wave merges its items of the attention meanwhile, and every thread
+// then gathers the merged outputs; the sums are complete, so the epilogue adds
+// them to the owned residual and publishes it.  (By query head, with the
+// merge of a head's parts in each of its workgroups and the partial products
+// added by atomics before a grid barrier, the phase and the hand-off to the
+// gate/up product took 16.4 us at the 8B shape, batch 1; now 14.3.)
 template <int D, int G, bool BAT>
 __device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int garrive, int ti) {
     const StepParams P = load_params(ka);
     const Lds S = lds_layout(kl_smem, P);
-    const int KTO = G * D / kTileK;
     const uint8_t *Wo = P.arena + (size_t)l * P.layer_stride + P.off_o;
-    auto epi = [&](int b, int r, float y0, float y1) {
-        long long *x = P.xf + (size_t)b * P.Hp;
-        add_fix(x + r, y0);
-        add_fix(x + r + 1, y1);
-    };
     if constexpr (BAT) {
+        const int KTO = G * D / kTileK;
         // 2-D partition: KSo K slices (the columns of nkv / KSo KV heads
         // each) x row groups; a workgroup writes its slice's partial sums,
         // which the next RMSNorm step folds into the residual.  Every wave
@@ -2860,55 +2518,42 @@ __device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int garri
             },
             D / kTileK, (size_t)P.o_rg * (D / kTileK));
     } else {
-        // per query head: the Sg workgroups of KV head g split into G
-        // groups, group hq applying the O-projection columns of query head
-        // g G + hq to its merged attention output, each workgroup for a
-        // range of rows
-        const int g = blockIdx.x / P.Sg, part = blockIdx.x % P.Sg;
-        if (g < P.nkv) {
-            int hq = 0;
-            while (hq + 1 < G && part >= (P.Sg * (hq + 1)) / G) ++hq;
-            const int p0 = (P.Sg * hq) / G, np = (P.Sg * (hq + 1)) / G - p0;
-            int a0, a1;
-            split_range(P.o_rg, np, part - p0, a0, a1);
-            constexpr int KTq = D / kTileK;
-            // With up to 4 query heads per KV head the waves split: waves
-            // kOEarly .. kWaves - 1 issue their loads before the merge and take
-            // no part in its gather, so half the matrix streams while the merge
-            // waits for the attention's chunks; waves 0 .. kOEarly - 1 gather
-            // the chunks and issue their loads after the merge.  (Every wave
-            // issuing its loads first makes the merge's gather queue behind
-            // them; the control wave in the gather slows it.)  The early waves
-            // go early only when one ring holds their whole share (at 8 query
-            // heads per KV head the share is several rings, and the split was
-            // measured slower).
-            constexpr bool SPLIT = G <= 4;
-            constexpr int NTM = SPLIT ? kOEarly * 64 : kThreads;
-            const int mine = ((a1 - a0) + kWaves - 1) / kWaves * KTq;   // tiles per wave, at most
-            const int EW = SPLIT && mine <= kGemvDepth ? kOEarly : kWaves + 1;
-            auto stage = [&](int b) {
-                if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 1);
-                // (with P.multi sequence b's output goes to S.a + b D; all
-                // sequences in one gather when their chunks fit)
-                if (!P.multi)
-                    merge_ll<D, G, NTM>(P, l, b, g, hq, S.a, S.a + D);
-                else if (P.B * P.C > kMergeChunks)
-                    merge_ll<D, G, NTM>(P, l, b, g, hq, S.a + b * D, S.a + kMultiSeq * D);
-                else if (b == 0)
-                    merge_ll_multi<D, G, NTM>(P, l, P.B, g, hq, S);
-                if (b == 0 && is_ctl_lane0()) {
-                    trace_stamp(P, ti, 2);
-                    trace_stamp(P, ti, 3);
-                }
-            };
-            const uint8_t *W = Wo + (size_t)(g * G + hq) * P.o_rg * KTq * kTileBytes;
-            if (P.multi)
-                gemv_phase<false, SPLIT, true>(W, KTq, a0, a1 - a0, 1, P.B, S.a, S.red, P.dummy,
-                                               [&]() {}, stage, epi, EW, D);
-            else
-                gemv_phase<false, SPLIT>(W, KTq, a0, a1 - a0, 1, P.B, S.a, S.red, P.dummy,
-                                         [&]() {}, stage, epi, EW);
-        }
+        const OwnRows R = own_rows(P);
+        constexpr int KTq = D / kTileK;
+        const int K = P.nq * D, KT = P.nq * KTq;
+        const unsigned tag = ll_tag(P, l);
+        auto wait = [&]() {
+            if ((kl_tid() >> 6) == kCtlWave) {
+                if (is_ctl_lane0()) trace_stamp(P, ti, 1);
+                merge_parts<D, G>(P, l);
+                if (is_ctl_lane0()) trace_stamp(P, ti, 2);
+            }
+            lds_barrier();   // (as in owners_wait)
+        };
+        auto stage = [&](int b) {
+            // (the control wave leaves the gather to the others, whose rings
+            // are done by then; with P.multi all sequences' outputs, b K
+            // floats apart)
+            if (!P.multi || b == 0)
+                ll_gather<8>(
+                    P, (P.multi ? P.B : 1) * K, tag, kl_tid(), kThreads,
+                    [&](int i) { return P.o_ll + (size_t)b * K + i; },
+                    [&](int i, unsigned v) { S.a[i] = __uint_as_float(v); });
+            if (!P.multi || b == P.B - 1) lds_barrier();
+            if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
+        };
+        auto epi = [&](int b, int r, float y0, float y1) {
+            const long long *x = own_x(P) + b * P.own_max + (r - R.first);
+            put_x(P, b, r - R.first, R, x[0] + to_fix(y0), P.xa_ll, tag);
+            put_x(P, b, r + 1 - R.first, R, x[1] + to_fix(y1), P.xa_ll, tag);
+        };
+        if (P.multi)
+            gemv_phase<true, KTq>(Wo, KT, R.first / kTileRows, R.count / kTileRows, P.B, S.a, S.red,
+                                  P.dummy, wait, stage, epi, K, P.o_rg * KTq);
+        else
+            gemv_phase<false, KTq>(Wo, KT, R.first / kTileRows, R.count / kTileRows, P.B, S.a, S.red,
+                                   P.dummy, wait, stage, epi, 0, P.o_rg * KTq);
+        if (is_ctl_lane0()) trace_stamp(P, ti, 0);
     }
     if (garrive >= 0) bar_arrive(P, garrive, ti);
 }
@@ -2994,8 +2639,7 @@ __device__ __forceinline__ MoeShare moe_share(const StepParams &P) {
 
 // RMSNorm, router, and the gate/up product + SwiGLU of this workgroup's
 // expert slot for each sequence: m[b][slot] as tagged words.
-__device__ __forceinline__ void moe_gateup(const StepParams &P, const Lds &S, int l, int gwait,
-                                           int ti) {
+__device__ __forceinline__ void moe_gateup(const StepParams &P, const Lds &S, int l, int ti) {
     const uint8_t *Lb = P.arena + (size_t)l * P.layer_stride;
     const float *gain = reinterpret_cast<const float *>(Lb + P.off_ffn_norm);
     const MoeShare ms = moe_share(P);
@@ -3009,14 +2653,23 @@ __device__ __forceinline__ void moe_gateup(const StepParams &P, const Lds &S, in
         first = r0 + a0;
         count = a1 - a0;
     }
-    if (gwait >= 0) bar_wait(P, gwait, ti);
+    // (a workgroup without rows in either product reads nothing: nothing it
+    // hands on would hold the residual's owners back from overwriting the
+    // words)
+    if (!member) return;
+    {
+        int a0, a1;
+        split_range(P.down_rg, P.Rc, ms.part, a0, a1);
+        if (count == 0 && a0 == a1) return;
+    }
+    if (is_ctl_lane0()) trace_stamp(P, ti, 1);
     for (int b = 0; b < P.B; ++b) {
-        stage_rms_deferred(P.xf + (size_t)b * P.Hp, gain, P.H, P.Hp, S.a, S.sm);
+        stage_rms_deferred(P, P.xa_ll + (size_t)b * P.Hp, ll_tag(P, l), gain, P.H, P.Hp, S.a, S.sm);
         route_experts(P, S, Lb, b);
         if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
-        const int e = member ? route_table(P)[4 * b + ms.slot] : 0;
-        gemv_phase<true>(
-            Lb + P.off_gu + (size_t)e * P.gu_estride, P.Hp / kTileK, first, count, 1, 1, S.a,
+        const int e = route_table(P)[4 * b + ms.slot];
+        gemv_phase(
+            Lb + P.off_gu + (size_t)e * P.gu_estride, P.Hp / kTileK, first, count, 1, S.a,
             S.red, P.dummy, [&]() {}, [&](int) {},
             [&](int, int r, float gt, float up) {
                 const float rs = rms_scale(S.sm, P.H, P.eps);
@@ -3035,15 +2688,17 @@ __device__ __forceinline__ void moe_down(const StepParams &P, const Lds &S, int 
     if (ms.slot >= P.topk || ms.j >= P.Sc) return;
     int a0, a1;
     split_range(P.down_rg, P.Rc, ms.part, a0, a1);
+    if (a0 == a1) return;
     const int kw = P.KTc * kTileK, c0 = ms.j * kw, nreal = max(0, min(kw, P.F - c0));
+    const int nj = P.topk * P.Sc;
     for (int b = 0; b < P.B; ++b) {
         const int *rt = route_table(P) + 4 * b;
         const int e = rt[ms.slot];
         const float we = __int_as_float(rt[2 + ms.slot]);
-        gemv_phase<true>(
+        gemv_phase(
             P.arena + (size_t)l * P.layer_stride + P.off_down + (size_t)e * P.down_estride +
                 (size_t)ms.j * P.down_rg * P.KTc * kTileBytes,
-            P.KTc, a0, a1 - a0, 1, 1, S.a, S.red, P.dummy, [&]() {},
+            P.KTc, a0, a1 - a0, 1, S.a, S.red, P.dummy, [&]() {},
             [&](int) {
                 if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 1);
                 if ((kl_tid() >> 6) == kCtlWave)
@@ -3061,9 +2716,9 @@ __device__ __forceinline__ void moe_down(const StepParams &P, const Lds &S, int 
                 }
             },
             [&](int, int r, float y0, float y1) {
-                long long *x = P.xf + (size_t)b * P.Hp;
-                add_fix(x + r, we * y0);
-                add_fix(x + r + 1, we * y1);
+                unsigned long long *w = P.dp_ll + ((size_t)b * nj + ms.slot * P.Sc + ms.j) * P.Hp + r;
+                st_ll_f(w, we * y0, ll_tag(P, l));
+                st_ll_f(w + 1, we * y1, ll_tag(P, l));
             });
     }
 }
@@ -3112,7 +2767,7 @@ __device__ __forceinline__ void phase_gateup(KArg ka, int l, int gwait, int garr
         return;
     }
     if (P.E > 1) {
-        moe_gateup(P, S, l, gwait, ti);
+        moe_gateup(P, S, l, ti);
         if (is_ctl_lane0()) trace_stamp(P, ti, 0);
         return;
     }
@@ -3130,14 +2785,15 @@ __device__ __forceinline__ void phase_gateup(KArg ka, int l, int gwait, int garr
     }
     weight_phase<false>(
         P, S, Lb + P.off_gu, P.Hp / kTileK, first, count,
-        [&]() { if (gwait >= 0) bar_wait(P, gwait, ti); }, [&]() {},
+        [&]() { if (is_ctl_lane0()) trace_stamp(P, ti, 1); }, [&]() {},
         [&](int b) {
             if (P.multi) {
                 if (b == 0)
-                    stage_rms_multi(P.xf, P.Hp, gain, P.H, P.Hp, P.B, S.a, P.Hp, S.sm, NoExtra(),
-                                    NoExtra(), 0);
+                    stage_rms_multi(P, P.xa_ll, P.Hp, ll_tag(P, l), gain, P.H, P.Hp, P.B, S.a, P.Hp,
+                                    S.sm, NoExtra(), NoExtra(), 0);
             } else {
-                stage_rms_deferred(P.xf + (size_t)b * P.Hp, gain, P.H, P.Hp, S.a, S.sm);
+                stage_rms_deferred(P, P.xa_ll + (size_t)b * P.Hp, ll_tag(P, l), gain, P.H, P.Hp, S.a,
+                                   S.sm);
             }
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
         },
@@ -3218,11 +2874,6 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
     const StepParams P = load_params(ka);
     const Lds S = lds_layout(kl_smem, P);
     const uint8_t *Wd = P.arena + (size_t)l * P.layer_stride + P.off_down;
-    auto epi = [&](int b, int r, float y0, float y1) {
-        long long *x = P.xf + (size_t)b * P.Hp;
-        add_fix(x + r, y0);
-        add_fix(x + r + 1, y1);
-    };
     if constexpr (BAT) {
         // 2-D partition: KSd K slices (Sc / KSd FFN column blocks each) x row
         // groups, partial sums folded by the next RMSNorm step (as for the O
@@ -3252,8 +2903,16 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
             P.KTc, (size_t)P.down_rg * P.KTc);
     } else if (P.E > 1) {
         moe_down(P, S, l, ti);
+        if ((kl_tid() >> 6) == kCtlWave) gather_down(P, l, P.topk * P.Sc);
+        if (is_ctl_lane0()) trace_stamp(P, ti, 0);
     } else {
         const int j = blockIdx.x / P.Rc, part = blockIdx.x % P.Rc;
+        // (the partial products to the rows' owners, gather_down)
+        auto epi = [&](int b, int r, float y0, float y1) {
+            unsigned long long *w = P.dp_ll + ((size_t)b * P.Sc + j) * P.Hp + r;
+            st_ll_f(w, y0, ll_tag(P, l));
+            st_ll_f(w + 1, y1, ll_tag(P, l));
+        };
         if (j < P.Sc) {
             int a0, a1;
             split_range(P.down_rg, P.Rc, part, a0, a1);
@@ -3301,21 +2960,21 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
                 },
                 [&](int, int, int, uint16_t *) {}, epi, 0, 0, NoGroupDone(), kw);
         }
+        if ((kl_tid() >> 6) == kCtlWave) gather_down(P, l, P.Sc);
+        if (is_ctl_lane0()) trace_stamp(P, ti, 0);
     }
     if (garrive >= 0) bar_arrive(P, garrive, ti);
 }
 
-// The final residual stream -> hidden_out (fp32), elements spread over the
-// grid, threads tid = 0 .. nt - 1 of every workgroup.  (One memory round trip;
-// by one workgroup alone the copy is a chain of B H / kThreads of them, which
-// ended 130 us after the rest of the head at the 8B shape and batch 32, 280 us
-// at the 70B shape.)
-template <bool PS>
-__device__ __forceinline__ void copy_hidden(const StepParams &P, int tid, int nt) {
-    for (int idx = blockIdx.x * nt + tid; idx < P.B * P.H; idx += P.nwg * nt) {
+// Batched path: the final residual stream -> hidden_out (fp32), elements
+// spread over the grid.  (One memory round trip; by one workgroup alone the
+// copy is a chain of B H / kThreads of them, which ended 130 us after the rest
+// of the head at the 8B shape and batch 32, 280 us at the 70B shape.)
+__device__ __forceinline__ void copy_hidden(const StepParams &P) {
+    for (int idx = blockIdx.x * kThreads + kl_tid(); idx < P.B * P.H; idx += P.nwg * kThreads) {
         const int b = idx / P.H;
         const float x = from_fix((long long)ld_dev_u64(P.xf + (size_t)b * P.Hp + idx % P.H));
-        P.hidden_out[idx] = ok_of<PS>(P, b) ? x : __builtin_nanf("");
+        P.hidden_out[idx] = seq_ok(P, b) ? x : __builtin_nanf("");
     }
 }
 
@@ -3343,17 +3002,11 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
         }
         __syncthreads();
     };
-    // per-sequence path: the control wave copies the hidden state once the
-    // compute waves are busy with the product
-    auto hidden = [&]() {
-        if (P.hidden_out && (kl_tid() >> 6) == kCtlWave)
-            copy_hidden<!BAT>(P, kl_tid() & 63, 64);
-    };
     weight_phase<BAT>(
         P, S, reinterpret_cast<const uint8_t *>(P.lm_head), P.Hp / kTileK, R.first, R.count,
         [&]() {
             if (gwait >= 0) bar_wait(P, gwait, ti);
-            if (!BAT && R.count == 0) hidden();   // (no rows: nothing is staged)
+            if (!BAT) owners_wait(P, ti);
         },
         [&]() {
             // (folds the last down projection's partials, x: xf2 -> xf), and
@@ -3363,18 +3016,18 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
             __syncthreads();
             rms_table(P, S);
             if (is_ctl_lane0()) trace_stamp(P, ti, 3);
-            if (P.hidden_out) copy_hidden<!BAT>(P, kl_tid(), kThreads);
+            if (P.hidden_out) copy_hidden(P);
         },
         [&](int b) {
             if (P.multi) {
                 if (b == 0)
-                    stage_rms_multi(P.xf, P.Hp, P.final_norm, P.H, P.Hp, P.B, S.a, P.Hp, S.sm,
-                                    NoExtra(), NoExtra(), 0);
+                    stage_rms_multi(P, P.xb_ll, P.Hp, ll_tag(P, P.L), P.final_norm, P.H, P.Hp, P.B,
+                                    S.a, P.Hp, S.sm, NoExtra(), NoExtra(), 0);
             } else {
-                stage_rms_deferred(P.xf + (size_t)b * P.Hp, P.final_norm, P.H, P.Hp, S.a, S.sm);
+                stage_rms_deferred(P, P.xb_ll + (size_t)b * P.Hp, ll_tag(P, P.L), P.final_norm, P.H,
+                                   P.Hp, S.a, S.sm);
             }
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
-            if (b == 0) hidden();
         },
         [&](int c, int b0, int nb, uint16_t *buf) { stage_act_chunk(P, c, b0, nb, buf); },
         [&](int b, int r, float y0, float y1) {
@@ -3395,11 +3048,23 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
             }
         },
         0, 0, [&](int b0, int nb) { flush(b0, nb); }, P.Hp);
-    if (!BAT) flush(0, P.B);
+    if constexpr (!BAT) {
+        flush(0, P.B);
+        // the hidden state: every workgroup its own rows (each row's last
+        // value was put by the control wave or before the launch)
+        if (P.hidden_out && (kl_tid() >> 6) == kCtlWave) {
+            const OwnRows O = own_rows(P);
+            for (int i = kl_tid() & 63; i < P.B * O.count; i += 64) {
+                const int b = i / O.count, r = i % O.count;
+                P.hidden_out[(size_t)b * P.H + O.first + r] =
+                    ok_of<true>(P, b) ? from_fix(own_x(P)[b * P.own_max + r]) : __builtin_nanf("");
+            }
+        }
+    }
     // the step's last phase: the next step's tags (every workgroup of every
     // launch of this step read the epoch at its start)
     if (blockIdx.x == 0 && kl_tid() == 0)
-        __hip_atomic_store(P.epoch_ptr, ll_next_epoch(*launch_epoch(P), P.L), __ATOMIC_RELAXED,
+        __hip_atomic_store(P.epoch_ptr, ll_next_epoch(*launch_epoch(P), P.L + 1), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     if (is_ctl_lane0()) trace_stamp(P, ti, 0);
 }
@@ -3429,8 +3094,9 @@ __global__ __launch_bounds__(kThreads) void kl_step_kernel(StepParams P, int l0,
     auto xb = [&]() { return batched ? na++ : -1; };    // the phase's own barrier
     const bool has_attn = phases & kPhAttn, has_op = phases & kPhOproj;
     const bool has_down = phases & kPhDown;
+    // (the per-sequence path has no grid barriers: tagged words throughout)
     if (phases & kPhEmbed) {
-        phase_embed(ka, -1, ga((has_qkv && nlay > 0) || has_head), ti++);
+        phase_embed(ka, -1, BAT ? ga((has_qkv && nlay > 0) || has_head) : -1, ti++);
     }
     for (int l = l0; l < l1; ++l) {
         // batched steps: attn -> oproj and gateup -> down are grid barriers
@@ -3441,7 +3107,7 @@ __global__ __launch_bounds__(kThreads) void kl_step_kernel(StepParams P, int l0,
         }
         if (phases & kPhAttn) phase_attn<D, G, BAT>(ka, l, BAT ? ga(has_op) : -1, ti++);
         if (phases & kPhOproj) {
-            const int w = BAT && has_attn ? gw() : -1, a = ga(has_gu);
+            const int w = BAT && has_attn ? gw() : -1, a = BAT ? ga(has_gu) : -1;
             phase_oproj<D, G, BAT>(ka, l, w, a, ti++);
         }
         if (phases & kPhGateUp) {
@@ -3452,7 +3118,7 @@ __global__ __launch_bounds__(kThreads) void kl_step_kernel(StepParams P, int l0,
             // (batched: the SwiGLU fold of the gate/up partials ends with a
             // grid barrier of its own)
             const int w = BAT && has_gu ? gw() : -1, x = xb();
-            phase_down<BAT>(ka, l, w, x, ga((has_qkv && l + 1 < l1) || has_head), ti++);
+            phase_down<BAT>(ka, l, w, x, BAT ? ga((has_qkv && l + 1 < l1) || has_head) : -1, ti++);
         }
     }
     if (has_head) {
