@@ -1186,11 +1186,13 @@ __device__ __forceinline__ GemmLds gemm_lds(char *smem) {
 // compiler wait for all outstanding loads before each of the loop's LDS
 // accesses (draining the ring once per pass), so the two modes are separate
 // instances and the streaming copies run in a loop of the control wave's own.
-template <bool resident, class Pre, class Stage, class Epi>
+// ready(c) (control wave) waits until chunk c's inputs are complete.
+template <bool resident, class Pre, class Ready, class Stage, class Epi>
 __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, int KT, int first,
                                                int count, int ktg, size_t gstride, int b0,
                                                int nb, const uint8_t *dummy, const GemmLds &L,
-                                               Pre &&pre, Stage &&stage, Epi &&epi) {
+                                               Pre &&pre, Ready &&ready, Stage &&stage,
+                                               Epi &&epi) {
     constexpr int U = kGemmDepth;
     constexpr int CT = kGemmChunkK / kTileK;   // k-tiles per chunk
     constexpr int MB = kGemmMaxBlk;
@@ -1251,9 +1253,17 @@ __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, in
     }
     pre();
     if (count <= 0) return;
+    // The first chunk (resident: both) is copied by all nine waves, whose
+    // rings are full by now: copied by the control wave alone it took three
+    // round trips, as one wave has at most 63 memory operations in flight.
+    if (!compute) {
+        ready(0);
+        if (resident && nkc > 1) ready(1);
+    }
     __syncthreads();   // (the buffers may still hold the previous sequence group)
-    stage(0, L.act[0]);
-    if (resident && nkc > 1) stage(1, L.act[1]);
+    stage(0, L.act[0], true);
+    if (resident && nkc > 1) stage(1, L.act[1], true);
+    ctl_copy_wait();
     __syncthreads();
 
     if constexpr (!resident) {
@@ -1261,7 +1271,11 @@ __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, in
             // chunk f + 1 into buffer (f + 1) % 2 while the compute waves work on chunk f
             const int total = ngrp_wg * nkc;
             for (int f = 0; f < total; ++f) {
-                if (f + 1 < total) stage((f + 1) % nkc, L.act[(f + 1) & 1]);
+                if (f + 1 < total) {
+                    if (f + 1 < nkc) ready(f + 1);
+                    stage((f + 1) % nkc, L.act[(f + 1) & 1], false);
+                    ctl_copy_wait();
+                }
                 __syncthreads();
             }
             return;
@@ -1341,17 +1355,17 @@ __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, in
     }
 }
 
-template <class Pre, class Stage, class Epi>
+template <class Pre, class Ready, class Stage, class Epi>
 __device__ __forceinline__ void gemm_rows(const uint8_t *__restrict__ W, int KT, int first,
                                           int count, int ktg, size_t gstride, int b0, int nb,
                                           const uint8_t *dummy, const GemmLds &L, Pre &&pre,
-                                          Stage &&stage, Epi &&epi) {
+                                          Ready &&ready, Stage &&stage, Epi &&epi) {
     if (KT <= 2 * (kGemmChunkK / kTileK))
-        gemm_rows_mode<true>(W, KT, first, count, ktg, gstride, b0, nb, dummy, L, pre, stage,
-                             epi);
+        gemm_rows_mode<true>(W, KT, first, count, ktg, gstride, b0, nb, dummy, L, pre, ready,
+                             stage, epi);
     else
-        gemm_rows_mode<false>(W, KT, first, count, ktg, gstride, b0, nb, dummy, L, pre, stage,
-                              epi);
+        gemm_rows_mode<false>(W, KT, first, count, ktg, gstride, b0, nb, dummy, L, pre, ready,
+                              stage, epi);
 }
 
 
@@ -1376,8 +1390,9 @@ __device__ __forceinline__ void gemm_rows(const uint8_t *__restrict__ W, int KT,
 // matrix-core engine otherwise (sequences in groups of kGemmBatch; the
 // weights stream once per group).  In the batched path every input is staged
 // as bf16 chunks: prep() runs once after wait(), both once the first weight
-// loads are in flight; stageb(c, b0, nb, buf) fills chunk c for sequences
-// b0 .. b0 + nb - 1 (the control wave's memory-to-LDS copies).
+// loads are in flight; ready(c) (control wave) waits for chunk c's inputs;
+// stageb(c, b0, nb, buf, all) fills chunk c for sequences b0 .. b0 + nb - 1
+// (memory-to-LDS copies, by all waves or by the control wave).
 // (done(b0, nb) runs in every thread after the matrix-core path's group of
 // sequences b0 .. b0 + nb - 1)
 struct NoGroupDone {
@@ -1386,14 +1401,17 @@ struct NoGroupDone {
 // Per-sequence path: with P.multi, the sequences' vectors sit astride floats
 // apart and share each pass (stage1(b) is called for every b before the
 // pass; stage1(0) may stage them all).
+struct NoReady {   // weight_phase whose inputs are complete after prep()
+    __device__ void operator()(int) const {}
+};
 template <bool BAT, class Wait, class Prep, class Stage1, class StageB, class Epi,
-          class Done = NoGroupDone>
+          class Done = NoGroupDone, class Ready = NoReady>
 __device__ __forceinline__ void weight_phase(const StepParams &P, const Lds &S,
                                              const uint8_t *W, int KT, int first, int count,
                                              Wait &&wait, Prep &&prep, Stage1 &&stage1,
                                              StageB &&stageb, Epi &&epi, int ktg = 0,
                                              size_t gstride = 0, Done done = Done(),
-                                             int astride = 0) {
+                                             int astride = 0, Ready ready = Ready()) {
     if constexpr (!BAT) {
         if (P.multi)
             gemv_phase<true>(W, KT, first, count, P.B, S.a, S.red, P.dummy, wait, stage1, epi,
@@ -1412,7 +1430,8 @@ __device__ __forceinline__ void weight_phase(const StepParams &P, const Lds &S,
                           prep();
                       }
                   },
-                  [&](int c, uint16_t *buf) { stageb(c, b0, nb, buf); }, epi);
+                  [&](int c) { if (b0 == 0) ready(c); },
+                  [&](int c, uint16_t *buf, bool all) { stageb(c, b0, nb, buf, all); }, epi);
         done(b0, nb);
     }
 }
@@ -1530,35 +1549,57 @@ __device__ __forceinline__ float rms_of(const StepParams &P, const Lds &S, int b
 // row stride ld.  The copies are straight-line code without branches: a
 // branch or loop between two copies makes the compiler wait for the first
 // before issuing the second (it cannot tell that their LDS ranges are
-// disjoint).  So every padding row (b >= nb) receives a copy of row nb - 1,
-// and lanes past kc copy a clamped in-row address: the matrix-core loop
-// reads neither (outputs of padding sequences are discarded, columns past
-// kc are never consumed).
-__device__ __forceinline__ void ctl_copy_rows(const uint16_t *hi, const uint16_t *lo, int ld,
-                                              int k0, int kc, int b0, int nb, uint16_t *buf) {
-    if ((kl_tid() >> 6) != kCtlWave) return;
+// disjoint).  Lanes past kc copy a clamped in-row address, and padding rows (b
+// >= nb) are left as they are (or receive a copy of row nb - 1): the
+// matrix-core loop's columns are independent, outputs of padding sequences
+// are discarded, and columns past kc are never consumed.
+//
+// NR rows first, first + step, ...
+template <int NR>
+__device__ __forceinline__ void copy_rows(const uint16_t *hi, const uint16_t *lo, int ld, int k0,
+                                          int kc, int b0, int nb, uint16_t *buf, int first,
+                                          int step) {
     const int lane = kl_tid() & 63;
     const uint64_t col = (uint64_t)(k0 + min(lane * 8, kc - 8));
     // (the row offset is opaque to the compiler at each step, so that the
     // addresses are formed right before their copies instead of all at once)
-    uint64_t row = (uint64_t)b0 * ld;
+    uint64_t row = (uint64_t)(b0 + first) * ld;
     const uint64_t last = (uint64_t)(b0 + nb - 1) * ld;
+    uint16_t *d = buf + first * kActStride;
 #pragma unroll
-    for (int b = 0; b < kGemmBatch; ++b) {
+    for (int b = 0; b < NR; ++b) {
         const uint64_t o = min(row, last) + col;
-        __builtin_amdgcn_global_load_lds(hi + o, buf + b * kActStride, 16, 0, kLdsCoherent);
-        __builtin_amdgcn_global_load_lds(lo + o, buf + kLoOff + b * kActStride, 16, 0,
+        __builtin_amdgcn_global_load_lds(hi + o, d + b * step * kActStride, 16, 0, kLdsCoherent);
+        __builtin_amdgcn_global_load_lds(lo + o, d + kLoOff + b * step * kActStride, 16, 0,
                                          kLdsCoherent);
-        row += (uint64_t)ld;
+        row += (uint64_t)step * ld;
         asm volatile("" : "+v"(row));
     }
-    ctl_copy_wait();
+}
+// All waves (wave w the rows w, w + kWaves + 1, ...) or the control wave; the
+// caller waits for the copies.
+__device__ __forceinline__ void copy_chunk(const uint16_t *hi, const uint16_t *lo, int ld, int k0,
+                                           int kc, int b0, int nb, uint16_t *buf, bool all) {
+    constexpr int NW = kWaves + 1;
+    static_assert(kGemmBatch <= 4 * NW, "rows per wave");
+    const int wid = __builtin_amdgcn_readfirstlane(kl_tid() >> 6);
+    if (all) {
+        const int n = nb > wid ? (nb - wid + NW - 1) / NW : 0;
+        if (n == 1) copy_rows<1>(hi, lo, ld, k0, kc, b0, nb, buf, wid, NW);
+        else if (n == 2) copy_rows<2>(hi, lo, ld, k0, kc, b0, nb, buf, wid, NW);
+        else if (n == 3) copy_rows<3>(hi, lo, ld, k0, kc, b0, nb, buf, wid, NW);
+        else if (n == 4) copy_rows<4>(hi, lo, ld, k0, kc, b0, nb, buf, wid, NW);
+    } else if (wid == kCtlWave) {
+        if (nb <= 8) copy_rows<8>(hi, lo, ld, k0, kc, b0, nb, buf, 0, 1);
+        else if (nb <= 16) copy_rows<16>(hi, lo, ld, k0, kc, b0, nb, buf, 0, 1);
+        else copy_rows<kGemmBatch>(hi, lo, ld, k0, kc, b0, nb, buf, 0, 1);
+    }
 }
 
 __device__ __forceinline__ void stage_act_chunk(const StepParams &P, int c, int b0, int nb,
-                                                uint16_t *buf) {
+                                                uint16_t *buf, bool all) {
     const int k0 = c * kGemmChunkK;
-    ctl_copy_rows(P.act, P.act_lo, P.Hp, k0, min(kGemmChunkK, P.Hp - k0), b0, nb, buf);
+    copy_chunk(P.act, P.act_lo, P.Hp, k0, min(kGemmChunkK, P.Hp - k0), b0, nb, buf, all);
 }
 
 // Chunk c of a two-term bf16 matrix src / src_lo [b][ld] with K columns
@@ -1566,9 +1607,9 @@ __device__ __forceinline__ void stage_act_chunk(const StepParams &P, int c, int 
 // the previous chunk).
 __device__ __forceinline__ void stage_bf16_chunk(const uint16_t *src, const uint16_t *src_lo,
                                                  int ld, int K, int c, int b0, int nb,
-                                                 uint16_t *buf) {
+                                                 uint16_t *buf, bool all) {
     const int k0 = c * kGemmChunkK;
-    ctl_copy_rows(src, src_lo, ld, k0, min(kGemmChunkK, K - k0), b0, nb, buf);
+    copy_chunk(src, src_lo, ld, k0, min(kGemmChunkK, K - k0), b0, nb, buf, all);
 }
 
 // Per-sequence path: the residual has one owner per row, the workgroup that
@@ -1790,16 +1831,17 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
                 if (is_ctl_lane0()) trace_stamp(P, ti, 3);
             },
             [&](int) {},
-            [&](int c, int b0, int nb, uint16_t *buf) {
-                const int sl = col0 / kGemmChunkK + c;
-                if (b0 == 0) norm_wait(P, 2 * l, sl, sl + 1);
-                stage_bf16_chunk(P.act + col0, P.act_lo + col0, P.Hp, KTs * kTileK, c, b0, nb, buf);
+            [&](int c, int b0, int nb, uint16_t *buf, bool all) {
+                stage_bf16_chunk(P.act + col0, P.act_lo + col0, P.Hp, KTs * kTileK, c, b0, nb, buf, all);
             },
             [&](int b, int r, float y0, float y1) {
                 st_dev(pp + (size_t)b * rows + r, y0);
                 st_dev(pp + (size_t)b * rows + r + 1, y1);
             },
-            KT, 0);
+            KT, 0, NoGroupDone(), 0, [&](int c) {
+                const int sl = col0 / kGemmChunkK + c;
+                norm_wait(P, 2 * l, sl, sl + 1);
+            });
         bar_arrive(P, qbar, -1);
         bar_wait(P, qbar, -1);
         if (member) {
@@ -1831,7 +1873,7 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
             }
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
         },
-        [&](int, int, int, uint16_t *) {},
+        [&](int, int, int, uint16_t *, bool) {},
         [&](int b, int r, float y0, float y1) {
             // the deferred RMSNorm scale
             const float rs = rms_scale(seq_sm(P, S, b), P.H, P.eps);
@@ -2509,8 +2551,8 @@ __device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int garri
             P, S, Wo + (size_t)ksc * gps * P.o_rg * KTO * kTileBytes, gps * KTO, a0, a1 - a0,
             [&]() { if (gwait >= 0) bar_wait(P, gwait, ti); },
             [&]() {}, [&](int) {},
-            [&](int c, int b0, int nb, uint16_t *buf) {
-                stage_bf16_chunk(P.acto + col0, P.acto_lo + col0, P.nq * D, width, c, b0, nb, buf);
+            [&](int c, int b0, int nb, uint16_t *buf, bool all) {
+                stage_bf16_chunk(P.acto + col0, P.acto_lo + col0, P.nq * D, width, c, b0, nb, buf, all);
             },
             [&](int b, int r, float y0, float y1) {
                 st_dev(part + (size_t)b * P.Hp + r, y0);
@@ -2753,16 +2795,17 @@ __device__ __forceinline__ void phase_gateup(KArg ka, int l, int gwait, int garr
                 if (is_ctl_lane0()) trace_stamp(P, ti, 3);
             },
             [&](int) {},
-            [&](int c, int b0, int nb, uint16_t *buf) {
-                const int sl = col0 / kGemmChunkK + c;
-                if (b0 == 0) norm_wait(P, 2 * l + 1, sl, sl + 1);
-                stage_bf16_chunk(P.act + col0, P.act_lo + col0, P.Hp, KTs * kTileK, c, b0, nb, buf);
+            [&](int c, int b0, int nb, uint16_t *buf, bool all) {
+                stage_bf16_chunk(P.act + col0, P.act_lo + col0, P.Hp, KTs * kTileK, c, b0, nb, buf, all);
             },
             [&](int b, int r, float gt, float up) {
                 st_dev(part + (size_t)b * grow + r, gt);
                 st_dev(part + (size_t)b * grow + r + 1, up);
             },
-            KT, 0);
+            KT, 0, NoGroupDone(), 0, [&](int c) {
+                const int sl = col0 / kGemmChunkK + c;
+                norm_wait(P, 2 * l + 1, sl, sl + 1);
+            });
         if (garrive >= 0) bar_arrive(P, garrive, ti);
         return;
     }
@@ -2797,7 +2840,7 @@ __device__ __forceinline__ void phase_gateup(KArg ka, int l, int gwait, int garr
             }
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
         },
-        [&](int, int, int, uint16_t *) {},
+        [&](int, int, int, uint16_t *, bool) {},
         [&](int b, int r, float gt, float up) {
             // the deferred RMSNorm scale
             const float rs = rms_scale(seq_sm(P, S, b), P.H, P.eps);
@@ -2893,8 +2936,8 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
                 if (is_ctl_lane0()) trace_stamp(P, ti, 3);
             },
             [&](int) {},
-            [&](int c, int b0, int nb, uint16_t *buf) {
-                stage_bf16_chunk(P.actm + col0, P.actm_lo + col0, P.Fp, width, c, b0, nb, buf);
+            [&](int c, int b0, int nb, uint16_t *buf, bool all) {
+                stage_bf16_chunk(P.actm + col0, P.actm_lo + col0, P.Fp, width, c, b0, nb, buf, all);
             },
             [&](int b, int r, float y0, float y1) {
                 st_dev(part + (size_t)b * P.Hp + r, y0);
@@ -2958,7 +3001,7 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
                         trace_stamp(P, ti, 3);
                     }
                 },
-                [&](int, int, int, uint16_t *) {}, epi, 0, 0, NoGroupDone(), kw);
+                [&](int, int, int, uint16_t *, bool) {}, epi, 0, 0, NoGroupDone(), kw);
         }
         if ((kl_tid() >> 6) == kCtlWave) gather_down(P, l, P.Sc);
         if (is_ctl_lane0()) trace_stamp(P, ti, 0);
@@ -3029,7 +3072,7 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
             }
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
         },
-        [&](int c, int b0, int nb, uint16_t *buf) { stage_act_chunk(P, c, b0, nb, buf); },
+        [&](int c, int b0, int nb, uint16_t *buf, bool all) { stage_act_chunk(P, c, b0, nb, buf, all); },
         [&](int b, int r, float y0, float y1) {
             // the deferred RMSNorm scale
             const float rs = !BAT ? rms_scale(seq_sm(P, S, b), P.H, P.eps) : rms_of(P, S, b);
