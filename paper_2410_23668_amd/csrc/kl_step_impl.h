@@ -149,6 +149,22 @@ __device__ __forceinline__ void split_range(int n, int parts, int i, int &a, int
     b = (int)((long long)n * (i + 1) / parts);
 }
 
+// The same for the rows of a long weight stream, 4 % more to the workgroups
+// on even XCDs (workgroup w runs on XCD w % 8) and 4 % less to those on odd
+// ones.  Under a full read stream the odd XCD of each pair gets 8 to 10 % less
+// of the bandwidth: with equal shares the 70B shape's gate/up product ended
+// after 128 us on even XCDs and 140 us on odd ones, the 8B shape's LM head
+// after 140 and 152.  (Shares of a few rows come out equal.)
+__device__ __forceinline__ void split_rows(int n, int parts, int i, int &a, int &b) {
+    const int odd = (blockIdx.x - i) & 1;   // XCD parity of part 0
+    const auto bound = [&](int k) {
+        const long long skew = (k & 1) ? (odd ? -1 : 1) : 0;   // in 1/25 of a share
+        return k == parts ? n : (int)(n * (25ll * k + skew) / (25ll * parts));
+    };
+    a = bound(i);
+    b = bound(i + 1);
+}
+
 // A sequence whose token or position is out of range still runs through the
 // step with clamped values (every read stays in bounds), but writes nothing
 // the caller owns except NaN logits and hidden state: its K/V slots are left
@@ -230,9 +246,7 @@ __device__ __forceinline__ void st_dev_u32(unsigned *p, unsigned v) {
 // workgroups add: results are reproducible however the work is split.  The
 // range (+-2^31) and resolution (2^-32) are far beyond fp32 activations'.
 constexpr double kFixScale = 4294967296.0;   // 2^32
-__device__ __forceinline__ long long to_fix(float v) {
-    return __double2ll_rn((double)v * kFixScale);
-}
+__device__ __forceinline__ long long to_fix(double v) { return __double2ll_rn(v * kFixScale); }
 __device__ __forceinline__ float from_fix(long long v) {
     return (float)v * (1.0f / 4294967296.0f);
 }
@@ -792,9 +806,11 @@ constexpr int kRedStride = kWaves * kRgBatch * kTileRows;
 // A workgroup owns the row groups first .. first + count - 1 (a strided
 // assignment, stride = grid size, was measured no faster).
 struct RgRange { int first, count; };
+template <bool BAT>
 __device__ __forceinline__ RgRange own_rgs(int nrg, const StepParams &P) {
     int a, b;
-    split_range(nrg, P.nwg, blockIdx.x, a, b);
+    if (BAT) split_range(nrg, P.nwg, blockIdx.x, a, b);
+    else split_rows(nrg, P.nwg, blockIdx.x, a, b);
     return RgRange{a, b - a};
 }
 
@@ -807,6 +823,9 @@ __device__ __forceinline__ RgRange own_rgs(int nrg, const StepParams &P) {
 // Both orders are fixed by the partition alone.
 // The first ring of loads is issued before wait() and stage(0), overlapping
 // their latency.
+// The waves' sums are added in 64 bits.  (A long K range of several packed
+// matrices, KTG > 0: each matrix's products are summed apart as well, so that
+// the O projection over all heads rounds no more than its sums by head did.)
 // KTG > 0: the K range spans several packed matrices of KTG k-tiles per row
 // group each, gstride tiles apart (k-tile kt of row group r is tile
 // (kt / KTG) gstride + r KTG + kt % KTG); 0: one matrix of KT.
@@ -885,7 +904,8 @@ __device__ __forceinline__ void gemv_rows(const uint8_t *__restrict__ W, int KT,
             if (ib == 0) stage(b);
             const int nrg = min(BATCH, count - ib);
             int cr = RowSplit ? wid : 0, ck = 0;   // batch item of the row group in progress
-            float acc = 0.f;
+            float acc = 0.f, tot = 0.f;   // (KTG: of the packed matrix in progress, of those before)
+            int cg = 0;
             // item i sits in slot i % U and is refilled with item i + U (or
             // the dummy line) right after it is consumed
             if (compute)
@@ -905,14 +925,19 @@ __device__ __forceinline__ void gemv_rows(const uint8_t *__restrict__ W, int KT,
                         acc = fmaf(bf_hi(wv.z), a1.y, acc);
                         acc = fmaf(bf_lo(wv.w), a1.z, acc);
                         acc = fmaf(bf_hi(wv.w), a1.w, acc);
+                        if (KTG && ++cg == KTG) {
+                            tot += acc;
+                            acc = 0.f;
+                            cg = 0;
+                        }
                         if (++ck == nk) {
-                            const float t = sum8(acc);
+                            const float t = sum8(tot + acc);
                             if (sub == 0) {
                                 if (RowSplit) red[cr * kTileRows + row] = t;
                                 else red[(wid * kRgBatch + cr) * kTileRows + row] = t;
                             }
-                            acc = 0.f;
-                            ck = 0;
+                            acc = tot = 0.f;
+                            ck = cg = 0;
                             cr += rstep;
                         }
                     }
@@ -922,7 +947,7 @@ __device__ __forceinline__ void gemv_rows(const uint8_t *__restrict__ W, int KT,
             lds_barrier();
             for (int t = kl_tid(); t < nrg * (kTileRows / 2); t += kThreads) {
                 const int rgi = t / (kTileRows / 2), pr = (t % (kTileRows / 2)) * 2;
-                float y0 = 0.f, y1 = 0.f;
+                double y0 = 0, y1 = 0;
                 if (RowSplit) {
                     y0 = red[rgi * kTileRows + pr];
                     y1 = red[rgi * kTileRows + pr + 1];
@@ -1012,11 +1037,15 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
             for (int bb = 0; bb < B; ++bb) stage(bb);
         const int nrg = min(BATCH, count - ib);
         int cr = 0, ck = 0;   // the group in progress (its first row group), its k index
-        float acc[NP][kMultiSeq];
+        float acc[NP][kMultiSeq], tot[KTG ? NP : 1][KTG ? kMultiSeq : 1];
+        int cg = 0;
 #pragma unroll
         for (int h = 0; h < NP; ++h)
 #pragma unroll
-            for (int bb = 0; bb < kMultiSeq; ++bb) acc[h][bb] = 0.f;
+            for (int bb = 0; bb < kMultiSeq; ++bb) {
+                acc[h][bb] = 0.f;
+                if (KTG) tot[h][bb] = 0.f;
+            }
         // a group's NP tiles sit in slots s .. s + NP - 1; they are consumed
         // together (each sequence's vector read once for all of them), then
         // refilled in order
@@ -1050,6 +1079,16 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
                             }
                         }
                     }
+                    if (KTG && ++cg == KTG) {
+#pragma unroll
+                        for (int hh = 0; hh < NP; ++hh)
+#pragma unroll
+                            for (int bb = 0; bb < kMultiSeq; ++bb) {
+                                tot[hh][bb] += acc[hh][bb];
+                                acc[hh][bb] = 0.f;
+                            }
+                        cg = 0;
+                    }
                     if (++ck == nk) {   // the group's row groups are done
 #pragma unroll
                         for (int hh = 0; hh < NP; ++hh) {
@@ -1059,13 +1098,14 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
 #pragma unroll
                             for (int bb = 0; bb < kMultiSeq; ++bb) {
                                 if (bb < B) {
-                                    const float t = sum8(acc[hh][bb]);
+                                    const float t = sum8(KTG ? tot[hh][bb] + acc[hh][bb] : acc[hh][bb]);
                                     if (c < mine && sub == 0) red[bb * kRedStride + ri] = t;
                                 }
                                 acc[hh][bb] = 0.f;
+                                if (KTG) tot[hh][bb] = 0.f;
                             }
                         }
-                        ck = 0;
+                        ck = cg = 0;
                         cr += NP;
                     }
                 }
@@ -1078,7 +1118,7 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
             const int bb = t / (nrg * (kTileRows / 2)), tt = t - bb * (nrg * (kTileRows / 2));
             const int rgi = tt / (kTileRows / 2), pr = (tt % (kTileRows / 2)) * 2;
             const float *rd = red + bb * kRedStride;
-            float y0 = 0.f, y1 = 0.f;
+            double y0 = 0, y1 = 0;
             if (RowSplit) {
                 y0 = rd[rgi * kTileRows + pr];
                 y1 = rd[rgi * kTileRows + pr + 1];
@@ -1640,6 +1680,8 @@ __device__ __forceinline__ void gather_down(const StepParams &P, int l, int nj) 
     const OwnRows R = own_rows(P);
     const int n = nj * R.count, lane = kl_tid() & 63;
     if (n == 0) return;
+    // (a sequence at a time, in rounds of as many loads as the 8B shape needs:
+    // larger rounds, or all sequences in one, measured no faster)
     for (int b = 0; b < P.B; ++b) {
         const unsigned long long *src = P.dp_ll + (size_t)b * nj * P.Hp + R.first;
         unsigned long long *own = reinterpret_cast<unsigned long long *>(own_x(P) + b * P.own_max);
@@ -1943,6 +1985,22 @@ __device__ __forceinline__ int attn_units_of(int pnew, int up) { return pnew / u
 
 // A workgroup's share, in LDS (seg_table): first sequence, its first unit,
 // units of the share, units of the whole batch, workgroups that have shares.
+// On the per-sequence path short shares keep to one sequence each (a second
+// segment costs about 3.5 us, a share's odd units less than that below 96
+// units): sequence b's workgroups are one, and of the others the part that its
+// units have of the batch's.
+constexpr int kSegUnits = 96;
+__device__ __forceinline__ bool seg_by_sequence(const StepParams &P, int T) {
+    return !P.batched && P.B <= P.Sg && T < kSegUnits * P.Sg;
+}
+struct SeqParts { int first, span, count; };   // workgroups of a sequence; those with units
+__device__ __forceinline__ SeqParts seq_parts(const StepParams &P, int b, int before, int units,
+                                              int T) {
+    const int rest = P.Sg - P.B;
+    const int p0 = b + (int)((long long)rest * before / T);
+    const int p1 = b + 1 + (int)((long long)rest * (before + units) / T);
+    return SeqParts{p0, p1 - p0, min(p1 - p0, units)};
+}
 // (one wave, once per launch, before the launch's first barrier)
 __device__ __forceinline__ void seg_init(const StepParams &P, int lane) {
     const int up = 2048 / P.d;
@@ -1952,10 +2010,30 @@ __device__ __forceinline__ void seg_init(const StepParams &P, int lane) {
         for (int off = 1; off < 64; off <<= 1) u += from_lane(u, lane ^ off);
         T += u;
     }
-    const int np = min(P.Sg, T), part = blockIdx.x % P.Sg;
+    const int part = blockIdx.x % P.Sg;
+    int *t = seg_table(P);
+    const bool whole = seg_by_sequence(P, T);
+    if (whole) {   // (B <= kMfmaBatch: one lane walks the sequences)
+        if (lane == 0) {
+            int b = 0, before = 0, u = 0;
+            SeqParts q{};
+            for (;; ++b, before += u) {
+                u = attn_units_of(eff_pos(P, b), up);
+                q = seq_parts(P, b, before, u, T);
+                if (b + 1 == P.B || part < q.first + q.span) break;
+            }
+            int x0 = 0, x1 = 0;
+            if (part - q.first < q.count) split_range(u, q.count, part - q.first, x0, x1);
+            t[0] = b;
+            t[1] = x0;
+            t[2] = x1 - x0;
+            t[3] = T;
+        }
+        return;
+    }
+    const int np = min(P.Sg, T);
     int a = 0, e = 0;
     if (part < np) split_range(T, np, part, a, e);
-    int *t = seg_table(P);
     if (lane == 0) {
         t[0] = t[1] = 0;
         t[2] = e - a;
@@ -2116,9 +2194,8 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
         };
         enter();
         lds_barrier();
-        // D = 128: 4 column blocks with two terms in one, the third apart;
-        // D = 64: 2 column blocks per term
-        constexpr int NQB = D == 128 ? (LL ? 8 : 4) : (LL ? 6 : 4);
+        // query operands: D = 128: 4 column blocks with two terms in one, then
+        // 4 with the third; D = 64: 2 column blocks per term
         for (int seg = 0;; ++seg) {
             const int z = seg & 1;
             left -= u1 - u0;
@@ -2150,24 +2227,40 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
             auto unit = [&](u32x4 *kq, u32x4 *vq, int p0, int lim, auto &&kdone, auto &&vdone) {
                 float s[4];
                 if constexpr (D == 128) {
-                    f32x4 t = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int x = 0; x < NQB; ++x)
-                        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, kq[x & 3]), x < 4 ? qb[x & 3] : query(x, lane), t,
+                    const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
+                    auto dot = [&](int x, const f32x4 &c) {
+                        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, kq[x & 3]), x < 4 ? qb[x & 3] : query(x, lane), c,
                             0, 0, 0);
+                    };
+                    if constexpr (LL) {
+                        // (the column blocks' sums and the third terms' on their
+                        // own, added as a tree: in one accumulator the scores'
+                        // rounding grew the step's error by a half)
+                        f32x4 a = dot(0, z4) + dot(1, z4);
+                        a += dot(2, z4) + dot(3, z4);
+                        const f32x4 c = dot(7, dot(6, dot(5, dot(4, z4))));
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) s[v] = t[v] + dpp<0x128>(t[v]);   // the terms
+                        for (int v = 0; v < 4; ++v) s[v] = a[v] + (dpp<0x128>(a[v]) + c[v]);
+                    } else {
+                        const f32x4 a = dot(3, dot(2, dot(1, dot(0, z4))));
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) s[v] = a[v] + dpp<0x128>(a[v]);   // both terms
+                    }
                 } else {
                     f32x4 t[2];
 #pragma unroll
                     for (int y = 0; y < 2; ++y) {
-                        t[y] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int x = 0; x < NQB; ++x)
-                            t[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
+                        auto dot = [&](int x, const f32x4 &c) {
+                            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                                 __builtin_bit_cast(bf16x8, kq[2 * y + (x & 1)]),
-                                x < 4 ? qb[x & 3] : query(x, lane), t[y], 0, 0, 0);
+                                x < 4 ? qb[x & 3] : query(x, lane), c, 0, 0, 0);
+                        };
+                        if constexpr (LL)
+                            t[y] = (dot(0, z4) + dot(1, z4)) + dot(5, dot(4, dot(3, dot(2, z4))));
+                        else
+                            t[y] = dot(3, dot(2, dot(1, dot(0, z4))));
                     }
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
@@ -2440,8 +2533,8 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
     lds_barrier();   // (the attention area is the next phase's)
 }
 
-// Per-sequence path, control wave: the merged attention outputs this
-// workgroup hands on, o = sum_c w_c A_c / sum_c w_c L_c with w_c = 2^(M_c - M),
+// Per-sequence path, one wave: the merged attention outputs of sequence b that
+// this workgroup hands on, o = sum_c w_c A_c / sum_c w_c L_c with w_c = 2^(M_c - M),
 // M the largest of the parts' maxima (A_c, M_c, L_c the parts' unnormalised
 // outputs, maxima in log2 units and sums).  Items of 16 outputs of one query
 // head and sequence are spread over the grid (8B shape, batch 1: one per
@@ -2450,19 +2543,28 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
 // them.  Lane 16 c + j takes output j of parts c, c + 4, ..., lane c the
 // maximum and sum of part c.
 template <int D, int G>
-__device__ __forceinline__ void merge_parts(const StepParams &P, int l) {
+__device__ __forceinline__ void merge_parts(const StepParams &P, int l, int b) {
     constexpr int MD = 16, WD = D + 2, NB = 8;   // outputs per item; loads per lane and round
     const int lane = kl_tid() & 63, j = lane & 15, cl = lane >> 4;
     const unsigned tag = ll_tag(P, l);
     const int T = __builtin_amdgcn_readfirstlane(seg_table(P)[3]);
     const int np = __builtin_amdgcn_readfirstlane(seg_table(P)[4]);
     const int items = P.nq * (D / MD);
-    int seq0 = 0;
-    for (int b = 0; b < P.B; ++b) {
-        const int U = attn_units_of(__builtin_amdgcn_readfirstlane(pos_of<true>(P, b)), 2048 / D);
-        const int f = (int)(((long long)(seq0 + 1) * np - 1) / T);
-        const int nc = (int)(((long long)(seq0 + U) * np - 1) / T) - f + 1;
-        seq0 += U;
+    const auto units = [&](int q) {
+        return attn_units_of(__builtin_amdgcn_readfirstlane(pos_of<true>(P, q)), 2048 / D);
+    };
+    int seq0 = 0;   // sequence b's first unit, counted over the batch
+    for (int q = 0; q < b; ++q) seq0 += units(q);
+    {
+        int f, nc;
+        if (seg_by_sequence(P, T)) {
+            const SeqParts q = seq_parts(P, b, seq0, units(b), T);
+            f = q.first;
+            nc = q.count;
+        } else {
+            f = (int)(((long long)(seq0 + 1) * np - 1) / T);
+            nc = (int)(((long long)(seq0 + units(b)) * np - 1) / T) - f + 1;
+        }
         for (int it = blockIdx.x; it < items; it += P.nwg) {
             const int h = it / (D / MD), d0 = it % (D / MD) * MD, g = h / G;
             const unsigned long long *src =
@@ -2565,26 +2667,27 @@ __device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int garri
         const int K = P.nq * D, KT = P.nq * KTq;
         const unsigned tag = ll_tag(P, l);
         auto wait = [&]() {
-            if ((kl_tid() >> 6) == kCtlWave) {
-                if (is_ctl_lane0()) trace_stamp(P, ti, 1);
-                merge_parts<D, G>(P, l);
-                if (is_ctl_lane0()) trace_stamp(P, ti, 2);
-            }
+            // (sequence 0 by the control wave, whose loads do not queue behind
+            // a ring; the others by a compute wave each, beside it)
+            const int wid = __builtin_amdgcn_readfirstlane(kl_tid() >> 6);
+            const int b = wid == kCtlWave ? 0 : wid + 1;
+            if (is_ctl_lane0()) trace_stamp(P, ti, 1);
+            if (b < P.B) merge_parts<D, G>(P, l, b);
+            if (is_ctl_lane0()) trace_stamp(P, ti, 2);
             lds_barrier();   // (as in owners_wait)
         };
         auto stage = [&](int b) {
             // (the control wave leaves the gather to the others, whose rings
             // are done by then; with P.multi all sequences' outputs, b K
             // floats apart)
-            if (!P.multi || b == 0)
-                ll_gather<8>(
-                    P, (P.multi ? P.B : 1) * K, tag, kl_tid(), kThreads,
-                    [&](int i) { return P.o_ll + (size_t)b * K + i; },
-                    [&](int i, unsigned v) { S.a[i] = __uint_as_float(v); });
+            auto word = [&](int i) { return P.o_ll + (size_t)b * K + i; };
+            auto put = [&](int i, unsigned v) { S.a[i] = __uint_as_float(v); };
+            if (!P.multi) ll_gather<8>(P, K, tag, kl_tid(), kThreads, word, put);
+            else if (b == 0) ll_gather<16>(P, P.B * K, tag, kl_tid(), kThreads, word, put);
             if (!P.multi || b == P.B - 1) lds_barrier();
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
         };
-        auto epi = [&](int b, int r, float y0, float y1) {
+        auto epi = [&](int b, int r, double y0, double y1) {
             const long long *x = own_x(P) + b * P.own_max + (r - R.first);
             put_x(P, b, r - R.first, R, x[0] + to_fix(y0), P.xa_ll, tag);
             put_x(P, b, r + 1 - R.first, R, x[1] + to_fix(y1), P.xa_ll, tag);
@@ -2691,7 +2794,7 @@ __device__ __forceinline__ void moe_gateup(const StepParams &P, const Lds &S, in
         const int r0 = min(P.gu_rg, ms.j * P.KTc * 2 * kTileK / kTileRows);
         const int r1 = min(P.gu_rg, (ms.j + 1) * P.KTc * 2 * kTileK / kTileRows);
         int a0, a1;
-        split_range(r1 - r0, P.Rc, ms.part, a0, a1);
+        split_rows(r1 - r0, P.Rc, ms.part, a0, a1);
         first = r0 + a0;
         count = a1 - a0;
     }
@@ -2701,7 +2804,7 @@ __device__ __forceinline__ void moe_gateup(const StepParams &P, const Lds &S, in
     if (!member) return;
     {
         int a0, a1;
-        split_range(P.down_rg, P.Rc, ms.part, a0, a1);
+        split_rows(P.down_rg, P.Rc, ms.part, a0, a1);
         if (count == 0 && a0 == a1) return;
     }
     if (is_ctl_lane0()) trace_stamp(P, ti, 1);
@@ -2729,7 +2832,7 @@ __device__ __forceinline__ void moe_down(const StepParams &P, const Lds &S, int 
     const MoeShare ms = moe_share(P);
     if (ms.slot >= P.topk || ms.j >= P.Sc) return;
     int a0, a1;
-    split_range(P.down_rg, P.Rc, ms.part, a0, a1);
+    split_rows(P.down_rg, P.Rc, ms.part, a0, a1);
     if (a0 == a1) return;
     const int kw = P.KTc * kTileK, c0 = ms.j * kw, nreal = max(0, min(kw, P.F - c0));
     const int nj = P.topk * P.Sc;
@@ -2822,7 +2925,7 @@ __device__ __forceinline__ void phase_gateup(KArg ka, int l, int gwait, int garr
         const int r0 = min(P.gu_rg, j * P.KTc * 2 * kTileK / kTileRows);
         const int r1 = min(P.gu_rg, (j + 1) * P.KTc * 2 * kTileK / kTileRows);
         int a0, a1;
-        split_range(r1 - r0, P.Rc, part, a0, a1);
+        split_rows(r1 - r0, P.Rc, part, a0, a1);
         first = r0 + a0;
         count = a1 - a0;
     }
@@ -2958,7 +3061,7 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
         };
         if (j < P.Sc) {
             int a0, a1;
-            split_range(P.down_rg, P.Rc, part, a0, a1);
+            split_rows(P.down_rg, P.Rc, part, a0, a1);
             const int kw = P.KTc * kTileK, c0 = j * kw, nreal = max(0, min(kw, P.F - c0));
             weight_phase<false>(
                 P, S, Wd + (size_t)j * P.down_rg * P.KTc * kTileBytes, P.KTc, a0, a1 - a0,
@@ -3026,7 +3129,7 @@ template <bool BAT>
 __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
     const StepParams P = load_params(ka);
     const Lds S = lds_layout(kl_smem, P);
-    const RgRange R = own_rgs(P.head_rg, P);
+    const RgRange R = own_rgs<BAT>(P.head_rg, P);
     const int V = P.V;
     // greedy sampling: this workgroup's best key per sequence (LDS atomics),
     // then one device-scope atomic per sequence into P.amax

@@ -1,0 +1,49 @@
+"""The attention's shares (equal runs of 4 KiB units of the batch's cached
+positions, or whole workgroups per sequence) and the hand-offs by row owner, at
+the places where they can go wrong: empty contexts, contexts around a unit
+(16 positions at head dimension 128, 32 at 64), fewer units than workgroups,
+more sequences than workgroups per KV head, sequences split over many shares,
+rows that do not divide the grid.  Against the oracle, every schedule bit for
+bit the same.  The bounds are those of the other parity tests."""
+import numpy as np
+import pytest
+
+from synth.workloads import TINY
+from tests.gpu_cases import MODES, Case, assert_bit_exact, check_against_oracle, say
+
+pytestmark = pytest.mark.gpu
+
+D64 = dict(TINY, n_layers=2)
+D128 = dict(TINY, n_layers=2, head_dim=128, hidden=264, ffn_dim=200)
+MHA = dict(TINY, n_layers=2, n_heads=64, n_kv_heads=64)      # 4 workgroups per KV head
+G8 = dict(D128, n_heads=16, n_kv_heads=2)
+
+CASES = [
+    ("d64 one", D64, [0]),
+    ("d64 units", D64, [31, 32, 33]),
+    ("d64 batched units", D64, [0, 1, 31, 32, 63, 64, 65, 500]),
+    ("d128 one", D128, [0]),
+    ("d128 units", D128, [15, 16, 17, 0]),
+    ("d128 long and short", D128, [3000, 1]),
+    ("d128 batched long and short", D128, [0, 2900, 16, 15, 1, 800]),
+    ("4 workgroups per head", MHA, [70, 0, 33]),
+    ("more sequences than workgroups per head", MHA, [5, 64, 0, 31, 200, 1, 32]),
+    ("2 workgroups per head", dict(MHA, n_heads=128, n_kv_heads=128), [40, 0, 100]),
+    ("8 heads per KV head", G8, [1000, 17]),
+    ("8 heads per KV head, batched", G8, [40, 0, 777, 16, 15]),
+    ("33 sequences", D128, [(37 * i) % 130 for i in range(33)]),
+]
+
+
+@pytest.mark.parametrize("name,cfg,filled", CASES, ids=[c[0] for c in CASES])
+def test_shares_of_the_attention(name, cfg, filled):
+    say(f"[shares] {name}: contexts {filled}")
+    cap = (max(filled) + 1 + 63) // 64 * 64
+    c = Case(cfg, len(filled), cap, np.asarray(filled, dtype=np.int32), seed=311 + len(filled))
+    ref = c.oracle_step(nthreads=8)
+    outs = [c.gpu_step(mode) for _, mode in MODES]
+    check_against_oracle(c, outs[1], ref)
+    for (what, _), o in zip(MODES, outs):
+        assert_bit_exact(o, outs[1], f"{what} vs looped")
+    assert c.model.device_error() == 0
+    c.model.close()
