@@ -133,13 +133,15 @@ typedef struct {
     int32_t n_workgroups;       /* persistent grid size used by every mode        */
     int32_t threads_per_group;
     int32_t lds_bytes;          /* dynamic LDS per workgroup                       */
-    int32_t attn_chunks_b1;     /* KV chunks per (sequence, KV head) at batch 1    */
+    int32_t attn_chunks_b1;     /* KV chunks per (sequence, KV head) at batch 1, at
+                                   most (a chunk has 4 KiB of keys or more)        */
     int32_t mfma_min_batch;     /* steps with batch >= this run the weight products
                                    on the matrix cores                             */
     int64_t arena_bytes;        /* packed weights + gains                          */
     int64_t scratch_bytes;      /* activations, partials, counters                 */
     int64_t noalloc_scratch_bytes;  /* scratch a kl_decode_step_noalloc call at
-                                       max_batch needs                             */
+                                       max_batch needs (besides a fixed reserve of
+                                       the library for hand-off words)             */
     int64_t noalloc_scratch_limit;  /* bytes of the static scratch                  */
 } kl_info;
 

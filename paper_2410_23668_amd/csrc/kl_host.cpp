@@ -469,7 +469,11 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     const int qkv_rows = nkv * S->qkv_rg * kTileRows;
     S->KSo = batched_k_slices(nkv, KTO, S->o_rg / 2, S->nwg);
     S->KSd = batched_k_slices(S->Sc, S->KTc, S->down_rg / 2, S->nwg);
-    S->KSg = folded_k_slices(KTH, 1, S->gu_rg / 2, S->nwg);
+    // (one slice where nearly every wave gets a block of its own: the SwiGLU is
+    // then applied in the epilogue, without partial sums, their fold and its
+    // grid barrier, at the price of streaming all of the activations)
+    S->KSg = 5LL * (S->gu_rg / 2) >= 4LL * kWaves * S->nwg
+                 ? 1 : folded_k_slices(KTH, 1, S->gu_rg / 2, S->nwg);
     S->KSq = folded_k_slices(KTH, 1, qkv_rows / 16, S->nwg);
 
     // step scratch for the largest batch, zeroed; the device error word

@@ -7,16 +7,15 @@
 //   looped     one cooperative launch for everything (kernel looping, Sec. 2
 //              and Sec. 3.2 of arXiv 2410.23668: the L chained layer calls
 //              become one call with an outer loop; kernel boundaries become
-//              device-scope grid barriers),
+//              tagged words and device-scope counters),
 //   per-layer  one launch per layer (the fused-layer kernel K0 of Sec. 2),
 //   per-op     one launch per phase.
 // The work partition depends only on StepParams::nwg, so every schedule
 // performs the same arithmetic in the same order: results are bit-identical.
 //
 // Pipelining across phases (the "pipelined outer loop" of Sec. 3.2): a phase
-// issues the first loads of its weight tiles before it waits for the barrier
-// that publishes its input activations, so HBM keeps streaming while the
-// grid synchronises.  Data that crosses workgroups (activations, partials,
+// issues the first loads of its weight tiles before it waits for its input
+// activations, so HBM keeps streaming while the grid synchronises.  Data that crosses workgroups (activations, partials,
 // the new KV slot) is written and read with device-coherent (agent-scope)
 // accesses, so a barrier needs no cache write-back or invalidation: only the
 // completion of the stores before the arrival.
@@ -783,7 +782,7 @@ __device__ __forceinline__ float *seq_sm(const StepParams &P, const Lds &S, int 
 // products over the 8 lanes of a row with DPP.  The slices are summed in wave
 // order through LDS, and epi(b, r, y_r, y_r+1) is called once per row pair.
 // Row groups are processed in batches of kRgBatch.  The first loads are
-// issued before wait() (the grid barrier that publishes the activations) and
+// issued before wait() (whatever precedes the staging of the activations) and
 // before stage(b) (which fills a with sequence b's activation vector); each
 // next batch's first loads are issued before the previous batch's reduction.
 // Tile loads in flight per wave (8 KiB; 16 MB over the chip, 2.5 us of HBM).
@@ -1226,13 +1225,15 @@ __device__ __forceinline__ GemmLds gemm_lds(char *smem) {
 // compiler wait for all outstanding loads before each of the loop's LDS
 // accesses (draining the ring once per pass), so the two modes are separate
 // instances and the streaming copies run in a loop of the control wave's own.
-// ready(c) (control wave) waits until chunk c's inputs are complete.
-template <bool resident, class Pre, class Ready, class Stage, class Epi>
+// ready(c) (control wave) waits until chunk c's inputs are complete;
+// all_ready() (control wave) runs once all of them are, before the first
+// products reach epi.
+template <bool resident, class Pre, class Ready, class AllReady, class Stage, class Epi>
 __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, int KT, int first,
                                                int count, int ktg, size_t gstride, int b0,
                                                int nb, const uint8_t *dummy, const GemmLds &L,
-                                               Pre &&pre, Ready &&ready, Stage &&stage,
-                                               Epi &&epi) {
+                                               Pre &&pre, Ready &&ready, AllReady &&all_ready,
+                                               Stage &&stage, Epi &&epi) {
     constexpr int U = kGemmDepth;
     constexpr int CT = kGemmChunkK / kTileK;   // k-tiles per chunk
     constexpr int MB = kGemmMaxBlk;
@@ -1303,6 +1304,7 @@ __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, in
     __syncthreads();   // (the buffers may still hold the previous sequence group)
     stage(0, L.act[0], true);
     if (resident && nkc > 1) stage(1, L.act[1], true);
+    if (resident && !compute) all_ready();
     ctl_copy_wait();
     __syncthreads();
 
@@ -1316,6 +1318,7 @@ __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, in
                     stage((f + 1) % nkc, L.act[(f + 1) & 1], false);
                     ctl_copy_wait();
                 }
+                if (f == nkc - 1) all_ready();
                 __syncthreads();
             }
             return;
@@ -1371,7 +1374,9 @@ __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, in
                     buf[s] = load_next();
                 }
             }
-            if (!resident) __syncthreads();   // chunk f consumed by every wave; f + 1 staged
+            // chunk f consumed by every wave; f + 1 staged (by the control wave,
+            // which waits for its copies; the ring stays in flight)
+            if (!resident) lds_barrier();
         }
         // the group's products: lane l holds rows 4 (l / 16) .. + 3 of the
         // block for sequence h 16 + l % 16
@@ -1395,31 +1400,38 @@ __device__ __forceinline__ void gemm_rows_mode(const uint8_t *__restrict__ W, in
     }
 }
 
-template <class Pre, class Ready, class Stage, class Epi>
+template <class Pre, class Ready, class AllReady, class Stage, class Epi>
 __device__ __forceinline__ void gemm_rows(const uint8_t *__restrict__ W, int KT, int first,
                                           int count, int ktg, size_t gstride, int b0, int nb,
                                           const uint8_t *dummy, const GemmLds &L, Pre &&pre,
-                                          Ready &&ready, Stage &&stage, Epi &&epi) {
+                                          Ready &&ready, AllReady &&all_ready, Stage &&stage,
+                                          Epi &&epi) {
     if (KT <= 2 * (kGemmChunkK / kTileK))
         gemm_rows_mode<true>(W, KT, first, count, ktg, gstride, b0, nb, dummy, L, pre, ready,
-                             stage, epi);
+                             all_ready, stage, epi);
     else
         gemm_rows_mode<false>(W, KT, first, count, ktg, gstride, b0, nb, dummy, L, pre, ready,
-                              stage, epi);
+                              all_ready, stage, epi);
 }
 
 
 // ---------------------------------------------------------------- phases
 //
 // Synchronization between the phases of a layer (l):
-//   grid barrier   after embed, oproj and down: the residual stream is
-//                  complete; qkv, gateup and head wait on it.
-//   cnt_qkv[g]     qkv -> attn: the workgroups of KV head g compute exactly
-//                  the q/k/v rows of that head, so the attention of head g
-//                  waits only for them (Sg arrivals per layer).
-//   cnt_gu[j]      gateup -> down: column block j of the FFN (Rc workgroups
-//                  compute its SwiGLU values; the same Rc workgroups then
-//                  apply the matching columns of the down projection).
+//   per-sequence path   tagged words throughout: q, k, v -> attention; the
+//                  attention's parts -> merge -> O projection; residual
+//                  (owners) -> gate/up; SwiGLU -> down; down's partial sums ->
+//                  owners -> residual -> next layer.  A writer of layer l + 1
+//                  has transitively waited for every reader of layer l's words,
+//                  because a workgroup reads words only in phases in which it
+//                  has rows.
+//   matrix-core path:
+//   grid barrier   after embed, the q/k/v product, attn, oproj, gateup and
+//                  down (and the SwiGLU fold, with several gate/up K slices).
+//   cnt_qkv[g]     qkv -> attn: KV head g's workgroups fold exactly the q/k/v
+//                  rows of that head, so the attention of head g waits only
+//                  for them (Sg arrivals per layer).
+//   norm_cnt[c]    RMSNorm slices -> products (norm_batched).
 // Local counters grow monotonically within a step (zeroed by the embedding
 // phase); their targets are (l + 1) times the arrivals per layer.
 // Every workgroup arrives on, and waits on, every grid barrier.
@@ -1444,14 +1456,18 @@ struct NoGroupDone {
 struct NoReady {   // weight_phase whose inputs are complete after prep()
     __device__ void operator()(int) const {}
 };
+struct NoAllReady {
+    __device__ void operator()(int, int) const {}
+};
 template <bool BAT, class Wait, class Prep, class Stage1, class StageB, class Epi,
-          class Done = NoGroupDone, class Ready = NoReady>
+          class Done = NoGroupDone, class Ready = NoReady, class AllReady = NoAllReady>
 __device__ __forceinline__ void weight_phase(const StepParams &P, const Lds &S,
                                              const uint8_t *W, int KT, int first, int count,
                                              Wait &&wait, Prep &&prep, Stage1 &&stage1,
                                              StageB &&stageb, Epi &&epi, int ktg = 0,
                                              size_t gstride = 0, Done done = Done(),
-                                             int astride = 0, Ready ready = Ready()) {
+                                             int astride = 0, Ready ready = Ready(),
+                                             AllReady all_ready = AllReady()) {
     if constexpr (!BAT) {
         if (P.multi)
             gemv_phase<true>(W, KT, first, count, P.B, S.a, S.red, P.dummy, wait, stage1, epi,
@@ -1470,7 +1486,7 @@ __device__ __forceinline__ void weight_phase(const StepParams &P, const Lds &S,
                           prep();
                       }
                   },
-                  [&](int c) { if (b0 == 0) ready(c); },
+                  [&](int c) { if (b0 == 0) ready(c); }, [&]() { all_ready(b0, nb); },
                   [&](int c, uint16_t *buf, bool all) { stageb(c, b0, nb, buf, all); }, epi);
         done(b0, nb);
     }
@@ -1974,12 +1990,15 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
 //           ones' (the other two quarters are never read).
 // All heads of the group share one pass over K and V, up to 8 of them at the
 // cost of one: per unit 32 fp32 products of 32 cycles against about 3000
-// cycles that its 8 KiB take from HBM (a SIMD's share).  The running maximum
+// cycles that its 8 KiB take from HBM (a SIMD's share): bound by HBM, 6.4 TB/s
+// at the 8B shape, batch 32.  The running maximum
 // moves only when a score passes it by 2^8 (the exponentials stay below 2^8
 // and exact sums are unaffected), so the loop has no cross-lane step.
-// 8B shape, batch 32, 4096 cached: see the phase table; 70B shape (8 heads a
-// group), batch 32: 166 us per layer with two head teams that each streamed
-// the chunk and multiplied on the vector units.
+// Measured, per layer: 70B shape (8 heads a group), batch 32, 4096 cached: 88
+// us for 537 MB, against 166 with two head teams that each streamed the chunk
+// and multiplied on the vector units; 8B shape, batch 16, 8192 cached: 95
+// against 132; batch 1, 4096 cached: 7.1 against 8.5, 32768 cached: 26 against
+// 35.
 template <int D> __device__ __forceinline__ constexpr int attn_unit() { return 2048 / D; }
 __device__ __forceinline__ int attn_units_of(int pnew, int up) { return pnew / up + 1; }
 
@@ -2881,7 +2900,8 @@ __device__ __forceinline__ void phase_gateup(KArg ka, int l, int gwait, int garr
         // few) x row groups, so a workgroup's load ring streams through all
         // of its blocks within few chunks; the gate and up partial sums go
         // to the slice's partial buffer, and the SwiGLU is applied when the
-        // down phase folds them (fold_swiglu)
+        // down phase folds them (fold_swiglu); with one slice (see the host's
+        // choice) it is applied in the epilogue
         const int KS = P.KSg, RB = P.nwg / KS, KT = P.Hp / kTileK, KTs = KT / KS;
         const int ks = blockIdx.x / RB, rb = blockIdx.x % RB, ksc = min(ks, KS - 1);
         int a0 = 0, a1 = 0;
@@ -2902,12 +2922,28 @@ __device__ __forceinline__ void phase_gateup(KArg ka, int l, int gwait, int garr
                 stage_bf16_chunk(P.act + col0, P.act_lo + col0, P.Hp, KTs * kTileK, c, b0, nb, buf, all);
             },
             [&](int b, int r, float gt, float up) {
-                st_dev(part + (size_t)b * grow + r, gt);
-                st_dev(part + (size_t)b * grow + r + 1, up);
+                if (KS > 1) {
+                    st_dev(part + (size_t)b * grow + r, gt);
+                    st_dev(part + (size_t)b * grow + r + 1, up);
+                    return;
+                }
+                // one slice: the sums are complete, and the SwiGLU is applied here
+                const float rs = rms_of(P, S, b), g = gt * rs;
+                uint16_t hi, lo;
+                split_bf16(g / (1.0f + expf(-g)) * (up * rs), hi, lo);
+                const size_t o = (size_t)b * P.Fp + (r >> 1);
+                st_dev_u16(P.actm + o, hi);
+                st_dev_u16(P.actm_lo + o, lo);
             },
-            KT, 0, NoGroupDone(), 0, [&](int c) {
+            KT, 0, NoGroupDone(), 0,
+            [&](int c) {
                 const int sl = col0 / kGemmChunkK + c;
                 norm_wait(P, 2 * l + 1, sl, sl + 1);
+            },
+            // (the sequences' RMSNorm scales for the epilogue: every slice is complete)
+            [&](int b0, int nb) {
+                const int b = b0 + (int)(kl_tid() & 63);
+                if (KS == 1 && (int)(kl_tid() & 63) < nb && b < kRScaleTable) S.red[b] = rms_r(P, b);
             });
         if (garrive >= 0) bar_arrive(P, garrive, ti);
         return;
@@ -3035,7 +3071,7 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
             P, S, Wd + (size_t)ksc * gps * P.down_rg * P.KTc * kTileBytes, gps * P.KTc, a0,
             a1 - a0, [&]() { if (gwait >= 0) bar_wait(P, gwait, ti); },
             [&]() {
-                fold_swiglu(P, S, xbar);
+                if (xbar >= 0) fold_swiglu(P, S, xbar);
                 if (is_ctl_lane0()) trace_stamp(P, ti, 3);
             },
             [&](int) {},
@@ -3261,9 +3297,10 @@ __global__ __launch_bounds__(kThreads) void kl_step_kernel(StepParams P, int l0,
             phase_gateup<BAT>(ka, l, w, a, ti++);
         }
         if (phases & kPhDown) {
-            // (batched: the SwiGLU fold of the gate/up partials ends with a
-            // grid barrier of its own)
-            const int w = BAT && has_gu ? gw() : -1, x = xb();
+            // (batched: the SwiGLU fold of the gate/up partials, with several K
+            // slices, ends with a grid barrier of its own)
+            const int w = BAT && has_gu ? gw() : -1;
+            const int x = BAT && load_params(ka).KSg > 1 ? na++ : -1;
             phase_down<BAT>(ka, l, w, x, BAT ? ga((has_qkv && l + 1 < l1) || has_head) : -1, ti++);
         }
     }

@@ -14,7 +14,8 @@
 // Tagged hand-offs.  A value crossing workgroups travels in one 8-byte word
 // with the tag of the step and layer that wrote it (value in the low 32
 // bits, tag in the high 32 bits); a reader accepts a word whose tag is the
-// current one.  Step s uses tags epoch_s .. epoch_s + L - 1 for its L layers;
+// current one.  Step s uses tags epoch_s .. epoch_s + L (layer l's words and its
+// input residual; the head's input): L + 1 of them;
 // the next step's range starts right after, and restarts at 1 before it
 // would reach 2^32, so no step's range contains 0, the tag of cleared memory.
 // (The epoch lives in device memory: read at launch start, advanced by the
@@ -66,7 +67,7 @@ KL_HD inline bool ll_current(unsigned long long word, unsigned tag) {
 KL_HD inline unsigned ll_value(unsigned long long word) { return (unsigned)word; }
 
 // The first tag of the step after one whose range started at 'prev', for a
-// model of n_layers layers (0 < n_layers < 2^30).
+// step of n_layers tags (0 < n_layers < 2^30).
 KL_HD inline unsigned ll_next_epoch(unsigned prev, int n_layers) {
     const unsigned L = (unsigned)n_layers;
     if (prev == 0 || prev > 0xFFFFFFFFu - 2u * L) return 1u;   // restart before wrapping

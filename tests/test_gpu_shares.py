@@ -47,3 +47,20 @@ def test_shares_of_the_attention(name, cfg, filled):
         assert_bit_exact(o, outs[1], f"{what} vs looped")
     assert c.model.device_error() == 0
     c.model.close()
+
+
+@pytest.mark.parametrize("hidden,batch", [(256, 6), (1032, 5), (520, 37)])
+def test_swiglu_in_the_gate_up_epilogue(hidden, batch):
+    """An FFN wide enough for one K slice of the batched gate/up product (the
+    SwiGLU is applied to its products directly): activations resident in LDS
+    (256, 520 columns) and streamed (1032), a second group of sequences (37)."""
+    cfg = dict(TINY, n_layers=2, hidden=hidden, ffn_dim=13320)
+    say(f"[swiglu epilogue] hidden {hidden} batch {batch}")
+    filled = (np.arange(batch, dtype=np.int32) * 29 + 3) % 90
+    c = Case(cfg, batch, 128, filled, seed=411 + batch)
+    ref = c.oracle_step(nthreads=8, sample=[0, batch // 2, batch - 1])
+    outs = [c.gpu_step(mode) for _, mode in MODES]
+    check_against_oracle(c, outs[1], ref, only=[0, batch // 2, batch - 1])
+    for (what, _), o in zip(MODES, outs):
+        assert_bit_exact(o, outs[1], f"{what} vs looped")
+    c.model.close()
