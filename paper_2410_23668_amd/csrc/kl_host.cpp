@@ -50,6 +50,7 @@ struct kl_state {
     int lds_red_seq;                  // the GEMV partial sums on the per-sequence path
     int own_max;                      // residual rows a workgroup owns, at most
     bool multi_ok;                    // up to kMultiSeq sequences share a GEMV pass
+    int lds_mm;                       // its slots on the matrix cores (0: on the vector units)
     int batched_from;                 // first batch of the matrix-core path
 };
 
@@ -173,10 +174,16 @@ void lds_layout_for(kl_state &s) {
     // mixture of experts: up to kMfmaBatch - 1, as its routing needs).  The
     // matrix-core path's area (and its partial sums after it) may overlap
     // the per-sequence path's partial sums: a launch runs one of the two.
-    const auto layout = [&](bool mu) {
+    // On the matrix cores a sequence's vector is three bf16 terms: where that
+    // and the weight re-layout slots fit.
+    const int mm = round64(std::max({multi, 3 * kMultiSeq * (s.Hp + 8) / 2 + kMultiSeq * d,
+                                     3 * kMultiSeq * (s.Ap + 8) / 2,
+                                     3 * kMultiSeq * (s.KTc * kTileK + 8) / 2}));
+    const auto layout = [&](bool mu, bool use_mm) {
         s.multi_ok = mu;
+        s.lds_mm = use_mm ? mm : 0;
         s.batched_from = c.n_experts > 1 ? kMfmaBatch : (mu ? kMultiSeq + 1 : kBatchedFrom);
-        const int seq_a = mu ? multi : one;
+        const int seq_a = use_mm ? mm + kWaves * 2048 / 4 : (mu ? multi : one);
         const int seq_end = seq_a + (mu ? kMultiSeq : 1) * rs;
         const bool bat = c.max_batch >= s.batched_from;
         const int bat_a = bat ? round64(std::max(seq_a, kGemmLdsBytes / 4)) : seq_a;
@@ -192,8 +199,10 @@ void lds_layout_for(kl_state &s) {
         s.lds_bytes = (s.lds_bar + 2 * kBarGroups + 4 + 2 * kMfmaBatch + 2 * kGemmBatch +
                        4 * kMfmaBatch + 8 + 2 * seqs * s.own_max) * (int)sizeof(float);
     };
-    layout(c.max_batch >= 2);
-    if (s.multi_ok && s.lds_bytes > 160 * 1024 - 256) layout(false);
+    const int most = 160 * 1024 - 256;
+    layout(c.max_batch >= 2, c.max_batch >= 2);
+    if (s.lds_mm && s.lds_bytes > most) layout(true, false);
+    if (s.multi_ok && s.lds_bytes > most) layout(false, false);
 }
 
 // Step scratch for a batch of B sequences (byte offsets from its base; every
@@ -684,6 +693,8 @@ static StepParams step_params(const kl_state &st, uint8_t *base, const ScratchPl
     // between the two paths)
     P.multi = !P.batched && batch >= 2 && batch <= kMultiSeq && st.multi_ok ? 1 : 0;
     P.lds_red = P.batched ? st.lds_red : st.lds_red_seq;
+    if (P.multi && st.lds_mm) P.multi = 2;
+    P.lds_mm = st.lds_mm;
     return P;
 }
 

@@ -24,14 +24,15 @@ constexpr int kRgBatch = 16;              // row groups reduced per LDS round
 // weight rows in blocks of 16.
 constexpr int kMfmaBatch = 8;
 // Up to kMultiSeq sequences share one pass of the GEMV engine: each weight
-// tile is applied to every staged vector, so the weights stream once (8B
-// shape, 4096 cached positions: 3.06, 3.52, 3.91, 4.35 ms at batch 1-4,
-// against 5.0 ms on the matrix-core path).  Dense models take the
-// matrix-core path from batch kMultiSeq + 1 on, or from kBatchedFrom where
-// the LDS cannot hold the shared pass's vectors beside the matrix-core
-// engine's area (one sequence per pass: 5.61 ms at batch 2).  A mixture of
-// experts keeps the GEMV path below kMfmaBatch (its experts are chosen per
-// token on that path).
+// tile is applied to every staged vector, so the weights stream once.  8
+// layers of the 8B shape, 4096 cached positions, batch 4: 1162 us with the
+// pass on the matrix cores, 1195 on the vector units.  Against the matrix-core
+// engine the vector-unit pass took 4.35 ms to 5.0 for all 32 layers, both
+// before the residual rows had owners.  Dense models take that engine from
+// batch kMultiSeq + 1 on, or from kBatchedFrom where the LDS cannot hold the
+// shared pass's vectors beside its area (one sequence per pass: 5.61 ms at
+// batch 2).  A mixture of experts keeps the GEMV path below kMfmaBatch (its
+// experts are chosen per token on that path).
 constexpr int kMultiSeq = 4;
 constexpr int kBatchedFrom = 2;
 constexpr int kGemmBatch = 32;
@@ -142,7 +143,8 @@ struct StepParams {
     int lds_red, lds_sm, lds_bar;   // dynamic LDS layout (float offsets)
     int batched;               // this step runs the matrix-core path (set by the host)
     int multi;                 // per-sequence path: the B <= kMultiSeq sequences share each
-                               // GEMV pass (set by the host)
+                               // GEMV pass (1), on the matrix cores (2) (set by the host)
+    int lds_mm;                // multi = 2: the waves' weight re-layout slots (float offset)
     unsigned long long *trace; // optional phase timestamps (see kl_set_trace), or null
     int trace_max;             // phases recorded per launch
 };

@@ -36,6 +36,8 @@
 namespace kl {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- helpers
 
@@ -555,6 +557,25 @@ __device__ __forceinline__ Lds lds_layout(char *smem, const StepParams &P) {
     s.bar = reinterpret_cast<unsigned long long *>(f + P.lds_bar);
     return s;
 }
+__device__ __forceinline__ uint8_t *mm_slots(const StepParams &P, const Lds &S) {
+    return P.multi == 2 ? reinterpret_cast<uint8_t *>(S.a + P.lds_mm) : nullptr;
+}
+// P.multi = 2: the pass runs on the matrix cores; a staged vector is three
+// bf16 terms (all 24 bits), column 4 t + b of the B operand being term t of
+// sequence b, in rows of mm_stride(K) elements.
+constexpr int kMmCols = 3 * kMultiSeq;
+__device__ __forceinline__ constexpr int mm_stride(int K) { return K + 8; }   // (bank spread)
+__device__ __forceinline__ uint16_t *mm_act(const Lds &S) {
+    return reinterpret_cast<uint16_t *>(S.a);
+}
+__device__ __forceinline__ void mm_put(uint16_t *x, int stride, int b, int i, float v) {
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        const uint16_t h = f2bf(v);
+        x[(4 * t + b) * stride + i] = h;
+        v -= bf2f(h);
+    }
+}
 // Per-sequence path: with P.multi the B sequences share each GEMV pass and
 // sequence b's staged vector sits b stride floats into the activation area
 // (its wave sums of squares b kSmSeq floats into sm); otherwise every
@@ -566,6 +587,7 @@ __device__ __forceinline__ float *seq_sm(const StepParams &P, const Lds &S, int 
 // The Q/K/V phase's staged RoPE row (cos, sin) of sequence b: after the
 // activation vectors.
 __device__ __forceinline__ float *rope_row(const StepParams &P, const Lds &S, int b) {
+    if (P.multi == 2) return S.a + kMmCols * mm_stride(P.Hp) / 2 + b * P.d;
     return S.a + (P.multi ? kMultiSeq * P.Hp + b * P.d : 2 * P.Hp);
 }
 
@@ -746,7 +768,12 @@ __device__ __forceinline__ void stage_rms_multi(const StepParams &P,
                     const int i = i0 + k * kThreads;
                     const float x = i < n ? __uint_as_float(ll_value(v[bb][k])) : 0.f;
                     ss[bb] = fmaf(x, x, ss[bb]);
-                    if (i < npad) a[bb * astride + i] = x * gv[k];
+                    if (i < npad) {
+                        if (P.multi == 2)
+                            mm_put(reinterpret_cast<uint16_t *>(a), mm_stride(npad), bb, i, x * gv[k]);
+                        else
+                            a[bb * astride + i] = x * gv[k];
+                    }
                 }
                 if (first && (int)kl_tid() < ne) edst(bb)[kl_tid()] = ev[bb];
             }
@@ -1134,6 +1161,138 @@ __device__ __forceinline__ void gemv_rows_multi(const uint8_t *__restrict__ W, i
     }
 }
 
+// The same on the matrix cores (P.multi = 2): row groups in pairs (16-row
+// blocks), each tile pair re-laid out through a per-wave LDS slot as in the
+// batched engine, one product per 32 columns for all sequences' three terms.
+// Two accumulators (the halves of a tile) keep the sums short.  The vector-unit
+// form is bound by its 8 multiplies per tile and sequence and the reads of the
+// vectors; here the cost does not grow with the sequences.  8 layers of the 8B
+// shape, batch 3 1067 -> 1043 us, batch 4 1195 -> 1162; the error against 64
+// bits is 0.8 times the vector-unit form's.  (P.multi = 1 stays where three
+// terms of the vectors do not fit in LDS, as at the 70B shape.)
+template <bool RowSplit, int KTG, class Wait, class Stage, class Epi>
+__device__ __forceinline__ void gemv_rows_mm(const uint8_t *__restrict__ W, int KT, int first,
+                                             int count, int B, const uint16_t *X, int xs,
+                                             uint8_t *slots, float *red, const uint8_t *dummy,
+                                             Wait &&wait, Stage &&stage, Epi &&epi, int gstride) {
+    constexpr int U = kGemvDepth, NP = 2;
+    constexpr int BATCH = RowSplit ? kWaves * kRgBatch : kRgBatch;
+    const int wid = __builtin_amdgcn_readfirstlane(kl_tid() >> 6);
+    const int lane = kl_tid() & 63;
+    const int kt0 = RowSplit ? 0 : (wid * KT) / kWaves;
+    const int nk = RowSplit ? KT : ((wid + 1) * KT) / kWaves - kt0;
+    const int ktr = KTG ? KTG : KT, rsz = (RowSplit ? kWaves : 1) * ktr;
+    const int kover = KTG ? gstride - ktr + 1 : 1;
+    const uint8_t *base = W + (size_t)lane * 16;
+    uint8_t *ws = slots + min(wid, kWaves - 1) * 2048;
+    const uint16_t *xb = X + min(lane & 15, kMmCols - 1) * xs + 8 * (lane >> 4);
+    u32x4 buf[U];
+    int n = 0, mine = 0, tile0 = 0, gi = 0, lk = 0, lt = 0, kr = 0;
+    auto load_h = [&](int h) {
+        const bool real = gi + h < mine;
+        const int t = __builtin_amdgcn_readfirstlane(tile0 + (gi + h) * rsz + lt);
+        const u32x4 v = ld_stream_16B(real ? base + (size_t)t * kTileBytes : dummy);
+        if (h == NP - 1) {
+            const bool wrap = lk + 1 == nk, over = KTG && kr + 1 == ktr;
+            lk = wrap ? 0 : lk + 1;
+            lt = wrap ? 0 : lt + (over ? kover : 1);
+            kr = wrap ? (KTG ? kt0 % ktr : 0) : (over ? 0 : kr + 1);
+            gi = wrap ? gi + NP : gi;
+        }
+        return v;
+    };
+    auto start = [&](int ib) {
+        const int nb = min(BATCH, count - ib);
+        mine = RowSplit ? (nb > wid ? (nb - wid + kWaves - 1) / kWaves : 0) : nb;
+        n = nk * NP * ((mine + NP - 1) / NP);
+        tile0 = (first + ib + (RowSplit ? wid : 0)) * ktr +
+                (KTG ? (kt0 / ktr) * gstride + kt0 % ktr : kt0);
+        gi = lk = lt = 0;
+        kr = KTG ? kt0 % ktr : 0;
+#pragma unroll
+        for (int s = 0; s < U; ++s) buf[s] = load_h(s % NP);
+    };
+    const bool compute = wid < kWaves;
+    const bool has_rows = count > 0;
+    if (has_rows && compute) start(0);
+    wait();
+    if (!has_rows) return;
+    for (int ib = 0; ib < count; ib += BATCH) {
+        if (ib > 0 && compute) start(ib);
+        if (ib == 0)
+            for (int bb = 0; bb < B; ++bb) stage(bb);
+        const int nrg = min(BATCH, count - ib);
+        int cr = 0, ck = 0, cg = 0;
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        f32x4 tot = {0.f, 0.f, 0.f, 0.f};
+        if (compute)
+        for (int i0 = 0; i0 < n; i0 += U) {
+#pragma unroll
+            for (int s = 0; s < U; s += NP) {
+                if (i0 + s < n) {
+                    const int wr = lane >> 3, wc = lane & 7;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        *reinterpret_cast<u32x4 *>(
+                            ws + t * 1024 + (wr * 8 + (wc ^ ((wr + t) & 7))) * 16) = buf[s + t];
+#pragma unroll
+                    for (int st = 0; st < 2; ++st) {
+                        const int r16 = lane & 15, ko = 4 * st + (lane >> 4);
+                        const int at = r16 >> 3, ar = r16 & 7;
+                        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(
+                            ws + at * 1024 + (ar * 8 + (ko ^ ((ar + at) & 7))) * 16);
+                        const bf16x8 x = *reinterpret_cast<const bf16x8 *>(
+                            xb + (kt0 + ck) * kTileK + 32 * st);
+                        acc[st] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x, acc[st], 0, 0, 0);
+                    }
+                    if (KTG && ++cg == KTG) {
+                        tot += acc[0] + acc[1];
+                        acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        cg = 0;
+                    }
+                    if (++ck == nk) {   // the pair's row groups are done
+                        const f32x4 y = tot + (acc[0] + acc[1]);
+                        const int b = lane & 15;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            // the terms: columns b, b + 4, b + 8
+                            const float t = y[v] + (dpp<0x12C>(y[v]) + dpp<0x128>(y[v]));
+                            const int r16 = 4 * (lane >> 4) + v, c = cr + (r16 >> 3);
+                            const int ri = (RowSplit ? (wid + c * kWaves) * kTileRows
+                                                     : (wid * kRgBatch + c) * kTileRows) + (r16 & 7);
+                            if (b < B && c < mine) red[b * kRedStride + ri] = t;
+                        }
+                        acc[0] = acc[1] = tot = f32x4{0.f, 0.f, 0.f, 0.f};
+                        ck = cg = 0;
+                        cr += NP;
+                    }
+                }
+#pragma unroll
+                for (int h = 0; h < NP; ++h) buf[s + h] = load_h(h);
+            }
+        }
+        lds_barrier();
+        for (int t = kl_tid(); t < B * nrg * (kTileRows / 2); t += kThreads) {
+            const int bb = t / (nrg * (kTileRows / 2)), tt = t - bb * (nrg * (kTileRows / 2));
+            const int rgi = tt / (kTileRows / 2), pr = (tt % (kTileRows / 2)) * 2;
+            const float *rd = red + bb * kRedStride;
+            double y0 = 0, y1 = 0;
+            if (RowSplit) {
+                y0 = rd[rgi * kTileRows + pr];
+                y1 = rd[rgi * kTileRows + pr + 1];
+            } else {
+                for (int w = 0; w < kWaves; ++w) {
+                    if (((w + 1) * KT) / kWaves == (w * KT) / kWaves) continue;   // empty slice
+                    y0 += rd[(w * kRgBatch + rgi) * kTileRows + pr];
+                    y1 += rd[(w * kRgBatch + rgi) * kTileRows + pr + 1];
+                }
+            }
+            epi(bb, (first + ib + rgi) * kTileRows + pr, y0, y1);
+        }
+        lds_barrier();
+    }
+}
+
 // Row groups are shared split-K when they are long enough for every wave to
 // hold two or more tiles, else row-split.  Multi: the B sequences share each
 // pass (gemv_rows_multi).
@@ -1142,8 +1301,18 @@ __device__ __forceinline__ void gemv_phase(const uint8_t *__restrict__ W, int KT
                                            int count, int B, const float *__restrict__ a,
                                            float *red, const uint8_t *dummy, Wait &&wait,
                                            Stage &&stage, Epi &&epi, int astride = 0,
-                                           int gstride = 0) {
+                                           int gstride = 0, uint8_t *mm_slots = nullptr) {
     if constexpr (Multi) {
+        if (mm_slots) {
+            const uint16_t *X = reinterpret_cast<const uint16_t *>(a);
+            if (KT >= 2 * kWaves)
+                gemv_rows_mm<false, KTG>(W, KT, first, count, B, X, mm_stride(astride), mm_slots, red,
+                                         dummy, wait, stage, epi, gstride);
+            else
+                gemv_rows_mm<true, KTG>(W, KT, first, count, B, X, mm_stride(astride), mm_slots, red,
+                                        dummy, wait, stage, epi, gstride);
+            return;
+        }
         if (KT >= 2 * kWaves)
             gemv_rows_multi<false, KTG>(W, KT, first, count, B, a, astride, red, dummy, wait, stage,
                                         epi, gstride);
@@ -1173,8 +1342,6 @@ __device__ __forceinline__ void gemv_phase(const uint8_t *__restrict__ W, int KT
 // buffers).  X is staged in LDS in chunks of kGemmChunkK columns (kActStride
 // bf16 per row; the hi rows, then kLoOff elements further the lo rows), in
 // two chunk buffers: stage(c, buf) fills chunk c.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kLoOff = kGemmBatch * kActStride;   // elements from a chunk's hi rows to its lo rows
 
@@ -1471,7 +1638,7 @@ __device__ __forceinline__ void weight_phase(const StepParams &P, const Lds &S,
     if constexpr (!BAT) {
         if (P.multi)
             gemv_phase<true>(W, KT, first, count, P.B, S.a, S.red, P.dummy, wait, stage1, epi,
-                             astride);
+                             astride, 0, mm_slots(P, S));
         else
             gemv_phase(W, KT, first, count, P.B, S.a, S.red, P.dummy, wait, stage1, epi);
         return;
@@ -2700,7 +2867,13 @@ __device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int garri
             // are done by then; with P.multi all sequences' outputs, b K
             // floats apart)
             auto word = [&](int i) { return P.o_ll + (size_t)b * K + i; };
-            auto put = [&](int i, unsigned v) { S.a[i] = __uint_as_float(v); };
+            auto put = [&](int i, unsigned v) {
+                if (P.multi == 2) {
+                    const int q = (i >= K) + (i >= 2 * K) + (i >= 3 * K);
+                    mm_put(mm_act(S), mm_stride(K), q, i - q * K, __uint_as_float(v));
+                }
+                else S.a[i] = __uint_as_float(v);
+            };
             if (!P.multi) ll_gather<8>(P, K, tag, kl_tid(), kThreads, word, put);
             else if (b == 0) ll_gather<16>(P, P.B * K, tag, kl_tid(), kThreads, word, put);
             if (!P.multi || b == P.B - 1) lds_barrier();
@@ -2713,7 +2886,7 @@ __device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int garri
         };
         if (P.multi)
             gemv_phase<true, KTq>(Wo, KT, R.first / kTileRows, R.count / kTileRows, P.B, S.a, S.red,
-                                  P.dummy, wait, stage, epi, K, P.o_rg * KTq);
+                                  P.dummy, wait, stage, epi, K, P.o_rg * KTq, mm_slots(P, S));
         else
             gemv_phase<false, KTq>(Wo, KT, R.first / kTileRows, R.count / kTileRows, P.B, S.a, S.red,
                                    P.dummy, wait, stage, epi, 0, P.o_rg * KTq);
@@ -3120,11 +3293,17 @@ __device__ __forceinline__ void phase_down(KArg ka, int l, int gwait, int xbar, 
                                 },
                                 [&](int i, unsigned v) {
                                     const int bb = i / nreal;
-                                    S.a[bb * kw + (i - bb * nreal)] = __uint_as_float(v);
+                                    if (P.multi == 2)
+                                        mm_put(mm_act(S), mm_stride(kw), bb, i - bb * nreal,
+                                               __uint_as_float(v));
+                                    else
+                                        S.a[bb * kw + (i - bb * nreal)] = __uint_as_float(v);
                                 });
                         for (int i = kl_tid(); i < P.B * (kw - nreal); i += kThreads) {
                             const int bb = i / (kw - nreal);
-                            S.a[bb * kw + nreal + (i - bb * (kw - nreal))] = 0.f;
+                            const int k = nreal + (i - bb * (kw - nreal));
+                            if (P.multi == 2) mm_put(mm_act(S), mm_stride(kw), bb, k, 0.f);
+                            else S.a[bb * kw + k] = 0.f;
                         }
                     } else {
                         if ((kl_tid() >> 6) == kCtlWave)

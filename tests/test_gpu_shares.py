@@ -8,6 +8,7 @@ bit the same.  The bounds are those of the other parity tests."""
 import numpy as np
 import pytest
 
+from paper_2410_23668_amd import binding as kb
 from synth.workloads import TINY
 from tests.gpu_cases import MODES, Case, assert_bit_exact, check_against_oracle, say
 
@@ -63,4 +64,31 @@ def test_swiglu_in_the_gate_up_epilogue(hidden, batch):
     check_against_oracle(c, outs[1], ref, only=[0, batch // 2, batch - 1])
     for (what, _), o in zip(MODES, outs):
         assert_bit_exact(o, outs[1], f"{what} vs looped")
+    c.model.close()
+
+
+@pytest.mark.parametrize("over,batch", [
+    (dict(hidden=64, ffn_dim=72), 2),                  # one tile of columns: whole row groups per wave
+    (dict(hidden=264, ffn_dim=200), 4),
+    (dict(hidden=1032, ffn_dim=3000), 3),              # column slices of uneven length, a padded one
+    (dict(hidden=1040, ffn_dim=1096, head_dim=128), 2),
+    (dict(hidden=520, ffn_dim=264, n_experts=4, top_k=2), 3),
+    (dict(hidden=6152, ffn_dim=520), 3),               # too wide for LDS: the vector-unit form
+], ids=str)
+def test_sequences_sharing_a_pass(over, batch):
+    """Batches of 2 to 4 take each weight pass together: on the matrix cores
+    (three bf16 terms of each vector) where LDS holds the terms, else on the
+    vector units."""
+    cfg = dict(TINY, n_layers=2, **over)
+    say(f"[shared pass] {over} batch {batch}")
+    filled = (np.arange(batch, dtype=np.int32) * 29 + 3) % 90
+    c = Case(cfg, batch, 128, filled, seed=511 + batch)
+    ref = c.oracle_step(nthreads=8)
+    # (a mixture of experts has no per-op schedule)
+    modes = [m for m in MODES if not ("n_experts" in over and m[1] == kb.KL_MODE_PER_OP)]
+    outs = {what: c.gpu_step(mode) for what, mode in modes}
+    check_against_oracle(c, outs["looped"], ref)
+    for what, o in outs.items():
+        assert_bit_exact(o, outs["looped"], f"{what} vs looped")
+    assert c.model.device_error() == 0
     c.model.close()
