@@ -2144,7 +2144,8 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
 // between lanes:
 //   scores  v_mfma_f32_16x16x32_bf16, A = 16 key rows (16 bytes of a row per
 //           lane), B = the queries (scaled, log2 units) as two bf16 terms
-//           (three on the per-sequence path: their 24 bits); column n is
+//           (three on the per-sequence path and at D = 64: their 24 bits,
+//           as fp32 queries on the vector units have); column n is
 //           head n & 7 (zero past G).  Tile row 4 k + v is the
 //           position that the value product below wants from lane (k, n) in
 //           its register v.
@@ -2256,7 +2257,7 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
     // two sets, alternating by segment: while a segment's units run, the
     // control wave merges the waves of the one before and stages the queries
     // of the one after
-    constexpr int NT = LL ? 3 : 2, QS = D + 8;      // query terms; bf16 per row (banks)
+    constexpr int NT = LL || D == 64 ? 3 : 2, QS = D + 8;      // query terms; bf16 per row (banks)
     uint16_t *const qs0 = reinterpret_cast<uint16_t *>(S.attn);   // [2][NT][G][QS] scaled queries
     float *const wm0 = S.attn + 2 * NT * G * QS / 2;   // [2][kWaves][G] wave maxima (log2 units)
     float *const wl0 = wm0 + 2 * kWaves * G;        // [2][kWaves][G] wave sums
@@ -2443,10 +2444,7 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
                                 __builtin_bit_cast(bf16x8, kq[2 * y + (x & 1)]),
                                 x < 4 ? qb[x & 3] : query(x, lane), c, 0, 0, 0);
                         };
-                        if constexpr (LL)
-                            t[y] = (dot(0, z4) + dot(1, z4)) + dot(5, dot(4, dot(3, dot(2, z4))));
-                        else
-                            t[y] = dot(3, dot(2, dot(1, dot(0, z4))));
+                        t[y] = (dot(0, z4) + dot(1, z4)) + dot(5, dot(4, dot(3, dot(2, z4))));
                     }
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
