@@ -1717,15 +1717,15 @@ __device__ __forceinline__ void norm_batched(const StepParams &P, const Lds &S,
     }
 }
 
-// The control wave waits until the slices [c0, c1) of RMSNorm step inst
-// (numbered within the step: 2 l for layer l's attention norm, 2 l + 1 for
-// its FFN norm, 2 L for the final norm) are complete.  No workgroup barrier:
+// The control wave waits until the slices R of RMSNorm step inst (numbered
+// within the step: 2 l for layer l's attention norm, 2 l + 1 for its FFN norm,
+// 2 L for the final norm) are complete.  No workgroup barrier:
 // the control wave then copies those slices (the other waves meet it at the
 // barrier after the copies).
-__device__ __forceinline__ void norm_wait(const StepParams &P, int inst, int c0, int c1) {
+__device__ __forceinline__ void norm_wait(const StepParams &P, int inst, SliceRange R) {
     if (is_ctl_lane0()) {
         const unsigned target = (unsigned)(inst + 1) * (unsigned)P.B;
-        for (int c = c0; c < c1; ++c)
+        for (int c = R.first; c < R.end; ++c)
             spin_until(P, [&]() {
                 return (int)(__hip_atomic_load(norm_cnt(P) + kNormCntStride * c, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT) - target) >= 0;
@@ -2063,10 +2063,8 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
                 st_dev(pp + (size_t)b * rows + r, y0);
                 st_dev(pp + (size_t)b * rows + r + 1, y1);
             },
-            KT, 0, NoGroupDone(), 0, [&](int c) {
-                const int sl = col0 / kGemmChunkK + c;
-                norm_wait(P, 2 * l, sl, sl + 1);
-            });
+            KT, 0, NoGroupDone(), 0,
+            [&](int c) { norm_wait(P, 2 * l, staged_slices(col0, KTs * kTileK, c, kGemmChunkK)); });
         bar_arrive(P, qbar, -1);
         bar_wait(P, qbar, -1);
         if (member) {
@@ -3108,8 +3106,7 @@ __device__ __forceinline__ void phase_gateup(KArg ka, int l, int gwait, int garr
             },
             KT, 0, NoGroupDone(), 0,
             [&](int c) {
-                const int sl = col0 / kGemmChunkK + c;
-                norm_wait(P, 2 * l + 1, sl, sl + 1);
+                norm_wait(P, 2 * l + 1, staged_slices(col0, KTs * kTileK, c, kGemmChunkK));
             },
             // (the sequences' RMSNorm scales for the epilogue: every slice is complete)
             [&](int b0, int nb) {
@@ -3371,7 +3368,7 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
             // (folds the last down projection's partials, x: xf2 -> xf), and
             // the sequences' RMSNorm scales for the epilogue
             norm_batched(P, S, P.final_norm, P.xf2, P.xf, P.KSd);
-            norm_wait(P, 2 * P.L, 0, (P.Hp + kGemmChunkK - 1) / kGemmChunkK);
+            norm_wait(P, 2 * P.L, SliceRange{0, (P.Hp + kGemmChunkK - 1) / kGemmChunkK});
             __syncthreads();
             rms_table(P, S);
             if (is_ctl_lane0()) trace_stamp(P, ti, 3);

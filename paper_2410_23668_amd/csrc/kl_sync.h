@@ -20,6 +20,12 @@
 // would reach 2^32, so no step's range contains 0, the tag of cleared memory.
 // (The epoch lives in device memory: read at launch start, advanced by the
 // step's last phase.)
+//
+// RMSNorm slices (matrix-core path).  A normalised row is handed over in slices
+// of 'chunk' columns, each with a counter; a product stages its K range in
+// chunks of as many columns, counted from the range's own first column, which
+// need not be a multiple of them: a chunk may lie in two slices, and waits for
+// both.
 #pragma once
 
 #include <stdint.h>
@@ -72,6 +78,14 @@ KL_HD inline unsigned ll_next_epoch(unsigned prev, int n_layers) {
     const unsigned L = (unsigned)n_layers;
     if (prev == 0 || prev > 0xFFFFFFFFu - 2u * L) return 1u;   // restart before wrapping
     return prev + L;
+}
+
+// The slices that hold columns of chunk c of the K range [col0, col0 + width).
+struct SliceRange { int first, end; };
+KL_HD inline SliceRange staged_slices(int col0, int width, int c, int chunk) {
+    const int k0 = col0 + c * chunk;
+    const int k1 = k0 + chunk < col0 + width ? k0 + chunk : col0 + width;
+    return SliceRange{k0 / chunk, (k1 - 1) / chunk + 1};
 }
 
 }  // namespace kl

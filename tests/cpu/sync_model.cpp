@@ -18,10 +18,14 @@
 //      thread with the error flag set, instead of hanging;
 //   3. tagged hand-offs: readers accept exactly the current layer's values,
 //      never an earlier layer's or step's, across the tag wrap;
-//   4. a missing tagged writer trips the watchdog too.
+//   4. a missing tagged writer trips the watchdog too;
+//   5. RMSNorm slices: a product that waits for staged_slices of a chunk reads
+//      no column whose slice is not complete, for K ranges that start and end
+//      anywhere in a slice.
 // Prints "sync model OK" and exits 0, else prints the failure and exits 1.
 // With --plant-early-barrier it runs check 1 with a planted off-by-one barrier
-// target, which the check (or ThreadSanitizer) must report.
+// target, with --plant-one-slice check 5 with a chunk that waits for the slice
+// of its first column alone, which the check (or ThreadSanitizer) must report.
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -40,7 +44,8 @@ namespace {
 constexpr int kSpin = 1 << 18;
 
 int g_fail = 0;
-int g_plant = 0;   // 1: a planted mistake (barrier k waits for barrier k - 1's target)
+int g_plant = 0;   // a planted mistake; 1: barrier k waits for barrier k - 1's target
+int g_plant_slice = 0;   // 1: a chunk waits for one slice
 void check(bool ok, const char *what) {
     if (!ok) {
         std::fprintf(stderr, "FAIL: %s\n", what);
@@ -204,6 +209,68 @@ void test_tagged_missing_writer() {
     check(err.load() == 1, "tags: a stale word is never taken as current");
 }
 
+// 5. every column of every chunk of every K range (KT k-tiles in KS equal
+// slices, as the host may choose them) lies in a slice that the chunk waits
+// for, and no other slice is waited for
+SliceRange waited_slices(int col0, int width, int c, int chunk) {
+    SliceRange r = staged_slices(col0, width, c, chunk);
+    if (g_plant_slice) r.end = r.first + 1;
+    return r;
+}
+void test_slice_cover(int chunk) {
+    const int tile = 64;
+    bool covered = true, tight = true;
+    for (int KT = 1; KT <= 320; ++KT)
+        for (int KS = 1; KS <= 16; ++KS) {
+            if (KT % KS) continue;
+            const int width = KT / KS * tile;
+            for (int ks = 0; ks < KS; ++ks) {
+                const int col0 = ks * width;
+                for (int c = 0; c * chunk < width; ++c) {
+                    const SliceRange r = waited_slices(col0, width, c, chunk);
+                    std::vector<int> touched;
+                    for (int k = c * chunk; k < width && k < (c + 1) * chunk; ++k) {
+                        const int sl = (col0 + k) / chunk;
+                        covered = covered && sl >= r.first && sl < r.end;
+                        if (touched.empty() || touched.back() != sl) touched.push_back(sl);
+                    }
+                    tight = tight && r.end - r.first == (int)touched.size();
+                }
+            }
+        }
+    check(covered, "slices: a chunk's columns lie in the slices it waits for");
+    check(g_plant_slice || tight, "slices: a chunk waits for no other slice");
+}
+// the same with threads: the row is plain data, ordered by the slice counters
+// alone; the last slice comes late
+void test_slice_handoff(int KT, int KS, int chunk) {
+    const int tile = 64, H = KT * tile, ns = (H + chunk - 1) / chunk, width = KT / KS * tile;
+    std::vector<int> row(H, -1);
+    std::vector<std::atomic<unsigned>> cnt(ns);
+    for (auto &c : cnt) c.store(0);
+    std::atomic<int> bad{0};
+    run_threads(ns + KS, [&](int w) {
+        if (w < ns) {   // the producer of slice w
+            for (int y = 0; y < 200 * w; ++y) std::this_thread::yield();
+            for (int i = w * chunk; i < H && i < (w + 1) * chunk; ++i) row[i] = i;
+            cnt[w].fetch_add(1, std::memory_order_release);
+            return;
+        }
+        const int col0 = (w - ns) * width;
+        for (int c = 0; c * chunk < width; ++c) {
+            const SliceRange r = waited_slices(col0, width, c, chunk);
+            for (int s = r.first; s < r.end; ++s)
+                for (int spins = 0; cnt[s].load(std::memory_order_acquire) == 0; ++spins) {
+                    if (spins >= kSpin) { bad.store(1); return; }
+                    std::this_thread::yield();
+                }
+            for (int k = c * chunk; k < width && k < (c + 1) * chunk; ++k)
+                if (row[col0 + k] != col0 + k) bad.store(1);
+        }
+    });
+    check(bad.load() == 0, "slices: every column staged is complete");
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -211,6 +278,12 @@ int main(int argc, char **argv) {
         // the model must catch a barrier that lets threads through one early
         g_plant = 1;
         test_barrier(20, 2, 5);
+        return g_fail ? 1 : 0;
+    }
+    if (argc > 1 && std::string(argv[1]) == "--plant-one-slice") {
+        g_plant_slice = 1;
+        test_slice_cover(512);
+        test_slice_handoff(12, 2, 512);
         return g_fail ? 1 : 0;
     }
     // group sizes: 20 threads on 16 counters (sizes 2 and 1); 5 on 5
@@ -221,6 +294,10 @@ int main(int argc, char **argv) {
     // near the top of the tag space: the range restarts at 1 instead of wrapping
     test_tagged(12, 4, 3, 0xFFFFFFFFu - 8u);
     test_tagged_missing_writer();
+    test_slice_cover(512);
+    test_slice_handoff(12, 2, 512);    // 768 columns in 2 K slices of 384
+    test_slice_handoff(40, 8, 512);    // 2560 in 8 of 320
+    test_slice_handoff(80, 4, 512);    // 5120 in 4 of 1280 (three chunks each)
     // the epoch arithmetic on its own
     check(ll_next_epoch(0, 32) == 1, "epoch: 0 restarts at 1");
     check(ll_next_epoch(1, 32) == 33, "epoch: consecutive ranges");

@@ -92,3 +92,27 @@ def test_sequences_sharing_a_pass(over, batch):
         assert_bit_exact(o, outs["looped"], f"{what} vs looped")
     assert c.model.device_error() == 0
     c.model.close()
+
+
+@pytest.mark.parametrize("over,batch", [
+    # K slices of 384 columns (gate/up), resident
+    (dict(hidden=768, ffn_dim=4096), 5),
+    # 8 K slices of 320 columns (q/k/v), resident
+    (dict(hidden=2560, n_heads=16, n_kv_heads=4, head_dim=128, ffn_dim=264), 6),
+    # 4 K slices of 1280 columns (q/k/v), streamed through LDS
+    (dict(hidden=5120, n_heads=28, n_kv_heads=14, head_dim=128, ffn_dim=264), 5),
+], ids=str)
+def test_k_slices_across_the_slices_of_the_norm(over, batch):
+    """K slices that do not start on a slice of the RMSNorm hand-off (512
+    columns): a staged chunk lies in two of them and waits for both."""
+    cfg = dict(TINY, n_layers=2, **over)
+    say(f"[straddling slices] {over} batch {batch}")
+    filled = (np.arange(batch, dtype=np.int32) * 29 + 3) % 90
+    c = Case(cfg, batch, 128, filled, seed=611 + batch)
+    ref = c.oracle_step(nthreads=8, sample=[0, batch - 1])
+    outs = [c.gpu_step(mode) for _, mode in MODES]
+    check_against_oracle(c, outs[1], ref, only=[0, batch - 1])
+    for (what, _), o in zip(MODES, outs):
+        assert_bit_exact(o, outs[1], f"{what} vs looped")
+    assert c.model.device_error() == 0
+    c.model.close()

@@ -1,5 +1,6 @@
 """The cross-workgroup protocols of the step kernel (grid barrier with epoch
-recovery, watchdog, tagged hand-offs and their tag ranges), modelled with
+recovery, watchdog, tagged hand-offs and their tag ranges, RMSNorm slices),
+modelled with
 host threads and std::atomic under ThreadSanitizer, on the library's own
 protocol arithmetic (csrc/kl_sync.h).  CPU only."""
 import os
@@ -34,7 +35,15 @@ def test_protocols_hold_under_thread_sanitizer(model):
 def test_model_catches_a_planted_early_barrier(model):
     # the same check with barrier k waiting for barrier k - 1's target: the
     # model (or ThreadSanitizer) must report it
-    r = subprocess.run([model, "--plant-early-barrier"], capture_output=True, text=True,
-                       timeout=300)
+    planted(model, "--plant-early-barrier")
+
+
+def test_model_catches_a_chunk_that_waits_for_one_slice(model):
+    # a staged chunk that waits for the RMSNorm slice of its first column alone
+    planted(model, "--plant-one-slice")
+
+
+def planted(model, mistake):
+    r = subprocess.run([model, mistake], capture_output=True, text=True, timeout=300)
     assert r.returncode != 0
     assert "FAIL" in r.stderr or "ThreadSanitizer" in r.stderr
