@@ -35,6 +35,7 @@ struct kl_state {
     int Sg, Sc, Rc, KTc;
     int *err;                         // device error word (its own allocation, 256 B)
     unsigned *epoch;                  // first tag of the next step (in the same allocation)
+    unsigned *epoch_arrivals;         // its arrival counter (likewise)
     unsigned long long *keys;         // argmax keys of the token loop: [2][max_batch]
     // the per-layer schedule as a graph, for the caller buffers it was built on
     hipGraph_t graph;
@@ -378,6 +379,7 @@ StepParams base_params(const kl_state &s) {
     P.KSo = s.KSo; P.KSd = s.KSd; P.KSg = s.KSg; P.KSq = s.KSq;
     P.err = s.err;
     P.epoch_ptr = s.epoch;
+    P.epoch_arrivals = s.epoch_arrivals;
     P.dummy = s.arena + s.off_dummy;
     P.nwg = s.nwg;
     P.lds_red = s.lds_red; P.lds_sm = s.lds_sm; P.lds_bar = s.lds_bar;
@@ -492,6 +494,7 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     TRY(hipMalloc(&S->err, 256));
     TRY(hipMemsetAsync(S->err, 0, 256, s));
     S->epoch = reinterpret_cast<unsigned *>(reinterpret_cast<uint8_t *>(S->err) + 128);
+    S->epoch_arrivals = reinterpret_cast<unsigned *>(reinterpret_cast<uint8_t *>(S->err) + 192);
     TRY(hipMalloc(&S->keys, (size_t)2 * c.max_batch * sizeof(unsigned long long)));
     TRY(hipMemsetAsync(S->keys, 0, (size_t)2 * c.max_batch * sizeof(unsigned long long), s));
     {

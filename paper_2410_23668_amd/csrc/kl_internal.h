@@ -119,6 +119,8 @@ struct StepParams {
     // writing step and layer in the high 32 bits)
     unsigned *epoch_ptr;       // device word: the current step's first tag (layer l's tag
                                // is *epoch_ptr + l; the step's last phase advances it)
+    unsigned *epoch_arrivals;  // device word: workgroups of the step's last phase that have
+                               // read it (the last one advances it and clears this)
     unsigned long long *q_ll;  // [B][nq*d] rotated queries (fp32)
     unsigned long long *kv_ll; // [B][nkv][d]: new key (d/2 words: bf16 dims i, i + d/2),
                                // then new value (d/2 words: bf16 dims 2j, 2j + 1)

@@ -456,7 +456,8 @@ __device__ __forceinline__ void local_wait(const StepParams &P, const unsigned *
 // round trip, instead of store drain, counter atomic, counter poll and data
 // load one after the other.  Tags are epoch + layer, each step using a fresh
 // range of tags that never includes 0 (cleared memory); the epoch is read at
-// launch start and advanced by the step's last phase (ll_next_epoch).
+// launch start and advanced by the step's last phase once every workgroup has
+// read it (ll_next_epoch, epoch_last_arrival).
 __device__ __forceinline__ unsigned ll_tag(const StepParams &P, int l) {
     return *launch_epoch(P) + (unsigned)l;
 }
@@ -3346,6 +3347,14 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
     unsigned long long *best = amax_slots(P);
     const bool sample = P.amax != nullptr;
     if (sample && kl_tid() < kGemmBatch) best[kl_tid()] = 0ull;   // (staging barriers follow)
+    // per-sequence path: this workgroup has read the epoch (bar_init); the
+    // answer is used at the end of the phase
+    unsigned arrivals = 0;
+    auto epoch_arrive = [&]() {
+        if (!BAT && is_ctl_lane0())
+            arrivals = __hip_atomic_fetch_add(P.epoch_arrivals, 1u, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+    };
     auto flush = [&](int b0, int nb) {
         if (!sample) return;
         __syncthreads();
@@ -3383,6 +3392,8 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
                 stage_rms_deferred(P, P.xb_ll + (size_t)b * P.Hp, ll_tag(P, P.L), P.final_norm, P.H,
                                    P.Hp, S.a, S.sm);
             }
+            // (behind the staging's loads, beside the products)
+            if (b == 0) epoch_arrive();
             if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
         },
         [&](int c, int b0, int nb, uint16_t *buf, bool all) { stage_act_chunk(P, c, b0, nb, buf, all); },
@@ -3405,6 +3416,7 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
         },
         0, 0, [&](int b0, int nb) { flush(b0, nb); }, P.Hp);
     if constexpr (!BAT) {
+        if (R.count == 0) epoch_arrive();   // (nothing was staged)
         flush(0, P.B);
         // the hidden state: every workgroup its own rows (each row's last
         // value was put by the control wave or before the launch)
@@ -3417,11 +3429,20 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
             }
         }
     }
-    // the step's last phase: the next step's tags (every workgroup of every
-    // launch of this step read the epoch at its start)
-    if (blockIdx.x == 0 && kl_tid() == 0)
+    // the step's last phase: the next step's tags.  Per-sequence path: by the
+    // last workgroup that has read this step's (a launch of the head alone
+    // polls for tags of this step, and nothing else of it orders a workgroup
+    // that starts late before one that is done; in the looped launch likewise
+    // a workgroup without work in the layers).  Matrix-core path: the head
+    // uses no tags, and a launch with layers has had every workgroup in its
+    // grid barriers.
+    const bool last = BAT ? blockIdx.x == 0 : epoch_last_arrival(arrivals, P.nwg);
+    if (last && is_ctl_lane0()) {
+        if (!BAT)
+            __hip_atomic_store(P.epoch_arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(P.epoch_ptr, ll_next_epoch(*launch_epoch(P), P.L + 1), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (is_ctl_lane0()) trace_stamp(P, ti, 0);
 }
 

@@ -18,8 +18,11 @@
 // input residual; the head's input): L + 1 of them;
 // the next step's range starts right after, and restarts at 1 before it
 // would reach 2^32, so no step's range contains 0, the tag of cleared memory.
-// (The epoch lives in device memory: read at launch start, advanced by the
-// step's last phase.)
+// The epoch lives in device memory.  Every workgroup of a launch reads it when
+// it starts, and the step's last phase advances it, where workgroups that start
+// late may still have to read it (nothing else of that launch orders them).  So
+// each workgroup adds one to an arrival counter after its own read, and the
+// last to arrive stores the next epoch and clears the counter.
 //
 // RMSNorm slices (matrix-core path).  A normalised row is handed over in slices
 // of 'chunk' columns, each with a counter; a product stages its K range in
@@ -78,6 +81,11 @@ KL_HD inline unsigned ll_next_epoch(unsigned prev, int n_layers) {
     const unsigned L = (unsigned)n_layers;
     if (prev == 0 || prev > 0xFFFFFFFFu - 2u * L) return 1u;   // restart before wrapping
     return prev + L;
+}
+
+// Whether the workgroup that found 'before' arrivals is the launch's last one.
+KL_HD inline bool epoch_last_arrival(unsigned before, int nwg) {
+    return before == (unsigned)nwg - 1u;
 }
 
 // The slices that hold columns of chunk c of the K range [col0, col0 + width).

@@ -21,11 +21,14 @@
 //   4. a missing tagged writer trips the watchdog too;
 //   5. RMSNorm slices: a product that waits for staged_slices of a chunk reads
 //      no column whose slice is not complete, for K ranges that start and end
-//      anywhere in a slice.
+//      anywhere in a slice;
+//   6. the epoch: in a launch of the step's last phase alone, a workgroup that
+//      starts after others are done still finds the step's own tags.
 // Prints "sync model OK" and exits 0, else prints the failure and exits 1.
 // With --plant-early-barrier it runs check 1 with a planted off-by-one barrier
 // target, with --plant-one-slice check 5 with a chunk that waits for the slice
-// of its first column alone, which the check (or ThreadSanitizer) must report.
+// of its first column alone, with --plant-early-epoch check 6 with the epoch
+// advanced by workgroup 0 when it is done, which the check (or ThreadSanitizer) must report.
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -46,6 +49,7 @@ constexpr int kSpin = 1 << 18;
 int g_fail = 0;
 int g_plant = 0;   // a planted mistake; 1: barrier k waits for barrier k - 1's target
 int g_plant_slice = 0;   // 1: a chunk waits for one slice
+int g_plant_epoch = 0;   // 1: workgroup 0 advances the epoch when it is done
 void check(bool ok, const char *what) {
     if (!ok) {
         std::fprintf(stderr, "FAIL: %s\n", what);
@@ -271,6 +275,47 @@ void test_slice_handoff(int KT, int KS, int chunk) {
     check(bad.load() == 0, "slices: every column staged is complete");
 }
 
+// 6. the step's last phase as a launch of its own: each workgroup reads the
+// epoch when it starts, polls for words of the layers' launches, is done;
+// workgroup 'late' starts once workgroup 0 is done (and every other one is, in
+// every second step)
+void test_epoch(int nwg, int steps, int layers, int late) {
+    std::atomic<unsigned> epoch{1}, arrivals{0};
+    std::vector<std::atomic<unsigned long long>> x(nwg);   // the last residual
+    std::atomic<int> err{0};
+    for (int s = 0; s < steps; ++s) {
+        const unsigned e = epoch.load();
+        for (int i = 0; i < nwg; ++i)
+            x[i].store(ll_word((unsigned)(s * 17 + i), e + (unsigned)layers));
+        std::atomic<int> done0{0}, done{0};
+        run_threads(nwg, [&](int w) {
+            if (w == late)
+                while (done0.load() == 0 || (s % 2 && done.load() < nwg - 1)) std::this_thread::yield();
+            const unsigned mine = epoch.load(std::memory_order_relaxed);
+            for (int i = 0; i < nwg; ++i)
+                for (int spins = 1;; ++spins) {
+                    const unsigned long long v = x[i].load(std::memory_order_relaxed);
+                    if (ll_current(v, mine + (unsigned)layers)) {
+                        if (ll_value(v) != (unsigned)(s * 17 + i)) err.store(3);
+                        break;
+                    }
+                    if (spins >= kSpin || err.load()) {
+                        err.store(1);
+                        break;
+                    }
+                }
+            const bool last = epoch_last_arrival(arrivals.fetch_add(1), nwg);
+            if (last) arrivals.store(0);
+            if (g_plant_epoch ? w == 0 : last) epoch.store(ll_next_epoch(mine, layers + 1));
+            if (w == 0) done0.store(1);
+            done.fetch_add(1);
+        });
+        check(err.load() == 0, "epoch: a late workgroup finds the step's own tags");
+        check(epoch.load() == ll_next_epoch(e, layers + 1) && arrivals.load() == 0,
+              "epoch: advanced once, the counter cleared");
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -286,6 +331,11 @@ int main(int argc, char **argv) {
         test_slice_handoff(12, 2, 512);
         return g_fail ? 1 : 0;
     }
+    if (argc > 1 && std::string(argv[1]) == "--plant-early-epoch") {
+        g_plant_epoch = 1;
+        test_epoch(8, 2, 3, 5);
+        return g_fail ? 1 : 0;
+    }
     // group sizes: 20 threads on 16 counters (sizes 2 and 1); 5 on 5
     test_barrier(20, 4, 5);
     test_barrier(5, 3, 7);
@@ -298,6 +348,8 @@ int main(int argc, char **argv) {
     test_slice_handoff(12, 2, 512);    // 768 columns in 2 K slices of 384
     test_slice_handoff(40, 8, 512);    // 2560 in 8 of 320
     test_slice_handoff(80, 4, 512);    // 5120 in 4 of 1280 (three chunks each)
+    test_epoch(8, 6, 3, 5);
+    test_epoch(1, 3, 3, 1);
     // the epoch arithmetic on its own
     check(ll_next_epoch(0, 32) == 1, "epoch: 0 restarts at 1");
     check(ll_next_epoch(1, 32) == 33, "epoch: consecutive ranges");
