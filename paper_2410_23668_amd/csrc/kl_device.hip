@@ -110,15 +110,19 @@ __global__ void kl_pack_rows_kernel(uint16_t *__restrict__ dst, int n_rg, int KT
     }
 }
 
-__global__ void kl_emit_tokens_kernel(int32_t *tokens, const unsigned long long *keys, int n) {
+__global__ void kl_emit_tokens_kernel(int32_t *tokens, const unsigned long long *keys,
+                                      unsigned long long *clear, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) tokens[i] = key_token(keys[i]);
+    if (i < n) {
+        tokens[i] = key_token(keys[i]);
+        clear[i] = 0ull;
+    }
 }
 
-hipError_t launch_emit_tokens(int32_t *tokens, const unsigned long long *keys, int n,
-                              hipStream_t stream) {
+hipError_t launch_emit_tokens(int32_t *tokens, const unsigned long long *keys,
+                              unsigned long long *clear, int n, hipStream_t stream) {
     hipLaunchKernelGGL(kl_emit_tokens_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, tokens,
-                       keys, n);
+                       keys, clear, n);
     return hipGetLastError();
 }
 

@@ -36,7 +36,8 @@ struct kl_state {
     int *err;                         // device error word (its own allocation, 256 B)
     unsigned *epoch;                  // first tag of the next step (in the same allocation)
     unsigned *epoch_arrivals;         // its arrival counter (likewise)
-    unsigned long long *keys;         // argmax keys of the token loop: [2][max_batch]
+    unsigned long long *keys;         // argmax keys of the token loop: [kKeySlots][max_batch]
+    bool keys_clear;                  // the first step's set is zero (a loop that failed left it)
     // the per-layer schedule as a graph, for the caller buffers it was built on
     hipGraph_t graph;
     hipGraphExec_t graph_exec;
@@ -495,8 +496,11 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     TRY(hipMemsetAsync(S->err, 0, 256, s));
     S->epoch = reinterpret_cast<unsigned *>(reinterpret_cast<uint8_t *>(S->err) + 128);
     S->epoch_arrivals = reinterpret_cast<unsigned *>(reinterpret_cast<uint8_t *>(S->err) + 192);
-    TRY(hipMalloc(&S->keys, (size_t)2 * c.max_batch * sizeof(unsigned long long)));
-    TRY(hipMemsetAsync(S->keys, 0, (size_t)2 * c.max_batch * sizeof(unsigned long long), s));
+    const size_t key_bytes = align_up((size_t)kKeySlots * c.max_batch * sizeof(unsigned long long),
+                                      16);
+    TRY(hipMalloc(&S->keys, key_bytes));
+    TRY(hipMemsetAsync(S->keys, 0, key_bytes, s));
+    S->keys_clear = true;
     {
         const unsigned first_tag = 1;
         TRY(hipMemcpyAsync(S->epoch, &first_tag, sizeof first_tag, hipMemcpyHostToDevice, s));
@@ -834,18 +838,25 @@ kl_status kl_decode_greedy(kl_state *st, const int32_t *token_ids, const int32_t
     StepParams P = step_params(*st, st->scratch, plan_scratch(*st, c.max_batch, false), token_ids,
                                positions, batch, kv, logits_out, nullptr);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // step n: positions + n; its head leaves the argmax keys in keys[n % 2],
-    // from which step n + 1's embedding takes its tokens (recording them as
-    // tokens_out[n])
+    // step n: positions + n; its head leaves the argmax keys in set
+    // key_slot(n), from which step n + 1's embedding takes its tokens
+    // (recording them as tokens_out[n])
+    const auto keys = [&](int n) { return st->keys + (size_t)key_slot(n) * c.max_batch; };
+    if (!st->keys_clear)
+        HIP_TRY(launch_zero(st->keys, align_up((size_t)c.max_batch * sizeof(unsigned long long), 16),
+                            s));
+    st->keys_clear = false;
     for (int32_t n = 0; n < n_steps; ++n) {
         P.pos_add = n;
-        P.amax = st->keys + (size_t)(n % 2) * c.max_batch;
-        P.tok_keys = n == 0 ? nullptr : st->keys + (size_t)((n - 1) % 2) * c.max_batch;
+        P.amax = keys(n);
+        P.amax_next = keys(n + 1);
+        P.tok_keys = n == 0 ? nullptr : keys(n - 1);
         P.tok_emit = n == 0 ? nullptr : tokens_out + (size_t)(n - 1) * batch;
         HIP_TRY(launch_schedule(P, mode, st->lds_bytes, s));
     }
-    HIP_TRY(launch_emit_tokens(tokens_out + (size_t)(n_steps - 1) * batch,
-                               st->keys + (size_t)((n_steps - 1) % 2) * c.max_batch, batch, s));
+    HIP_TRY(launch_emit_tokens(tokens_out + (size_t)(n_steps - 1) * batch, keys(n_steps - 1),
+                               keys(0), batch, s));
+    st->keys_clear = true;
     return KL_OK;
 }
 

@@ -95,6 +95,8 @@ struct StepParams {
     const unsigned long long *tok_keys;   // non-null: token b is the previous step's argmax
     int32_t *tok_emit;         // non-null: the embedding phase records the tokens it takes
     unsigned long long *amax;  // non-null: the head leaves each sequence's argmax key here
+                               // (cleared by the step before)
+    unsigned long long *amax_next;   // with amax: the next step's keys, cleared by this step
     int B;
     uint16_t *kc, *vc;         // [L][kv_batch][nkv][cap][d]
     int kv_batch, cap;
@@ -180,9 +182,10 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t stream);
 hipError_t launch_read_stream(const void *p, size_t bytes, int workgroups, uint32_t *out,
                               hipStream_t stream);
 
-// tokens[b] = the token of argmax key keys[b] (-1 where there is none), b < n.
-hipError_t launch_emit_tokens(int32_t *tokens, const unsigned long long *keys, int n,
-                              hipStream_t stream);
+// tokens[b] = the token of argmax key keys[b] (-1 where there is none), b < n; then
+// clear[b] = 0 (the keys of the next loop's first step; may be 'keys').
+hipError_t launch_emit_tokens(int32_t *tokens, const unsigned long long *keys,
+                              unsigned long long *clear, int n, hipStream_t stream);
 
 hipError_t launch_pack_rows(uint16_t *dst, int n_rg, int kt, int K, int ld, const int32_t *rowmap,
                             const uint16_t *src0, const uint16_t *src1, const uint16_t *src2,

@@ -1907,9 +1907,11 @@ __device__ __forceinline__ void phase_embed(KArg ka, int gwait, int garrive, int
             if (t < 0 || t >= P.V) bits |= KL_DEVERR_TOKEN;
             if (p < 0 || p >= P.cap || p >= P.max_seq) bits |= KL_DEVERR_POSITION;
             if (bits) atomicOr(P.err, bits);
-            // token loop: record the token taken, clear this step's argmax
+            // token loop: record the token taken, clear the next step's argmax
+            // (this step's is in use as soon as some workgroup's head is done,
+            // which nothing here precedes)
             if (P.tok_emit) P.tok_emit[b] = t;
-            if (P.amax) st_dev_u64(P.amax + b, 0ull);
+            if (P.amax) st_dev_u64(P.amax_next + b, 0ull);
         }
         // (the batched RMSNorm counters exist, and are used, in batched steps only)
         const int nc = 2 * P.nkv + P.Sc +

@@ -24,6 +24,12 @@
 // each workgroup adds one to an arrival counter after its own read, and the
 // last to arrive stores the next epoch and clears the counter.
 //
+// Argmax keys of the token loop: three sets in turn.  Step n's head takes the
+// maximum into set key_slot(n) while the step still reads its tokens from
+// set key_slot(n - 1), and clears set key_slot(n + 1), which nothing else
+// touches in that step: the clearing is ordered before its use by the launch
+// boundary alone, whatever the order of the workgroups within a launch.
+//
 // RMSNorm slices (matrix-core path).  A normalised row is handed over in slices
 // of 'chunk' columns, each with a counter; a product stages its K range in
 // chunks of as many columns, counted from the range's own first column, which
@@ -87,6 +93,10 @@ KL_HD inline unsigned ll_next_epoch(unsigned prev, int n_layers) {
 KL_HD inline bool epoch_last_arrival(unsigned before, int nwg) {
     return before == (unsigned)nwg - 1u;
 }
+
+// The set of argmax keys of step n of a token loop (n >= -1).
+constexpr int kKeySlots = 3;
+KL_HD inline int key_slot(int n) { return (n + kKeySlots) % kKeySlots; }
 
 // The slices that hold columns of chunk c of the K range [col0, col0 + width).
 struct SliceRange { int first, end; };

@@ -28,7 +28,8 @@
 // With --plant-early-barrier it runs check 1 with a planted off-by-one barrier
 // target, with --plant-one-slice check 5 with a chunk that waits for the slice
 // of its first column alone, with --plant-early-epoch check 6 with the epoch
-// advanced by workgroup 0 when it is done, which the check (or ThreadSanitizer) must report.
+// advanced by workgroup 0 when it is done, with --plant-own-keys check 7 with
+// each step clearing its own set of keys, which the check (or ThreadSanitizer) must report.
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -49,6 +50,7 @@ constexpr int kSpin = 1 << 18;
 int g_fail = 0;
 int g_plant = 0;   // a planted mistake; 1: barrier k waits for barrier k - 1's target
 int g_plant_slice = 0;   // 1: a chunk waits for one slice
+int g_plant_keys = 0;    // 1: a step clears the keys it takes its own maximum into
 int g_plant_epoch = 0;   // 1: workgroup 0 advances the epoch when it is done
 void check(bool ok, const char *what) {
     if (!ok) {
@@ -316,6 +318,38 @@ void test_epoch(int nwg, int steps, int layers, int late) {
     }
 }
 
+// 7. a token loop: step n's workgroups take the maximum of their keys, workgroup
+// 0 clears a set when the others are done; loops of different lengths in a row
+void test_keys(int nwg, const std::vector<int> &loops) {
+    std::vector<std::atomic<unsigned long long>> keys(kKeySlots);
+    for (auto &k : keys) k.store(0);
+    std::atomic<int> bad{0};
+    for (int steps : loops) {
+        unsigned long long want = 0;
+        for (int n = 0; n < steps; ++n) {
+            std::atomic<int> done{1};
+            // (every step's largest key is below the ones of the steps before)
+            const unsigned long long top = 100000ull - 100ull * (unsigned)n;
+            run_threads(nwg, [&](int w) {
+                if (w == 0) {
+                    while (done.load() < nwg) std::this_thread::yield();
+                    keys[key_slot(g_plant_keys ? n : n + 1)].store(0);
+                    return;
+                }
+                if (n > 0 && keys[key_slot(n - 1)].load() != want) bad.store(1);
+                const unsigned long long k = top + (unsigned)w;
+                unsigned long long o = keys[key_slot(n)].load();
+                while (o < k && !keys[key_slot(n)].compare_exchange_weak(o, k)) {}
+                done.fetch_add(1);
+            });
+            want = top + (unsigned)(nwg - 1);
+        }
+        check(keys[key_slot(steps - 1)].load() == want, "keys: a step's maximum is its own");
+        keys[key_slot(0)].store(0);   // the loop's last launch
+    }
+    check(bad.load() == 0, "keys: every workgroup reads the step before's maximum");
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -336,6 +370,11 @@ int main(int argc, char **argv) {
         test_epoch(8, 2, 3, 5);
         return g_fail ? 1 : 0;
     }
+    if (argc > 1 && std::string(argv[1]) == "--plant-own-keys") {
+        g_plant_keys = 1;
+        test_keys(6, {2});
+        return g_fail ? 1 : 0;
+    }
     // group sizes: 20 threads on 16 counters (sizes 2 and 1); 5 on 5
     test_barrier(20, 4, 5);
     test_barrier(5, 3, 7);
@@ -350,6 +389,7 @@ int main(int argc, char **argv) {
     test_slice_handoff(80, 4, 512);    // 5120 in 4 of 1280 (three chunks each)
     test_epoch(8, 6, 3, 5);
     test_epoch(1, 3, 3, 1);
+    test_keys(6, {1, 5, 2, 3, 4, 1, 1});
     // the epoch arithmetic on its own
     check(ll_next_epoch(0, 32) == 1, "epoch: 0 restarts at 1");
     check(ll_next_epoch(1, 32) == 33, "epoch: consecutive ranges");

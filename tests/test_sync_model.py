@@ -1,8 +1,8 @@
 """The cross-workgroup protocols of the step kernel (grid barrier with epoch
 recovery, watchdog, tagged hand-offs and their tag ranges, RMSNorm slices, the
-advance of the epoch), modelled with host threads and std::atomic under
-ThreadSanitizer, on the library's own protocol arithmetic (csrc/kl_sync.h).
-CPU only."""
+advance of the epoch, the token loop's argmax keys), modelled with host threads
+and std::atomic under ThreadSanitizer, on the library's own protocol arithmetic
+(csrc/kl_sync.h).  CPU only."""
 import os
 import shutil
 import subprocess
@@ -46,6 +46,11 @@ def test_model_catches_a_chunk_that_waits_for_one_slice(model):
 def test_model_catches_an_epoch_advanced_before_every_read(model):
     # workgroup 0 of the step's last phase advances the epoch when it is done
     planted(model, "--plant-early-epoch")
+
+
+def test_model_catches_keys_cleared_in_their_own_step(model):
+    # a token loop whose step clears the argmax keys that it fills itself
+    planted(model, "--plant-own-keys")
 
 
 def planted(model, mistake):
