@@ -47,13 +47,9 @@ struct kl_state {
     int trace_max;
     int32_t *rowmaps;                 // device row maps used by set_layer / set_globals
     const int32_t *maps[5];           // by RowMap
-    int nwg, lds_bytes;
-    int lds_red, lds_sm, lds_bar;
-    int lds_red_seq;                  // the GEMV partial sums on the per-sequence path
+    int nwg;
+    LdsLayout lds;
     int own_max;                      // residual rows a workgroup owns, at most
-    bool multi_ok;                    // up to kMultiSeq sequences share a GEMV pass
-    int lds_mm;                       // its slots on the matrix cores (0: on the vector units)
-    int batched_from;                 // first batch of the matrix-core path
 };
 
 namespace {
@@ -115,98 +111,6 @@ kl_status validate_config(const kl_config *c) {
     return KL_OK;
 }
 
-// FFN column blocks: the largest divisor of the k-tile count of ffn_dim that
-// is at most 32 (and at most the grid).
-int largest_divisor_at_most(int n, int cap) {
-    for (int k = std::min(n, cap); k > 1; --k)
-        if (n % k == 0) return k;
-    return 1;
-}
-
-// K slices of a batched product over n K units of t k-tiles each, for a
-// matrix of nblk 16-row blocks: the fewest slices (a divisor of n, at most
-// kMaxKSlices) whose K range stays resident in LDS and that give every
-// workgroup kWaves blocks or more; failing that, the resident choice with the
-// most blocks per workgroup; if no slice fits in LDS, the most slices (the
-// activations then stream through LDS in chunks).
-int batched_k_slices(int n, int t, int nblk, int nwg) {
-    int best = -1;
-    for (int s = 1; s <= std::min(n, kMaxKSlices); ++s) {
-        if (n % s || (n / s) * t * kTileK > kGemmResidentK) continue;
-        best = s;
-        if ((long long)nblk * s >= (long long)kWaves * nwg) break;
-    }
-    return best > 0 ? best : largest_divisor_at_most(n, kMaxKSlices);
-}
-// K slices of the gate/up and q/k/v products, whose K-slice partial sums a
-// grid-wide fold reads back (the SwiGLU fold, the q/k/v fold): the fewest
-// slices (a divisor of n, at most kMaxKSlices) whose K range is at most two
-// resident ranges (the activations then stream through LDS) and that give
-// every workgroup kWaves / 2 blocks or more; failing that, batched_k_slices.
-// Fewer slices halve what the fold reads.  (8B shape, batch 32: 7.95 ms with
-// 4 gate/up and 8 q/k/v slices, 7.48 with 2 and 4; the same for the O and
-// down products, whose partials the next RMSNorm folds, gained nothing.)
-int folded_k_slices(int n, int t, int nblk, int nwg) {
-    for (int s = 1; s <= std::min(n, kMaxKSlices); ++s) {
-        if (n % s || (n / s) * t * kTileK > 2 * kGemmResidentK) continue;
-        if ((long long)nblk * s >= (long long)(kWaves / 2) * nwg) return s;
-    }
-    return batched_k_slices(n, t, nblk, nwg);
-}
-
-// Dynamic LDS layout of the step kernel (offsets in floats): the activation
-// vector / attention area, the GEMV wave partials, 64 floats of small
-// reductions and flags, then the barrier bases.
-void lds_layout_for(kl_state &s) {
-    const kl_config &c = s.cfg;
-    const int g = c.n_heads / c.n_kv_heads, d = c.head_dim;
-    // attention: two sets of queries, waves' (max, sum, output) per head, new
-    // key and value; flags
-    const int attn_main = 3 * g * (d + 8) + 4 * kWaves * g + 2 * kWaves * g * (d + 4) + 2 * d + 4;
-    const auto round64 = [](int v) { return (v + 63) & ~63; };
-    const int rs = kWaves * kRgBatch * kTileRows;   // one sequence's GEMV partial sums
-    // per-sequence path, one sequence per GEMV pass: activations and RoPE row,
-    // a SwiGLU block, the merged attention output
-    const int one = round64(std::max({2 * s.Hp + d, s.KTc * kTileK, attn_main, s.Ap}));
-    // kMultiSeq sequences per pass
-    const int multi = round64(std::max({kMultiSeq * (s.Hp + d), kMultiSeq * s.KTc * kTileK,
-                                        kMultiSeq * s.Ap, attn_main, 2 * s.Hp + d}));
-    // The first batch of the matrix-core path: with several sequences per
-    // GEMV pass the per-sequence path serves up to kMultiSeq sequences (a
-    // mixture of experts: up to kMfmaBatch - 1, as its routing needs).  The
-    // matrix-core path's area (and its partial sums after it) may overlap
-    // the per-sequence path's partial sums: a launch runs one of the two.
-    // On the matrix cores a sequence's vector is three bf16 terms: where that
-    // and the weight re-layout slots fit.
-    const int mm = round64(std::max({multi, 3 * kMultiSeq * (s.Hp + 8) / 2 + kMultiSeq * d,
-                                     3 * kMultiSeq * (s.Ap + 8) / 2,
-                                     3 * kMultiSeq * (s.KTc * kTileK + 8) / 2}));
-    const auto layout = [&](bool mu, bool use_mm) {
-        s.multi_ok = mu;
-        s.lds_mm = use_mm ? mm : 0;
-        s.batched_from = c.n_experts > 1 ? kMfmaBatch : (mu ? kMultiSeq + 1 : kBatchedFrom);
-        const int seq_a = use_mm ? mm + kWaves * 2048 / 4 : (mu ? multi : one);
-        const int seq_end = seq_a + (mu ? kMultiSeq : 1) * rs;
-        const bool bat = c.max_batch >= s.batched_from;
-        const int bat_a = bat ? round64(std::max(seq_a, kGemmLdsBytes / 4)) : seq_a;
-        s.lds_red_seq = seq_a;
-        s.lds_red = bat_a;
-        s.lds_sm = std::max(seq_end, bat_a + rs);
-        s.lds_bar = s.lds_sm + 64;
-        // + the step's epoch, position and validity per sequence, the head's
-        // argmax keys of a group of sequences, the experts and their weights
-        // per sequence (two slots), the workgroup's share of the attention, its
-        // residual rows
-        const int seqs = std::min(c.max_batch, s.batched_from - 1);
-        s.lds_bytes = (s.lds_bar + 2 * kBarGroups + 4 + 2 * kMfmaBatch + 2 * kGemmBatch +
-                       4 * kMfmaBatch + 8 + 2 * seqs * s.own_max) * (int)sizeof(float);
-    };
-    const int most = 160 * 1024 - 256;
-    layout(c.max_batch >= 2, c.max_batch >= 2);
-    if (s.lds_mm && s.lds_bytes > most) layout(true, false);
-    if (s.multi_ok && s.lds_bytes > most) layout(false, false);
-}
-
 // Step scratch for a batch of B sequences (byte offsets from its base; every
 // region 256-byte aligned):
 //   grid barrier counters (16 groups, 256 B apart) and the local counters:
@@ -248,7 +152,7 @@ ScratchPlan plan_scratch(const kl_state &S, int B, bool exact) {
     const int d = c.head_dim, g = c.n_heads / c.n_kv_heads, nkv = c.n_kv_heads;
     ScratchPlan p{};
     p.B = B;
-    p.batched = B >= S.batched_from;
+    p.batched = B >= S.lds.batched_from;
     size_t so = 0;
     auto take = [&](size_t bytes) {
         const size_t o = so;
@@ -262,7 +166,7 @@ ScratchPlan plan_scratch(const kl_state &S, int B, bool exact) {
     p.off_cnt_end = so;
     p.off_x = take((size_t)B * S.Hp * 8);
     // sequences of a per-sequence step
-    const int bl = exact && p.batched ? 0 : std::min(B, S.batched_from - 1);
+    const int bl = exact && p.batched ? 0 : std::min(B, S.lds.batched_from - 1);
     p.off_qll = take((size_t)bl * c.n_heads * d * 8);
     p.off_kvll = take((size_t)bl * nkv * d * 8);
     const int topk = c.n_experts > 1 ? c.top_k : 1;          // expert slots per token
@@ -383,7 +287,7 @@ StepParams base_params(const kl_state &s) {
     P.epoch_arrivals = s.epoch_arrivals;
     P.dummy = s.arena + s.off_dummy;
     P.nwg = s.nwg;
-    P.lds_red = s.lds_red; P.lds_sm = s.lds_sm; P.lds_bar = s.lds_bar;
+    P.lds_sm = s.lds.sm; P.lds_bar = s.lds.bar;
     P.own_max = s.own_max;
     P.trace = s.trace;
     P.trace_max = s.trace_max;
@@ -467,15 +371,6 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     S->arena_bytes = Gm.arena_bytes;
     TRY(hipMalloc(&S->arena, S->arena_bytes));
 
-    // grid: one persistent workgroup per CU
-    S->own_max = (S->o_rg + S->nwg - 1) / S->nwg * kTileRows;
-    lds_layout_for(*S);
-    if (S->lds_bytes > 160 * 1024 - 256)
-        return bail(fail(KL_ERR_UNSUPPORTED, "LDS need %d bytes exceeds 160 KiB", S->lds_bytes));
-    int per_cu = 0;
-    TRY(step_kernel_setup(c.head_dim, c.n_heads / c.n_kv_heads, S->lds_bytes, &per_cu));
-    if (per_cu < 1) return bail(fail(KL_ERR_UNSUPPORTED, "step kernel does not fit on a CU"));
-
     // K slices of the batched products (they depend on the grid, not on the batch)
     const int nkv = c.n_kv_heads;
     const int qkv_rows = nkv * S->qkv_rg * kTileRows;
@@ -487,6 +382,16 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     S->KSg = 5LL * (S->gu_rg / 2) >= 4LL * kWaves * S->nwg
                  ? 1 : folded_k_slices(KTH, 1, S->gu_rg / 2, S->nwg);
     S->KSq = folded_k_slices(KTH, 1, qkv_rows / 16, S->nwg);
+
+    // grid: one persistent workgroup per CU
+    S->own_max = (S->o_rg + S->nwg - 1) / S->nwg * kTileRows;
+    S->lds = lds_layout_for(c, Gm, S->own_max,
+                            matrix_cores_fill(S->o_rg / 2, S->KSo, S->KSd, S->nwg));
+    if (S->lds.bytes > kLdsMost)
+        return bail(fail(KL_ERR_UNSUPPORTED, "LDS need %d bytes exceeds 160 KiB", S->lds.bytes));
+    int per_cu = 0;
+    TRY(step_kernel_setup(c.head_dim, c.n_heads / c.n_kv_heads, S->lds.bytes, &per_cu));
+    if (per_cu < 1) return bail(fail(KL_ERR_UNSUPPORTED, "step kernel does not fit on a CU"));
 
     // step scratch for the largest batch, zeroed; the device error word
     S->scratch_bytes = plan_scratch(*S, c.max_batch, false).total;
@@ -695,13 +600,14 @@ static StepParams step_params(const kl_state &st, uint8_t *base, const ScratchPl
     P.kc = reinterpret_cast<uint16_t *>(kv->k); P.vc = reinterpret_cast<uint16_t *>(kv->v);
     P.kv_batch = kv->batch; P.cap = kv->capacity;
     P.logits = logits_out; P.hidden_out = hidden_out;
-    P.batched = batch >= st.batched_from ? 1 : 0;
+    P.batched = batch >= st.lds.batched_from ? 1 : 0;
     // (several sequences share a GEMV pass; the partial sums' place differs
     // between the two paths)
-    P.multi = !P.batched && batch >= 2 && batch <= kMultiSeq && st.multi_ok ? 1 : 0;
-    P.lds_red = P.batched ? st.lds_red : st.lds_red_seq;
-    if (P.multi && st.lds_mm) P.multi = 2;
-    P.lds_mm = st.lds_mm;
+    P.multi = !P.batched && batch >= 2 && batch <= st.lds.multi ? 1 : 0;
+    P.lds_red = P.batched ? st.lds.red : st.lds.red_seq;
+    if (P.multi && st.lds.mm) P.multi = 2;
+    P.lds_mm = st.lds.mm;
+    P.o_heads = P.multi ? o_heads_for(st.cfg, batch, st.lds.red_seq) : P.nq;
     return P;
 }
 
@@ -747,7 +653,7 @@ static kl_status launch_layer_graph(kl_state *st, const StepParams &P, hipStream
         st->graph = nullptr;
         HIP_TRY(hipGraphCreate(&st->graph, 0));
         const bool bat = P.batched != 0;
-        const int lds = st->lds_bytes;
+        const int lds = st->lds.bytes;
         hipGraphNode_t prev = nullptr, node = nullptr;
         HIP_TRY(add_step_node(st->graph, &node, nullptr, P, 0, 0, kPhEmbed, false, lds));
         for (int l = 0; l < P.L; ++l) {
@@ -803,7 +709,7 @@ static kl_status enqueue_step(kl_state *st, const int32_t *token_ids, const int3
         return launch_layer_graph(st, P, s);
     }
     if (no_alloc) HIP_TRY(launch_zero(base, plan.total, s));
-    HIP_TRY(launch_schedule(P, mode, st->lds_bytes, s));
+    HIP_TRY(launch_schedule(P, mode, st->lds.bytes, s));
     return KL_OK;
 }
 
@@ -852,7 +758,7 @@ kl_status kl_decode_greedy(kl_state *st, const int32_t *token_ids, const int32_t
         P.amax_next = keys(n + 1);
         P.tok_keys = n == 0 ? nullptr : keys(n - 1);
         P.tok_emit = n == 0 ? nullptr : tokens_out + (size_t)(n - 1) * batch;
-        HIP_TRY(launch_schedule(P, mode, st->lds_bytes, s));
+        HIP_TRY(launch_schedule(P, mode, st->lds.bytes, s));
     }
     HIP_TRY(launch_emit_tokens(tokens_out + (size_t)(n_steps - 1) * batch, keys(n_steps - 1),
                                keys(0), batch, s));
@@ -908,9 +814,9 @@ kl_status kl_get_info(const kl_state *st, kl_info *info) {
     if (!st || !info) return fail(KL_ERR_INVALID_ARGUMENT, "state and info must not be NULL");
     info->n_workgroups = st->nwg;
     info->threads_per_group = kThreads;
-    info->lds_bytes = st->lds_bytes;
+    info->lds_bytes = st->lds.bytes;
     info->attn_chunks_b1 = std::max(1, st->Sg);
-    info->mfma_min_batch = st->batched_from;
+    info->mfma_min_batch = st->lds.batched_from;
     info->arena_bytes = (int64_t)st->arena_bytes;
     info->scratch_bytes = (int64_t)st->scratch_bytes;
     info->noalloc_scratch_bytes = (int64_t)plan_scratch(*st, st->cfg.max_batch, true).base;

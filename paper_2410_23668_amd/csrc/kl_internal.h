@@ -5,51 +5,12 @@
 #include <hip/hip_runtime.h>
 
 #include "kl_layout.h"
+#include "kl_lds.h"
 #include "kl_sync.h"
 #include <stddef.h>
 #include <stdint.h>
 
 namespace kl {
-
-// Work geometry shared by host and device.
-constexpr int kWaves = 8;                 // compute waves per workgroup
-constexpr int kCtlWave = kWaves;          // the control wave: barriers and counters only
-constexpr int kThreads = (kWaves + 1) * 64;   // threads per workgroup
-constexpr int kRgBatch = 16;              // row groups reduced per LDS round
-// Batched steps (the matrix-core path) run the weight products on the matrix
-// cores.  An activation x enters them as two bf16 terms, hi = bf16(x) and
-// lo = bf16(x - hi), both multiplied into the same fp32 accumulators (about
-// 16 significant bits of x instead of 8).  Activations are staged in LDS in
-// chunks of kGemmChunkK columns for up to kGemmBatch sequences at a time,
-// weight rows in blocks of 16.
-constexpr int kMfmaBatch = 8;
-// Up to kMultiSeq sequences share one pass of the GEMV engine: each weight
-// tile is applied to every staged vector, so the weights stream once.  8
-// layers of the 8B shape, 4096 cached positions, batch 4: 1162 us with the
-// pass on the matrix cores, 1195 on the vector units.  Against the matrix-core
-// engine the vector-unit pass took 4.35 ms to 5.0 for all 32 layers, both
-// before the residual rows had owners.  Dense models take that engine from
-// batch kMultiSeq + 1 on, or from kBatchedFrom where the LDS cannot hold the
-// shared pass's vectors beside its area (one sequence per pass: 5.61 ms at
-// batch 2).  A mixture of experts keeps the GEMV path below kMfmaBatch (its
-// experts are chosen per token on that path).
-constexpr int kMultiSeq = 4;
-constexpr int kBatchedFrom = 2;
-constexpr int kGemmBatch = 32;
-constexpr int kGemmChunkK = 512;
-constexpr int kActStride = kGemmChunkK + 8;   // bf16 per staged activation row (bank spread)
-constexpr int kGemmMaxBlk = 4;            // 16-row blocks per wave per pass over the weights
-constexpr int kMaxKSlices = 16;           // K slices of a batched product (partial sums)
-constexpr int kGemmResidentK = 2 * kGemmChunkK;   // K columns a workgroup keeps resident
-// LDS of the batched path (bytes): two activation chunks of both terms, and
-// per-wave weight re-layout slots (2 KiB)
-constexpr int kGemmActBytes = kGemmBatch * kActStride * 2;   // one term of one chunk
-constexpr int kGemmLdsBytes = 4 * kGemmActBytes + kWaves * 2048;
-constexpr int kNormCntStride = 64;        // words between batched RMSNorm slice counters
-constexpr int kMaxGroup = 8;              // max query heads per KV head
-constexpr int kDownGather = 8;            // tagged words per control-wave lane per gather round
-constexpr int kBarGroups = kSyncBarGroups;   // first level of the grid barrier
-constexpr int kBarBytes = 8192;           // barrier counters: kBarGroups lines of 256 B
 
 // Phase selection bits of one launch of the step kernel.
 enum : int {
@@ -128,7 +89,7 @@ struct StepParams {
                                // then new value (d/2 words: bf16 dims 2j, 2j + 1)
     unsigned long long *po_ll; // attention parts, [nkv][Sg + B][group][d + 2]: outputs, max
                                // (log2 units) and sum (batched path: [nkv][Sg][..])
-    unsigned long long *o_ll;  // [B][nq*d] merged attention output (fp32)
+    unsigned long long *o_ll;  // [parts of o_heads][B][heads][d] merged attention output (fp32)
     unsigned long long *xa_ll, *xb_ll;   // [B][Hp] residual after the attention, after the
                                // layer (fp32; layer l's input has tag epoch + l)
     unsigned long long *dp_ll; // [B][topk Sc][Hp] down projection's partial sums (fp32)
@@ -149,6 +110,7 @@ struct StepParams {
     int multi;                 // per-sequence path: the B <= kMultiSeq sequences share each
                                // GEMV pass (1), on the matrix cores (2) (set by the host)
     int lds_mm;                // multi = 2: the waves' weight re-layout slots (float offset)
+    int o_heads;               // heads that the O projection stages at a time
     unsigned long long *trace; // optional phase timestamps (see kl_set_trace), or null
     int trace_max;             // phases recorded per launch
 };

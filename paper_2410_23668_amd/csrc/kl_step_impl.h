@@ -2718,6 +2718,16 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
     lds_barrier();   // (the attention area is the next phase's)
 }
 
+// Query head h's merged outputs of sequence b.  The O projection stages them
+// P.o_heads heads at a time: the words of such a part, of all sequences, are
+// contiguous.
+__device__ __forceinline__ unsigned long long *o_words(const StepParams &P, int b, int h, int d) {
+    int h0 = 0;
+    while (h - h0 >= P.o_heads) h0 += P.o_heads;
+    const int n = min(P.o_heads, P.nq - h0);
+    return P.o_ll + ((size_t)P.B * h0 + (size_t)b * n + (h - h0)) * d;
+}
+
 // Per-sequence path, one wave: the merged attention outputs of sequence b that
 // this workgroup hands on, o = sum_c w_c A_c / sum_c w_c L_c with w_c = 2^(M_c - M),
 // M the largest of the parts' maxima (A_c, M_c, L_c the parts' unnormalised
@@ -2786,7 +2796,7 @@ __device__ __forceinline__ void merge_parts(const StepParams &P, int l, int b) {
                 O = O * al + o;
                 M = mn;
             }
-            if (lane < MD) st_ll_f(P.o_ll + (size_t)b * P.nq * D + h * D + d0 + j, O / L, tag);
+            if (lane < MD) st_ll_f(o_words(P, b, h, D) + d0 + j, O / L, tag);
         }
     }
 }
@@ -2861,34 +2871,61 @@ __device__ __forceinline__ void phase_oproj(KArg ka, int l, int gwait, int garri
             if (is_ctl_lane0()) trace_stamp(P, ti, 2);
             lds_barrier();   // (as in owners_wait)
         };
-        auto stage = [&](int b) {
-            // (the control wave leaves the gather to the others, whose rings
-            // are done by then; with P.multi all sequences' outputs, b K
-            // floats apart)
-            auto word = [&](int i) { return P.o_ll + (size_t)b * K + i; };
-            auto put = [&](int i, unsigned v) {
-                if (P.multi == 2) {
-                    const int q = (i >= K) + (i >= 2 * K) + (i >= 3 * K);
-                    mm_put(mm_act(S), mm_stride(K), q, i - q * K, __uint_as_float(v));
-                }
-                else S.a[i] = __uint_as_float(v);
-            };
-            if (!P.multi) ll_gather<8>(P, K, tag, kl_tid(), kThreads, word, put);
-            else if (b == 0) ll_gather<16>(P, P.B * K, tag, kl_tid(), kThreads, word, put);
-            if (!P.multi || b == P.B - 1) lds_barrier();
-            if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
-        };
         auto epi = [&](int b, int r, double y0, double y1) {
             const long long *x = own_x(P) + b * P.own_max + (r - R.first);
             put_x(P, b, r - R.first, R, x[0] + to_fix(y0), P.xa_ll, tag);
             put_x(P, b, r + 1 - R.first, R, x[1] + to_fix(y1), P.xa_ll, tag);
         };
-        if (P.multi)
-            gemv_phase<true, KTq>(Wo, KT, R.first / kTileRows, R.count / kTileRows, P.B, S.a, S.red,
-                                  P.dummy, wait, stage, epi, K, P.o_rg * KTq, mm_slots(P, S));
-        else
-            gemv_phase<false, KTq>(Wo, KT, R.first / kTileRows, R.count / kTileRows, P.B, S.a, S.red,
-                                   P.dummy, wait, stage, epi, 0, P.o_rg * KTq);
+        if (P.multi) {
+            // (a part of the heads at a time, where LDS cannot hold the
+            // outputs of all: the sums of the parts but the last are added to
+            // the owned residual without publishing it)
+            for (int h0 = 0; h0 < P.nq; h0 += P.o_heads) {
+                const int nh = min(P.o_heads, P.nq - h0), Kp = nh * D;
+                gemv_phase<true, KTq>(
+                    Wo + (size_t)h0 * P.o_rg * KTq * kTileBytes, nh * KTq,
+                    R.first / kTileRows, R.count / kTileRows, P.B, S.a, S.red, P.dummy,
+                    [&]() { if (h0 == 0) wait(); },
+                    [&](int b) {
+                        // (the control wave leaves the gather to the others,
+                        // whose rings are done by then; all sequences'
+                        // outputs, b Kp floats apart)
+                        if (b == 0)
+                            ll_gather<16>(
+                                P, P.B * Kp, tag, kl_tid(), kThreads,
+                                [&](int i) { return P.o_ll + (size_t)P.B * h0 * D + i; },
+                                [&](int i, unsigned v) {
+                                    if (P.multi == 2) {
+                                        const int q = (i >= K) + (i >= 2 * K) + (i >= 3 * K);
+                                        mm_put(mm_act(S), mm_stride(K), q, i - q * K,
+                                               __uint_as_float(v));
+                                    } else {
+                                        S.a[i] = __uint_as_float(v);
+                                    }
+                                });
+                        if (b == P.B - 1) lds_barrier();
+                        if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
+                    },
+                    [&](int b, int r, double y0, double y1) {
+                        if (h0 + nh == P.nq) return epi(b, r, y0, y1);
+                        long long *x = own_x(P) + b * P.own_max + (r - R.first);
+                        x[0] += to_fix(y0);
+                        x[1] += to_fix(y1);
+                    },
+                    Kp, P.o_rg * KTq, mm_slots(P, S));
+            }
+        } else {
+            gemv_phase<false, KTq>(
+                Wo, KT, R.first / kTileRows, R.count / kTileRows, P.B, S.a, S.red, P.dummy, wait,
+                [&](int b) {
+                    ll_gather<8>(P, K, tag, kl_tid(), kThreads,
+                                 [&](int i) { return P.o_ll + (size_t)b * K + i; },
+                                 [&](int i, unsigned v) { S.a[i] = __uint_as_float(v); });
+                    lds_barrier();
+                    if (b == 0 && is_ctl_lane0()) trace_stamp(P, ti, 3);
+                },
+                epi, 0, P.o_rg * KTq);
+        }
         if (is_ctl_lane0()) trace_stamp(P, ti, 0);
     }
     if (garrive >= 0) bar_arrive(P, garrive, ti);

@@ -74,6 +74,13 @@ def test_swiglu_in_the_gate_up_epilogue(hidden, batch):
     (dict(hidden=1040, ffn_dim=1096, head_dim=128), 2),
     (dict(hidden=520, ffn_dim=264, n_experts=4, top_k=2), 3),
     (dict(hidden=6152, ffn_dim=520), 3),               # too wide for LDS: the vector-unit form
+    # heads whose outputs do not fit in LDS for all sequences: the O projection
+    # in 2 or 3 parts of them, or (matrix cores busy from batch 4 on) in one
+    (dict(hidden=264, head_dim=128, n_heads=72, n_kv_heads=9, ffn_dim=200), 4),
+    (dict(hidden=2560, n_heads=150, n_kv_heads=75, ffn_dim=264), 4),
+    (dict(hidden=520, head_dim=128, n_heads=200, n_kv_heads=25, ffn_dim=264), 3),
+    (dict(hidden=4096, head_dim=128, n_heads=128, n_kv_heads=16, ffn_dim=264), 2),
+    (dict(hidden=264, head_dim=128, n_heads=72, n_kv_heads=9, ffn_dim=200, n_experts=4, top_k=2), 4),
 ], ids=str)
 def test_sequences_sharing_a_pass(over, batch):
     """Batches of 2 to 4 take each weight pass together: on the matrix cores
@@ -83,6 +90,9 @@ def test_sequences_sharing_a_pass(over, batch):
     say(f"[shared pass] {over} batch {batch}")
     filled = (np.arange(batch, dtype=np.int32) * 29 + 3) % 90
     c = Case(cfg, batch, 128, filled, seed=511 + batch)
+    # (not one sequence per pass, nor the matrix-core path from batch 2 on)
+    want = 8 if "n_experts" in over else (3 if over.get("n_heads") == 128 else 5)
+    assert c.model.info().mfma_min_batch == want
     ref = c.oracle_step(nthreads=8)
     # (a mixture of experts has no per-op schedule)
     modes = [m for m in MODES if not ("n_experts" in over and m[1] == kb.KL_MODE_PER_OP)]
