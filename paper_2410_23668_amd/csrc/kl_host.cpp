@@ -387,7 +387,7 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     S->own_max = (S->o_rg + S->nwg - 1) / S->nwg * kTileRows;
     S->lds = lds_layout_for(c, Gm, S->own_max,
                             matrix_cores_fill(S->o_rg / 2, S->KSo, S->KSd, S->nwg));
-    if (S->lds.bytes > kLdsMost)
+    if (!lds_fits(S->lds) || 2 * S->Hp + d > kMaxHiddenVec)
         return bail(fail(KL_ERR_UNSUPPORTED, "LDS need %d bytes exceeds 160 KiB", S->lds.bytes));
     int per_cu = 0;
     TRY(step_kernel_setup(c.head_dim, c.n_heads / c.n_kv_heads, S->lds.bytes, &per_cu));

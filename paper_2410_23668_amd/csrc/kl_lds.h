@@ -50,7 +50,8 @@ constexpr int kDownGather = 8;            // tagged words per control-wave lane 
 constexpr int kBarGroups = kSyncBarGroups;   // first level of the grid barrier
 constexpr int kBarBytes = 8192;           // barrier counters: kBarGroups lines of 256 B
 constexpr int kMaxOParts = 4;             // parts of the heads in a shared O projection
-constexpr int kLdsMost = 160 * 1024 - 256;   // bytes of LDS a step may take
+constexpr int kLdsMost = 160 * 1024;      // bytes of LDS a step may take
+constexpr int kMaxHiddenVec = 39660;      // largest 2 Hp + head_dim that is taken
 
 // FFN column blocks: the largest divisor of the k-tile count of ffn_dim that
 // is at most 32 (and at most the grid).
@@ -107,6 +108,7 @@ struct LdsLayout {
     int sm, bar;
     int bytes;
 };
+inline bool lds_fits(const LdsLayout &s) { return s.bytes <= kLdsMost; }
 
 // Heads that the O projection stages at a time: all, or the largest of up to
 // kMaxOParts equal parts whose outputs of n sequences fit in 'area' floats.
@@ -127,12 +129,12 @@ inline LdsLayout lds_layout_for(const kl_config &c, const Geometry &G, int own_m
     const int rs = kWaves * kRgBatch * kTileRows;   // one sequence's GEMV partial sums
     // per-sequence path, one sequence per GEMV pass: activations and RoPE row,
     // a SwiGLU block, the merged attention output
-    const int one = round64(std::max({2 * G.Hp + d, G.KTc * kTileK, attn_main, G.Ap}));
+    const int one = round64(std::max({G.Hp + d, G.KTc * kTileK, attn_main, G.Ap}));
     // kMultiSeq sequences per pass, with 'outputs' floats of the merged
     // attention outputs at a time
     const auto multi = [&](int outputs) {
         return round64(std::max({kMultiSeq * (G.Hp + d), kMultiSeq * G.KTc * kTileK, outputs,
-                                 attn_main, 2 * G.Hp + d}));
+                                 attn_main}));
     };
     // The first batch of the matrix-core path: with several sequences per
     // GEMV pass the per-sequence path serves as many sequences (a
@@ -158,13 +160,14 @@ inline LdsLayout lds_layout_for(const kl_config &c, const Geometry &G, int own_m
         s.red = bat_a;
         s.sm = std::max(seq_end, bat_a + rs);
         s.bar = s.sm + 64;
-        // + the step's epoch, position and validity per sequence, the head's
-        // argmax keys of a group of sequences, the experts and their weights
-        // per sequence (two slots), the workgroup's share of the attention, its
-        // residual rows
+        // + the step's epoch, position and validity per sequence, the experts
+        // and their weights per sequence (two slots), the workgroup's share of
+        // the attention, the head's argmax keys of a group of sequences and,
+        // per-sequence path, the workgroup's residual rows (over the keys of
+        // the matrix-core path's larger groups)
         const int seqs = std::min(c.max_batch, s.batched_from - 1);
-        s.bytes = (s.bar + 2 * kBarGroups + 4 + 2 * kMfmaBatch + 2 * kGemmBatch +
-                   4 * kMfmaBatch + 8 + 2 * seqs * own_max) * (int)sizeof(float);
+        s.bytes = (s.bar + 2 * kBarGroups + 4 + 2 * kMfmaBatch + 4 * kMfmaBatch + 8 +
+                   2 * std::max(kMfmaBatch + seqs * own_max, kGemmBatch)) * (int)sizeof(float);
         return s;
     };
     if (c.max_batch >= 2) {
@@ -182,18 +185,17 @@ inline LdsLayout lds_layout_for(const kl_config &c, const Geometry &G, int own_m
         //   hidden 2560, 72 heads, ffn 9728 (one K slice of the down product:
         //     160 blocks in all), batch 2: 733 | 764 | 1186; 3: 814 | 860 |
         //     1245; 4: - | 942 | 1204.
-        const auto fits = [](const LdsLayout &s) { return s.bytes <= kLdsMost; };
         LdsLayout s = layout(kMultiSeq, kMultiSeq * G.Ap, true);
-        if (!fits(s)) s = layout(kMultiSeq, kMultiSeq * G.Ap, false);
-        if (!fits(s) && fills && c.n_experts <= 1) s = layout(2, 2 * G.Ap, false);
-        else if (!fits(s)) {
-            for (int n = kMultiSeq - 1; !fits(s) && n >= 2; --n)
+        if (!lds_fits(s)) s = layout(kMultiSeq, kMultiSeq * G.Ap, false);
+        if (!lds_fits(s) && fills && c.n_experts <= 1) s = layout(2, 2 * G.Ap, false);
+        else if (!lds_fits(s)) {
+            for (int n = kMultiSeq - 1; !lds_fits(s) && n >= 2; --n)
                 if (kMultiSeq * ((c.n_heads + kMaxOParts - 1) / kMaxOParts) * d <= n * G.Ap)
                     s = layout(kMultiSeq, n * G.Ap, false);
-            for (int p = 2; !fits(s) && p <= kMaxOParts; ++p)
+            for (int p = 2; !lds_fits(s) && p <= kMaxOParts; ++p)
                 s = layout(kMultiSeq, kMultiSeq * ((c.n_heads + p - 1) / p) * d, false);
         }
-        if (fits(s)) return s;
+        if (lds_fits(s)) return s;
     }
     return layout(1, 0, false);
 }

@@ -589,7 +589,7 @@ __device__ __forceinline__ float *seq_sm(const StepParams &P, const Lds &S, int 
 // activation vectors.
 __device__ __forceinline__ float *rope_row(const StepParams &P, const Lds &S, int b) {
     if (P.multi == 2) return S.a + kMmCols * mm_stride(P.Hp) / 2 + b * P.d;
-    return S.a + (P.multi ? kMultiSeq * P.Hp + b * P.d : 2 * P.Hp);
+    return S.a + (P.multi ? kMultiSeq * P.Hp + b * P.d : P.Hp);
 }
 
 __device__ __forceinline__ unsigned long long *bar_bases(const StepParams &P) {
@@ -603,24 +603,25 @@ __device__ __forceinline__ unsigned *launch_epoch(const StepParams &P) {
 __device__ __forceinline__ int *seq_table(const StepParams &P) {
     return reinterpret_cast<int *>(lds_layout(kl_smem, P).bar + kBarGroups) + 4;
 }
-// (then: the head's argmax keys of up to kGemmBatch sequences)
-__device__ __forceinline__ unsigned long long *amax_slots(const StepParams &P) {
-    return reinterpret_cast<unsigned long long *>(seq_table(P) + 2 * kMfmaBatch);
-}
 // (then, mixture of experts: per sequence, its two experts and their
 // weights (float bits), chosen in the gate/up phase, used by the down phase)
 __device__ __forceinline__ int *route_table(const StepParams &P) {
-    return reinterpret_cast<int *>(amax_slots(P) + kGemmBatch);
+    return seq_table(P) + 2 * kMfmaBatch;
 }
 
 // (then: the workgroup's share of the attention, see seg_init)
 __device__ __forceinline__ int *seg_table(const StepParams &P) {
     return route_table(P) + 4 * kMfmaBatch;
 }
+// (then: the head's argmax keys of up to kMfmaBatch or, on the matrix-core
+// path, kGemmBatch sequences)
+__device__ __forceinline__ unsigned long long *amax_slots(const StepParams &P) {
+    return reinterpret_cast<unsigned long long *>(seg_table(P) + 8);
+}
 // (then, per-sequence path: the residual rows this workgroup owns, int64
 // fixed point [sequence][own_max])
 __device__ __forceinline__ long long *own_x(const StepParams &P) {
-    return reinterpret_cast<long long *>(seg_table(P) + 8);
+    return reinterpret_cast<long long *>(amax_slots(P) + kMfmaBatch);
 }
 
 // ---------------------------------------------------------------- activations
@@ -3385,7 +3386,8 @@ __device__ __forceinline__ void phase_head(KArg ka, int gwait, int ti) {
     // then one device-scope atomic per sequence into P.amax
     unsigned long long *best = amax_slots(P);
     const bool sample = P.amax != nullptr;
-    if (sample && kl_tid() < kGemmBatch) best[kl_tid()] = 0ull;   // (staging barriers follow)
+    if (sample && kl_tid() < (BAT ? kGemmBatch : kMfmaBatch))
+        best[kl_tid()] = 0ull;   // (staging barriers follow)
     // per-sequence path: this workgroup has read the epoch (bar_init); the
     // answer is used at the end of the phase
     unsigned arrivals = 0;

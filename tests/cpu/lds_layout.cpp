@@ -41,7 +41,7 @@ void shape(int hidden, int d, int group, int ffn, int experts, int batch, bool f
     for (int nkv = 1; nkv * group <= kGrid; nkv += nkv < 8 ? 1 : 5) {
         const kl_config c = config(hidden, d, group, nkv, ffn, experts, batch);
         const LdsLayout s = layout(c, G, fills);
-        if (s.bytes > kLdsMost) continue;   // (refused)
+        if (!lds_fits(s)) continue;   // (refused)
         if (fills && !experts)   // (36000 floats beside 2 sequences' partial sums: 152 KiB)
             check(s.multi == few_heads || s.multi == 2 || (s.multi == 1 && 2 * G.Ap > 36000),
                   "two sequences' outputs fit", c);
@@ -53,7 +53,7 @@ void shape(int hidden, int d, int group, int ffn, int experts, int batch, bool f
             check(at_once > 0 && b * at_once * d <= s.red_seq, "attention outputs", c);
             check(!s.mm || at_once == c.n_heads, "matrix cores: all heads at once", c);
         }
-        check((nb > 1 ? kMultiSeq * G.Hp : 2 * G.Hp) + d * nb <= s.red_seq,
+        check((nb > 1 ? kMultiSeq * G.Hp : G.Hp) + d * nb <= s.red_seq,
               "residual and RoPE rows", c);
         check(nb * G.KTc * kTileK <= s.red_seq, "a SwiGLU block", c);
         check(s.red_seq + nb * kWaves * kRgBatch * kTileRows <= s.sm, "partial sums", c);
@@ -67,6 +67,25 @@ void shape(int hidden, int d, int group, int ffn, int experts, int batch, bool f
     }
 }
 
+// The residual rows a workgroup owns, and the share of the attention, decide
+// neither whether a hidden size is taken (2 Hp + d floats and 5040 bytes of
+// partial sums and tables have to fit in 160 KiB less 256 bytes) nor whether
+// four sequences share a pass (4 (Hp + d) floats and 17328 bytes).
+void rows_do_not_count(const kl_config &c) {
+    const Geometry G = layout_geometry(c, kGrid);
+    const int own = (G.o_rg + kGrid - 1) / kGrid * kTileRows, d = c.head_dim, most = 163584;
+    const auto round64 = [](int v) { return (v + 63) / 64 * 64; };
+    for (bool fills : {false, true}) {
+        const LdsLayout s = lds_layout_for(c, G, own, fills);
+        check(s.bytes <= 160 * 1024 || 2 * G.Hp + d > kMaxHiddenVec, "past the LDS", c);
+        if (c.max_batch == 4)   // (larger batches: the matrix-core path's area as well)
+            check((4 * round64(4 * (G.Hp + d)) + 4 * 4096 + 848 <= most) == (s.multi == 4),
+                  "rows decide the shared pass", c);
+    }
+    check((4 * round64(2 * G.Hp + d) + 4096 + 848 <= most) == (2 * G.Hp + d <= kMaxHiddenVec),
+          "hidden sizes that are taken", c);
+}
+
 }  // namespace
 
 int main() {
@@ -78,6 +97,11 @@ int main() {
                         for (int batch : {1, 2, 4, 32})
                             for (bool fills : {false, true})
                                 shape(hidden, d, group, ffn, experts, batch, fills);
+    for (int hidden = 8192; hidden <= 19968; hidden += 8)
+        for (int d : {64, 128})
+            for (int experts : {0, 8})
+                for (int batch : {1, 2, 4, 7, 32})
+                    rows_do_not_count(config(hidden, d, 4, 8, 11008, experts, batch));
     if (g_fail) return 1;
     std::printf("lds layout OK\n");
     return 0;

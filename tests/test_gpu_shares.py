@@ -126,3 +126,25 @@ def test_k_slices_across_the_slices_of_the_norm(over, batch):
         assert_bit_exact(o, outs[1], f"{what} vs looped")
     assert c.model.device_error() == 0
     c.model.close()
+
+
+@pytest.mark.parametrize("hidden,batch,experts", [(19776, 1, 0), (9024, 4, 0), (19776, 7, 4),
+                                                  (9024, 3, 4)])
+def test_hidden_sizes_that_fill_lds(hidden, batch, experts):
+    """The largest hidden size, and the largest whose sequences share a pass:
+    LDS has to hold the residual rows that a workgroup owns as well."""
+    cfg = dict(TINY, n_layers=3, hidden=hidden, ffn_dim=264)
+    if experts:
+        cfg.update(n_experts=experts, top_k=2)
+    say(f"[full LDS] hidden {hidden} batch {batch} experts {experts}")
+    filled = (np.arange(batch, dtype=np.int32) * 29 + 3) % 90
+    c = Case(cfg, batch, 128, filled, seed=711 + batch)
+    assert c.model.info().mfma_min_batch == (8 if experts else (5 if batch > 1 else 2))
+    ref = c.oracle_step(nthreads=8)
+    modes = [m for m in MODES if not (experts and m[1] == kb.KL_MODE_PER_OP)]
+    outs = {what: c.gpu_step(mode) for what, mode in modes}
+    check_against_oracle(c, outs["looped"], ref)
+    for what, o in outs.items():
+        assert_bit_exact(o, outs["looped"], f"{what} vs looped")
+    assert c.model.device_error() == 0
+    c.model.close()
