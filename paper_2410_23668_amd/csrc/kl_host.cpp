@@ -348,7 +348,9 @@ kl_status kl_model_create(const kl_config *cfg, kl_state **out) {
     if (!coop) return bail(fail(KL_ERR_UNSUPPORTED, "device lacks cooperative launch"));
 
     const int d = c.head_dim, g = c.n_heads / c.n_kv_heads;
-    // (the per-sequence O projection gives every query head workgroups of its own)
+    // (every KV head has workgroups of its own; and the O projection stages the
+    // outputs of all query heads, of one sequence at least: 128 KiB with as many
+    // heads of 128 as there are compute units)
     if (ncu < c.n_heads)
         return bail(fail(KL_ERR_UNSUPPORTED, "n_heads %d exceeds the %d compute units",
                          c.n_heads, ncu));

@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "kl_internal.h"
+#include "kl_shares.h"
 #include "kl.h"
 
 namespace kl {
@@ -2173,23 +2174,8 @@ template <int D> __device__ __forceinline__ constexpr int attn_unit() { return 2
 __device__ __forceinline__ int attn_units_of(int pnew, int up) { return pnew / up + 1; }
 
 // A workgroup's share, in LDS (seg_table): first sequence, its first unit,
-// units of the share, units of the whole batch, workgroups that have shares.
-// On the per-sequence path short shares keep to one sequence each (a second
-// segment costs about 3.5 us, a share's odd units less than that below 96
-// units): sequence b's workgroups are one, and of the others the part that its
-// units have of the batch's.
-constexpr int kSegUnits = 96;
-__device__ __forceinline__ bool seg_by_sequence(const StepParams &P, int T) {
-    return !P.batched && P.B <= P.Sg && T < kSegUnits * P.Sg;
-}
-struct SeqParts { int first, span, count; };   // workgroups of a sequence; those with units
-__device__ __forceinline__ SeqParts seq_parts(const StepParams &P, int b, int before, int units,
-                                              int T) {
-    const int rest = P.Sg - P.B;
-    const int p0 = b + (int)((long long)rest * before / T);
-    const int p1 = b + 1 + (int)((long long)rest * (before + units) / T);
-    return SeqParts{p0, p1 - p0, min(p1 - p0, units)};
-}
+// units of the share, units of the whole batch, workgroups that have shares,
+// whether the shares keep to a sequence each (seg_by_sequence, kl_shares.h).
 // (one wave, once per launch, before the launch's first barrier)
 __device__ __forceinline__ void seg_init(const StepParams &P, int lane) {
     const int up = 2048 / P.d;
@@ -2201,24 +2187,33 @@ __device__ __forceinline__ void seg_init(const StepParams &P, int lane) {
     }
     const int part = blockIdx.x % P.Sg;
     int *t = seg_table(P);
-    const bool whole = seg_by_sequence(P, T);
-    if (whole) {   // (B <= kMfmaBatch: one lane walks the sequences)
-        if (lane == 0) {
-            int b = 0, before = 0, u = 0;
-            SeqParts q{};
-            for (;; ++b, before += u) {
-                u = attn_units_of(eff_pos(P, b), up);
-                q = seq_parts(P, b, before, u, T);
-                if (b + 1 == P.B || part < q.first + q.span) break;
-            }
-            int x0 = 0, x1 = 0;
-            if (part - q.first < q.count) split_range(u, q.count, part - q.first, x0, x1);
-            t[0] = b;
-            t[1] = x0;
-            t[2] = x1 - x0;
-            t[3] = T;
+    if (lane == 0) t[5] = 0;
+    if (!P.batched && P.B > 1 && seg_short(P.Sg, P.B, T)) {   // (B <= kMfmaBatch: a lane a sequence)
+        const int u = lane < P.B ? attn_units_of(eff_pos(P, lane), up) : 0;
+        int before = u;   // inclusive sum
+        for (int off = 1; off < kMfmaBatch; off <<= 1) {
+            const int o = from_lane(before, max(lane - off, 0));
+            before += lane >= off ? o : 0;
         }
-        return;
+        before -= u;
+        const SeqParts q = seq_parts(P.Sg, P.B, lane, before, u, T);
+        int most = lane < P.B ? (u + q.count - 1) / q.count : 0;   // the largest share
+        for (int off = 1; off < kMfmaBatch; off <<= 1) most = max(most, from_lane(most, lane ^ off));
+        if (seg_by_sequence(P.Sg, T, __builtin_amdgcn_readfirstlane(most))) {
+            if (lane < P.B && part >= q.first && part < q.first + q.span) {
+                int x0 = 0, x1 = 0;
+                if (part - q.first < q.count) split_range(u, q.count, part - q.first, x0, x1);
+                t[0] = lane;
+                t[1] = x0;
+                t[2] = x1 - x0;
+            }
+            if (lane == 0) {
+                t[3] = T;
+                t[4] = P.Sg;   // (not used)
+                t[5] = 1;
+            }
+            return;
+        }
     }
     const int np = min(P.Sg, T);
     int a = 0, e = 0;
@@ -2753,8 +2748,8 @@ __device__ __forceinline__ void merge_parts(const StepParams &P, int l, int b) {
     for (int q = 0; q < b; ++q) seq0 += units(q);
     {
         int f, nc;
-        if (seg_by_sequence(P, T)) {
-            const SeqParts q = seq_parts(P, b, seq0, units(b), T);
+        if (__builtin_amdgcn_readfirstlane(seg_table(P)[5])) {
+            const SeqParts q = seq_parts(P.Sg, P.B, b, seq0, units(b), T);
             f = q.first;
             nc = q.count;
         } else {

@@ -28,6 +28,8 @@ CASES = [
     ("d128 long and short", D128, [3000, 1]),
     ("d128 batched long and short", D128, [0, 2900, 16, 15, 1, 800]),
     ("4 workgroups per head", MHA, [70, 0, 33]),
+    ("one long context, 4 workgroups per head", MHA, [3000, 10, 3, 40]),
+    ("one long context, 128 workgroups per head", D128, [3, 2500, 40]),
     ("more sequences than workgroups per head", MHA, [5, 64, 0, 31, 200, 1, 32]),
     ("2 workgroups per head", dict(MHA, n_heads=128, n_kv_heads=128), [40, 0, 100]),
     ("8 heads per KV head", G8, [1000, 17]),
