@@ -156,7 +156,12 @@ __device__ __forceinline__ void split_range(int n, int parts, int i, int &a, int
 // ones.  Under a full read stream the odd XCD of each pair gets 8 to 10 % less
 // of the bandwidth: with equal shares the 70B shape's gate/up product ended
 // after 128 us on even XCDs and 140 us on odd ones, the 8B shape's LM head
-// after 140 and 152.  (Shares of a few rows come out equal.)
+// after 140 and 152.  (Bounds are rounded down: with part 0 on an even XCD,
+// shares of a few rows come out equal; with part 0 on an odd one, as some FFN
+// column blocks of an odd number of workgroups, a share below 25 rows that
+// divides evenly leans by a row, 44 rows in 11 parts as 3 and 5 in turn.
+// Rounding it to equal shares was measured level: hidden 1024, ffn 1472, 8
+// layers 277 us either way.)
 __device__ __forceinline__ void split_rows(int n, int parts, int i, int &a, int &b) {
     const int odd = (blockIdx.x - i) & 1;   // XCD parity of part 0
     const auto bound = [&](int k) {
