@@ -2147,7 +2147,8 @@ __device__ __forceinline__ void phase_qkv(KArg ka, int l, int gwait, int qbar, i
 // from 49 to 86 us).
 //
 // A compute wave takes every kWaves-th unit of a segment and keeps the loads
-// of two units in flight (16 KiB; 128 KiB per workgroup, across segments).
+// of two units' keys in flight, and of one or two units' values (VD in
+// attn_units; 12 or 16 KiB, 96 or 128 KiB per workgroup, across segments).
 // Both products run on the matrix cores, in layouts that need no exchange
 // between lanes:
 //   scores  v_mfma_f32_16x16x32_bf16, A = 16 key rows (16 bytes of a row per
@@ -2326,9 +2327,13 @@ __device__ __forceinline__ void attn_units(KArg ka, int l, int g, int part, int 
         // position of score register s (0 .. 3): D = 128: slab s, position k;
         // D = 64: slab s, position 2 k (columns 0-7) or 2 k + 1 (columns 8-15)
         const int sp = D == 128 ? k4 : 2 * k4 + (n >> 3);
-        // units whose values are in flight (per-sequence path: one, where two
-        // spilled, and the reloads of spilled registers waited for the rings)
-        constexpr int VD = LL ? 1 : 2;
+        // units whose values are in flight: one where two spilled inside the
+        // unit loop, and the reloads of spilled registers waited for the rings
+        // (per-sequence path; D = 64, with the queries' third term: 8 layers
+        // of hidden 2048, 32 heads of 64 on 8 KV heads, batch 8, contexts 2000
+        // 691 -> 667 us, batch 32 961 -> 927; 4 layers with 32 KV heads, batch
+        // 8, 4000 565 -> 517, batch 32, 2000 828 -> 746)
+        constexpr int VD = LL || D == 64 ? 1 : 2;
         u32x4 kr[2][4], vr[VD][4];
         const uint16_t *kb = nullptr, *vb = nullptr;
         // the current segment: its sequence's units, its end and the end of
