@@ -113,9 +113,9 @@ kl_status validate_config(const kl_config *c) {
 
 // Step scratch for a batch of B sequences (byte offsets from its base; every
 // region 256-byte aligned):
-//   grid barrier counters (16 groups, 256 B apart) and the local counters:
-//     qkv and attention per KV head, gate/up per FFN column block, and at
-//     matrix-core steps the batched RMSNorm slice counters (256 bytes apart);
+//   grid barrier counters (16 groups, 256 B apart) and, for the matrix-core
+//     path, the local counters: q/k/v per KV head, the RMSNorm slices (256
+//     bytes apart);
 //   the residual stream, int64 fixed point [B][Hp];
 //   the per-sequence path's tagged words (8 bytes each, for up to
 //     kMfmaBatch - 1 sequences): rotated queries [B][nq d], the new key and
@@ -160,9 +160,8 @@ ScratchPlan plan_scratch(const kl_state &S, int B, bool exact) {
         return o;
     };
     const int nslices = (S.Hp + kGemmChunkK - 1) / kGemmChunkK;
-    const int norm_cnts = p.batched ? kNormCntStride * nslices : 0;
     p.off_bar = take(kBarBytes);
-    p.off_cnt = take((size_t)(2 * nkv + S.Sc + norm_cnts) * 4);
+    p.off_cnt = take(p.batched ? (size_t)(nkv + kNormCntStride * nslices) * 4 : 0);
     p.off_cnt_end = so;
     p.off_x = take((size_t)B * S.Hp * 8);
     // sequences of a per-sequence step

@@ -25,7 +25,7 @@ struct StepParams {
     int L, H, nq, nkv, d, F, V, group;
     int Hp, Ap, Fp;            // K extents padded to kTileK: hidden, n_heads*d, ffn
     int qkv_rg;                // row groups of one KV head's q/k/v block
-    int o_rg;                  // row groups of one KV head's O-projection block (H / 8)
+    int o_rg;                  // row groups of the O projection (H / 8)
     int gu_rg;                 // row groups of the gate/up matrix (2 F / 8)
     int down_rg;               // row groups of one FFN column block of the down matrix
     int head_rg;               // row groups of the LM head
@@ -98,10 +98,10 @@ struct StepParams {
     // batched path: activations as bf16 hi and lo terms (hi + lo ~ the fp32 value)
     uint16_t *act, *act_lo;    // [max_batch][Hp] normalised activations
     uint16_t *actm, *actm_lo;  // [max_batch][Fp] SwiGLU output
-    uint16_t *acto, *acto_lo;  // [max_batch][nq*d] attention output, when C == 1
+    uint16_t *acto, *acto_lo;  // [max_batch][nq*d] attention output
     unsigned long long *bar;   // grid barrier counters (monotonic): group g at [32 (g + 1)]
-    unsigned *cnt;             // local counters: [nkv] qkv, [nkv] attention, [Sc] gate/up,
-                               // then the batched RMSNorm slices (256 bytes apart)
+    unsigned *cnt;             // matrix-core path's local counters: [nkv] q/k/v, then the
+                               // RMSNorm slices (256 bytes apart)
     int *err;                  // device error word
     const uint8_t *dummy;      // 16 readable bytes: target of the GEMV ring's spare loads
     int nwg;                   // grid size

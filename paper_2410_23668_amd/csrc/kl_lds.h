@@ -45,7 +45,6 @@ constexpr int kGemmResidentK = 2 * kGemmChunkK;   // K columns a workgroup keeps
 constexpr int kGemmActBytes = kGemmBatch * kActStride * 2;   // one term of one chunk
 constexpr int kGemmLdsBytes = 4 * kGemmActBytes + kWaves * 2048;
 constexpr int kNormCntStride = 64;        // words between batched RMSNorm slice counters
-constexpr int kMaxGroup = 8;              // max query heads per KV head
 constexpr int kDownGather = 8;            // tagged words per control-wave lane per gather round
 constexpr int kBarGroups = kSyncBarGroups;   // first level of the grid barrier
 constexpr int kBarBytes = 8192;           // barrier counters: kBarGroups lines of 256 B

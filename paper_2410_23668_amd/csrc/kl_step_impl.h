@@ -62,12 +62,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 
 // The two bf16 terms of a matrix-core activation: hi = bf16(x), lo =
 // bf16(x - hi) (x - hi is exact in fp32), so hi + lo = x (1 + O(2^-17)).
-// Two values per call, packed as (x0 | x1 << 16).
-__device__ __forceinline__ void split_bf16x2(float x0, float x1, unsigned &hi, unsigned &lo) {
-    const uint16_t h0 = f2bf(x0), h1 = f2bf(x1);
-    hi = (unsigned)h0 | ((unsigned)h1 << 16);
-    lo = (unsigned)f2bf(x0 - bf2f(h0)) | ((unsigned)f2bf(x1 - bf2f(h1)) << 16);
-}
 __device__ __forceinline__ void split_bf16(float x, uint16_t &hi, uint16_t &lo) {
     hi = f2bf(x);
     lo = f2bf(x - bf2f(hi));
@@ -88,12 +82,6 @@ __device__ __forceinline__ float sum8(float v) {
     return v;
 }
 __device__ __forceinline__ float sum16(float v) { v = sum8(v); return v + dpp<0x140>(v); }
-
-template <int LP>
-__device__ __forceinline__ float sum_lanes(float v) {
-    if constexpr (LP == 8) return sum8(v);
-    else return sum16(v);
-}
 
 // op(v, v of lane ^ 16) and op(v, v of lane ^ 32) by the row and half swaps
 // of gfx950.  (The shuffle built on the lane index keeps that index live across
@@ -267,11 +255,6 @@ __device__ __forceinline__ unsigned long long ld_dev_u64(const void *p) {
     return __hip_atomic_load(reinterpret_cast<unsigned long long *>(const_cast<void *>(p)),
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ u32x4 ld_dev_16B(const void *p) {
-    const unsigned long long a = ld_dev_u64(p);
-    const unsigned long long b = ld_dev_u64(reinterpret_cast<const char *>(p) + 8);
-    return u32x4{(unsigned)a, (unsigned)(a >> 32), (unsigned)b, (unsigned)(b >> 32)};
-}
 __device__ __forceinline__ u32x4 ld_stream_16B(const void *p) {
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
 }
@@ -433,21 +416,6 @@ __device__ __forceinline__ void bar_wait(const StepParams &P, int k, int ti) {
     __syncthreads();
 }
 
-// Wait until a local counter (monotonic within a step; zeroed by the
-// embedding phase) reaches target.
-__device__ __forceinline__ void local_wait(const StepParams &P, const unsigned *cnt,
-                                           unsigned target, int ti) {
-    if (is_ctl_lane0()) {
-        trace_stamp(P, ti, 1);
-        spin_until(P, [&]() {
-            return (int)(__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
-                         target) >= 0;
-        });
-        trace_stamp(P, ti, 2);
-    }
-    __syncthreads();
-}
-
 // ---------------------------------------------------------------- tagged hand-offs
 //
 // On the per-sequence path, values that cross workgroups inside a layer (the
@@ -583,13 +551,10 @@ __device__ __forceinline__ void mm_put(uint16_t *x, int stride, int b, int i, fl
         v -= bf2f(h);
     }
 }
-// Per-sequence path: with P.multi the B sequences share each GEMV pass and
-// sequence b's staged vector sits b stride floats into the activation area
-// (its wave sums of squares b kSmSeq floats into sm); otherwise every
-// sequence is staged at the start of the area in turn.
-__device__ __forceinline__ float *seq_vec(const StepParams &P, const Lds &S, int b, int stride) {
-    return S.a + (P.multi ? b * stride : 0);
-}
+// Per-sequence path: with P.multi the B sequences share each GEMV pass, their
+// staged vectors one after the other in the activation area (sequence b's wave
+// sums of squares b kSmSeq floats into sm); otherwise every sequence is staged
+// at the start of the area in turn.
 __device__ __forceinline__ float *seq_sm(const StepParams &P, const Lds &S, int b);
 // The Q/K/V phase's staged RoPE row (cos, sin) of sequence b: after the
 // activation vectors.
@@ -632,21 +597,10 @@ __device__ __forceinline__ long long *own_x(const StepParams &P) {
 
 // ---------------------------------------------------------------- activations
 
-// Control wave only: copy 'bytes' (a multiple of 16; src and dst 16-byte
-// aligned) from device memory straight to LDS (global_load_lds, 16 bytes per
-// lane, device-coherent: cache-policy bits sc1), then wait for the copy.  The
-// control wave has no weight loads in flight, so the copy does not queue
-// behind them.
+// Cache-policy bits (sc1, device-coherent) of the copies from device memory
+// straight to LDS (global_load_lds, 16 bytes per lane), and the wait for a
+// wave's copies.
 constexpr int kLdsCoherent = 16;
-__device__ __forceinline__ void ctl_copy_to_lds(const void *src, void *dst, int bytes) {
-    const int lane = kl_tid() & 63;
-    const char *s = static_cast<const char *>(src);
-    char *d = static_cast<char *>(dst);
-    for (int off = 0; off < bytes; off += 64 * 16) {
-        if (off + lane * 16 < bytes)
-            __builtin_amdgcn_global_load_lds(s + off + lane * 16, d + off, 16, 0, kLdsCoherent);
-    }
-}
 __device__ __forceinline__ void ctl_copy_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // Activation staging: loads are issued in batches of kStageBatch per thread
@@ -1681,7 +1635,7 @@ __device__ __forceinline__ void weight_phase(const StepParams &P, const Lds &S,
 // control wave and the items' atomics contend (measured slower than the
 // grid barrier).
 __device__ __forceinline__ unsigned *norm_cnt(const StepParams &P) {
-    return P.cnt + 2 * P.nkv + P.Sc;
+    return P.cnt + P.nkv;
 }
 __device__ __forceinline__ void norm_batched(const StepParams &P, const Lds &S,
                                              const float *gain, const long long *xin,
@@ -1920,11 +1874,10 @@ __device__ __forceinline__ void phase_embed(KArg ka, int gwait, int garrive, int
             if (P.tok_emit) P.tok_emit[b] = t;
             if (P.amax) st_dev_u64(P.amax_next + b, 0ull);
         }
-        // (the batched RMSNorm counters exist, and are used, in batched steps only)
-        const int nc = 2 * P.nkv + P.Sc +
-                       (P.batched ? kNormCntStride * ((P.Hp + kGemmChunkK - 1) / kGemmChunkK) : 0);
-        for (int i = kl_tid(); i < nc; i += kThreads)
-            __hip_atomic_store(P.cnt + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int nc = P.nkv + kNormCntStride * ((P.Hp + kGemmChunkK - 1) / kGemmChunkK);
+        if (P.batched)   // (the local counters are used by batched steps only)
+            for (int i = kl_tid(); i < nc; i += kThreads)
+                __hip_atomic_store(P.cnt + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!P.batched) {   // every workgroup its own residual rows, published as layer 0's input
         const OwnRows R = own_rows(P);
