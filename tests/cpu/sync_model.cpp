@@ -23,13 +23,20 @@
 //      no column whose slice is not complete, for K ranges that start and end
 //      anywhere in a slice;
 //   6. the epoch: in a launch of the step's last phase alone, a workgroup that
-//      starts after others are done still finds the step's own tags.
+//      starts after others are done still finds the step's own tags;
+//   7. the token loop's argmax keys: a step's maximum is its own;
+//   8. reuse of the per-sequence path's word buffers: eight buffers written
+//      again in every layer without any barrier, each phase reading and writing
+//      what the kernel's does (workgroups without rows in a phase read
+//      nothing in it): no word is overwritten before its last reader has it.
 // Prints "sync model OK" and exits 0, else prints the failure and exits 1.
 // With --plant-early-barrier it runs check 1 with a planted off-by-one barrier
 // target, with --plant-one-slice check 5 with a chunk that waits for the slice
 // of its first column alone, with --plant-early-epoch check 6 with the epoch
 // advanced by workgroup 0 when it is done, with --plant-own-keys check 7 with
-// each step clearing its own set of keys, which the check (or ThreadSanitizer) must report.
+// each step clearing its own set of keys, with --plant-idle-reader check 8 with
+// a workgroup that reads a layer's input without having rows of its product,
+// which the check (or ThreadSanitizer) must report.
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -51,6 +58,7 @@ int g_fail = 0;
 int g_plant = 0;   // a planted mistake; 1: barrier k waits for barrier k - 1's target
 int g_plant_slice = 0;   // 1: a chunk waits for one slice
 int g_plant_keys = 0;    // 1: a step clears the keys it takes its own maximum into
+int g_plant_idle = 0;    // 1: a workgroup without rows reads the residual
 int g_plant_epoch = 0;   // 1: workgroup 0 advances the epoch when it is done
 void check(bool ok, const char *what) {
     if (!ok) {
@@ -185,7 +193,7 @@ void test_tagged(int nwg, int steps, int layers, unsigned first_epoch) {
                     }
                     if (ll_value(v) != (unsigned)(s * 7919 + l * 131 + i)) G.err.store(3);
                 }
-                // the kernel separates a buffer's reuse by a grid barrier
+                // (here a grid barrier separates the buffer's uses; without: 8)
                 me.arrive();
                 if (!me.wait(l)) return;
             }
@@ -350,6 +358,111 @@ void test_keys(int nwg, const std::vector<int> &loops) {
     check(bad.load() == 0, "keys: every workgroup reads the step before's maximum");
 }
 
+// 8. one step of the per-sequence path at a time: nwg workgroups, of which the
+// last has no rows in the layers; B sequences, each in its turn inside a phase
+// (a pass that they share reads and writes the same words at once)
+struct Words {
+    std::vector<std::atomic<unsigned long long>> w;
+    explicit Words(int n) : w(n) { for (auto &x : w) x.store(0); }
+};
+void test_reuse(int B, int steps, int layers, unsigned seed) {
+    // owners of the residual rows: workgroups 0 .. 2, two rows each; q/k/v and
+    // attention: 2 heads of 3 workgroups, the third without units; merge: one
+    // output per workgroup 0 .. 3; FFN: 2 column blocks of 3 workgroups, the
+    // first of a block without gate/up rows, the last without down rows
+    constexpr int kWg = 8, H = 6, Q = 4, P = 2, O = 4, M = 2, J = 2;
+    Words xb(B * H), xa(B * H), q(B * 2 * Q), po(B * 2 * P * 2), o(B * O), m(B * J * M), dp(B * J * H);
+    std::atomic<unsigned> epoch{1}, arrivals{0};
+    std::atomic<int> err{0};
+    for (int s = 0; s < steps; ++s) {
+        const unsigned e = epoch.load();
+        run_threads(kWg, [&](int w) {
+            unsigned rng = seed + 977u * (unsigned)w + 131071u * (unsigned)s;
+            const unsigned mine = epoch.load(std::memory_order_relaxed);
+            auto value = [&](int id, int i, int l) { return (unsigned)(s * 1000003 + l * 1009 + id * 97 + i); };
+            auto pause = [&]() {   // (now and then a workgroup falls far behind)
+                rng = rng * 1664525u + 1013904223u;
+                const int n = (rng >> 20) % 16 == 0 ? 300 : (rng >> 24) % 4;
+                for (int k = 0; k < n; ++k) std::this_thread::yield();
+            };
+            auto put = [&](Words &b, int id, int i, int l) {
+                b.w[i].store(ll_word(value(id, i, l), mine + (unsigned)l), std::memory_order_relaxed);
+            };
+            auto get = [&](Words &b, int id, int i, int l) {
+                for (int spins = 1;; ++spins) {
+                    const unsigned long long v = b.w[i].load(std::memory_order_relaxed);
+                    if (ll_current(v, mine + (unsigned)l)) {
+                        if (ll_value(v) != value(id, i, l)) err.store(3);
+                        return;
+                    }
+                    // (a newer tag: overwritten before this reader had it)
+                    if ((unsigned)(v >> 32) > mine + (unsigned)l || spins >= kSpin) err.store(4);
+                    if (err.load(std::memory_order_relaxed)) return;
+                    std::this_thread::yield();
+                }
+            };
+            const bool owner = w < 3, layer = w < 6;
+            const int g = w / 3, part = w % 3;
+            if (owner)
+                for (int i = 0; i < 2 * B; ++i) put(xb, 0, (i / 2) * H + 2 * w + i % 2, 0);
+            for (int l = 0; l < layers; ++l) {
+                pause();
+                if (layer || (g_plant_idle && w == kWg - 1))   // q/k/v
+                    for (int b = 0; b < B; ++b) {
+                        for (int i = 0; i < H; ++i) get(xb, 0, b * H + i, l);
+                        if (!layer) continue;
+                        for (int i = part; i < Q; i += 3) put(q, 1, (b * 2 + g) * Q + i, l);
+                    }
+                pause();
+                if (layer && part < P)                         // attention shares
+                    for (int b = 0; b < B; ++b) {
+                        for (int i = 0; i < Q; ++i) get(q, 1, (b * 2 + g) * Q + i, l);
+                        for (int i = 0; i < 2; ++i) put(po, 2, ((b * 2 + g) * P + part) * 2 + i, l);
+                    }
+                pause();
+                if (w < O)                                     // merge
+                    for (int b = 0; b < B; ++b) {
+                        for (int i = 0; i < 2 * P; ++i) get(po, 2, (b * 2 + w / 2) * P * 2 + i, l);
+                        put(o, 3, b * O + w, l);
+                    }
+                if (owner)                                     // O projection
+                    for (int b = 0; b < B; ++b) {
+                        for (int i = 0; i < O; ++i) get(o, 3, b * O + i, l);
+                        for (int i = 0; i < 2; ++i) put(xa, 4, b * H + 2 * w + i, l);
+                    }
+                pause();
+                if (layer && part > 0)                         // gate/up
+                    for (int b = 0; b < B; ++b) {
+                        for (int i = 0; i < H; ++i) get(xa, 4, b * H + i, l);
+                        put(m, 5, (b * J + g) * M + part - 1, l);
+                    }
+                pause();
+                if (layer && part < 2)                         // down
+                    for (int b = 0; b < B; ++b) {
+                        for (int i = 0; i < M; ++i) get(m, 5, (b * J + g) * M + i, l);
+                        for (int i = 3 * part; i < 3 * part + 3; ++i) put(dp, 6, (b * J + g) * H + i, l);
+                    }
+                if (owner) {                                   // the owners' sums
+                    for (int b = 0; b < B; ++b)
+                        for (int j = 0; j < J; ++j)
+                            for (int i = 0; i < 2; ++i) get(dp, 6, (b * J + j) * H + 2 * w + i, l);
+                    for (int i = 0; i < 2 * B; ++i) put(xb, 0, (i / 2) * H + 2 * w + i % 2, l + 1);
+                }
+            }
+            pause();
+            if (w % 2)                                         // head
+                for (int i = 0; i < B * H; ++i) get(xb, 0, i, layers);
+            if (epoch_last_arrival(arrivals.fetch_add(1), kWg)) {
+                arrivals.store(0);
+                epoch.store(ll_next_epoch(mine, layers + 1));
+            }
+        });
+        check(err.load() == 0, "reuse: every word is read before it is overwritten");
+        check(epoch.load() == ll_next_epoch(e, layers + 1), "reuse: the epoch is advanced once");
+        if (err.load()) return;
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -375,6 +488,11 @@ int main(int argc, char **argv) {
         test_keys(6, {2});
         return g_fail ? 1 : 0;
     }
+    if (argc > 1 && std::string(argv[1]) == "--plant-idle-reader") {
+        g_plant_idle = 1;
+        for (unsigned seed = 1; seed <= 40 && !g_fail; ++seed) test_reuse(1, 4, 6, seed);
+        return g_fail ? 1 : 0;
+    }
     // group sizes: 20 threads on 16 counters (sizes 2 and 1); 5 on 5
     test_barrier(20, 4, 5);
     test_barrier(5, 3, 7);
@@ -390,6 +508,10 @@ int main(int argc, char **argv) {
     test_epoch(8, 6, 3, 5);
     test_epoch(1, 3, 3, 1);
     test_keys(6, {1, 5, 2, 3, 4, 1, 1});
+    for (unsigned seed = 1; seed <= 12; ++seed) {
+        test_reuse(1, 4, 6, seed);
+        test_reuse(3, 3, 5, seed + 100);
+    }
     // the epoch arithmetic on its own
     check(ll_next_epoch(0, 32) == 1, "epoch: 0 restarts at 1");
     check(ll_next_epoch(1, 32) == 33, "epoch: consecutive ranges");

@@ -1,6 +1,7 @@
 """The cross-workgroup protocols of the step kernel (grid barrier with epoch
 recovery, watchdog, tagged hand-offs and their tag ranges, RMSNorm slices, the
-advance of the epoch, the token loop's argmax keys), modelled with host threads
+advance of the epoch, the token loop's argmax keys, the reuse of the
+per-sequence path's words), modelled with host threads
 and std::atomic under ThreadSanitizer, on the library's own protocol arithmetic
 (csrc/kl_sync.h).  CPU only."""
 import os
@@ -51,6 +52,11 @@ def test_model_catches_an_epoch_advanced_before_every_read(model):
 def test_model_catches_keys_cleared_in_their_own_step(model):
     # a token loop whose step clears the argmax keys that it fills itself
     planted(model, "--plant-own-keys")
+
+
+def test_model_catches_a_reader_that_nothing_waits_for(model):
+    # a workgroup without rows in a layer that reads the layer's input
+    planted(model, "--plant-idle-reader")
 
 
 def planted(model, mistake):
