@@ -28,9 +28,10 @@ constexpr int kMfmaBatch = 8;
 // pass on the matrix cores, 1195 on the vector units.  Against the matrix-core
 // engine the vector-unit pass took 4.35 ms to 5.0 for all 32 layers, both
 // before the residual rows had owners.  Dense models take that engine from
-// batch kMultiSeq + 1 on, or from kBatchedFrom where the LDS cannot hold the
-// shared pass's vectors beside its area (one sequence per pass: 5.61 ms at
-// batch 2).  A mixture of experts keeps the GEMV path below kMfmaBatch (its
+// the batch on that does not share a pass: kMultiSeq + 1, 3 with many heads
+// (lds_layout_for), or kBatchedFrom where the LDS cannot hold the vectors of
+// two sequences beside its area (one sequence per pass: 5.61 ms at batch 2).  A
+// mixture of experts keeps the GEMV path below kMfmaBatch (its
 // experts are chosen per token on that path).
 constexpr int kMultiSeq = 4;
 constexpr int kBatchedFrom = 2;
